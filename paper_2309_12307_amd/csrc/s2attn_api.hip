@@ -227,6 +227,7 @@ s2::KArgs make_kargs(const s2attn_params* p) {
   a.shifted_from = shifted_from(p, a.shift);
   a.split = (p->wrap_variant == S2ATTN_WRAP_SPLIT && a.shift > 0) ? p->G - a.shift : p->G;
   a.mixed = kv_heads_mixed(p->H, p->Hkv, a.shifted_from) ? 1 : 0;
+  a.parts = a.mixed ? 2 : 1;
   // the kernels built for partial tiles also take rows narrower than the 128-element tile (D = 64)
   a.ragged = (p->dtype == S2ATTN_BF16 && (p->D != 128 || p->G % 128 != 0 || a.shift % 64 != 0 ||
                                           (a.split < p->G && a.split % 128 != 0))) ? 1 : 0;
@@ -301,7 +302,15 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
   int ds_heads = 0;
   if (p->bwd_algo == S2ATTN_BWD_STORED_DS) ds_heads = ds_heads_per_pass(p, p->workspace_bytes - basic);
   mark(0);
-  if (s2::launch_delta(a, p->dtype, st) != 0) return S2ATTN_ERR_LAUNCH;
+  if (p->dtype == S2ATTN_F32) {   // one launch, delta included
+    mark(1);
+    if (s2::launch_bwd_f32(a, st) != 0) return S2ATTN_ERR_LAUNCH;
+    mark(2);
+    if (a.mixed && s2::launch_combine_partials(a, p->dtype, st) != 0) return S2ATTN_ERR_LAUNCH;
+    mark(3);
+    return S2ATTN_OK;
+  }
+  if (s2::launch_delta_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
   mark(1);
   if (ds_heads > 0) {
     // kv heads in passes of ds_heads: dK/dV kernel (stores dS), then dQ from the stored dS
@@ -316,11 +325,9 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
     mark(3);
     return S2ATTN_OK;
   }
-  rc = p->dtype == S2ATTN_F32 ? s2::launch_bwd_dkdv_f32(a, st) : s2::launch_bwd_dkdv_bf16(a, st);
-  if (rc != 0) return S2ATTN_ERR_LAUNCH;
+  if (s2::launch_bwd_dkdv_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
   mark(2);
-  rc = p->dtype == S2ATTN_F32 ? s2::launch_bwd_dq_f32(a, st) : s2::launch_bwd_dq_bf16(a, st);
-  if (rc != 0) return S2ATTN_ERR_LAUNCH;
+  if (s2::launch_bwd_dq_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
   if (a.mixed && s2::launch_combine_partials(a, p->dtype, st) != 0) return S2ATTN_ERR_LAUNCH;
   mark(3);
   return S2ATTN_OK;

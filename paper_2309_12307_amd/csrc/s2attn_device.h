@@ -18,7 +18,7 @@ struct KArgs {
   void* dq; void* dk; void* dv;
   float* delta;                              // (B,H,N) fp32
   float* lse2;                               // (B,H,N) fp32: lse * log2(e), written by the pre-pass
-  float* dkv_partial;                        // fp32 [2 tensors][2 classes][B,N,Hkv,D] or null
+  float* dkv_partial;                        // fp32 [dk, dv][parts][B,N,Hkv,D] or null
   void* ds_spill;                            // bf16 dS tiles handed from the dK/dV kernel to the dQ kernel, or null
   int c_begin, c_count;                      // kv heads [c_begin, c_begin + c_count) of this launch (spill path)
   TStride sq, sk, sv, sdq, sdk, sdv;         // q, k, v and their gradients may be strided views
@@ -29,6 +29,7 @@ struct KArgs {
   int shifted_from;                          // heads >= shifted_from use the shifted partition
   int split;                                 // Variant 2: rows [0,split) | [split,G) of the wrap group; G = off
   int mixed;                                 // some kv head serves both head classes
+  int parts;                                 // pieces the query heads of a kv head are cut into for dK/dV
   int ragged;                                // bf16 path: G % 128 != 0, shift % 64 != 0 or a Variant 2 split that
                                              // is not a multiple of 128 (partial tiles, wrap point inside a tile)
   float scale;                               // softmax scale
@@ -83,6 +84,69 @@ __device__ __forceinline__ void decode_slot(int slot, int T, int il, int& y, int
   const int within = slot - chunk * span;
   rank = __builtin_amdgcn_readfirstlane(within / il);
   y = chunk * il + (within - rank * il);
+}
+
+// Block -> (sequence, rank) when a launch has n_seq tile sequences: XCD x (block ids go round
+// the eight XCDs) walks sequences [x n_seq / 8, (x + 1) n_seq / 8), so that neighbours, which
+// share K and V (or Q and dO), meet in one L2, and no XCD has more than one sequence more than
+// another.  False: the block has no tile (sequence counts are padded to a multiple of il).
+__device__ __forceinline__ bool decode_block(int block, int T, int il, int n_seq, int& seq, int& rank) {
+  const int xcd = block & 7;
+  int y;
+  decode_slot(block >> 3, T, il, y, rank);
+  const int each = n_seq >> 3, more = n_seq & 7;
+  seq = __builtin_amdgcn_readfirstlane(xcd * each + min(xcd, more) + y);
+  rank = __builtin_amdgcn_readfirstlane(rank);
+  return __builtin_amdgcn_readfirstlane(y) < each + (xcd < more ? 1 : 0);
+}
+
+// Sequence number -> (batch, head, group), query heads of one (kv head, group) next to each other.
+struct HeadPos {
+  int b, c, h, g;
+};
+__device__ __forceinline__ HeadPos head_of_seq(const KArgs& a, int seq) {
+  HeadPos p;
+  const int NG = __builtin_amdgcn_readfirstlane(a.N / a.G);
+  int t = __builtin_amdgcn_readfirstlane(seq / a.r);
+  const int hr = seq - t * a.r;
+  int u = __builtin_amdgcn_readfirstlane(t / NG);
+  p.g = t - u * NG;
+  p.b = __builtin_amdgcn_readfirstlane(u / a.Hkv);
+  p.c = u - p.b * a.Hkv;
+  p.h = p.c * a.r + hr;
+  return p;
+}
+
+// The same for dK/dV: (batch, kv head, group, part of the kv head's query heads).
+struct KvPos {
+  int b, c, g, part;
+};
+__device__ __forceinline__ KvPos kv_of_seq(const KArgs& a, int seq) {
+  KvPos p;
+  const int NG = __builtin_amdgcn_readfirstlane(a.N / a.G);
+  int t = __builtin_amdgcn_readfirstlane(seq / a.parts);
+  p.part = seq - t * a.parts;
+  int u = __builtin_amdgcn_readfirstlane(t / NG);
+  p.g = t - u * NG;
+  p.b = __builtin_amdgcn_readfirstlane(u / a.Hkv);
+  p.c = u - p.b * a.Hkv;
+  return p;
+}
+
+// Query heads [h_lo, h_lo + n) of part `part` of kv head c, all of one class, and their shift.
+// A kv head with both classes gives the first parts / 2 parts to the unshifted heads (so parts
+// is at least 2 there); a part may be empty.
+__device__ __forceinline__ void part_heads(const KArgs& a, int c, int part, int& h_lo, int& n, int& shift) {
+  int lo = c * a.r, hi = lo + a.r, p = part, np = a.parts;
+  const int f = min(max(a.shifted_from, lo), hi);
+  const bool both = f > lo && f < hi;
+  if (both) {
+    const int n0 = np / 2;
+    if (p < n0) { hi = f; np = n0; } else { lo = f; p -= n0; np -= n0; }
+  }
+  h_lo = __builtin_amdgcn_readfirstlane(lo + (hi - lo) * p / np);
+  n = __builtin_amdgcn_readfirstlane(lo + (hi - lo) * (p + 1) / np - h_lo);
+  shift = lo >= a.shifted_from ? a.shift : 0;
 }
 
 // ---- dS hand-over between the two backward kernels (tile-aligned shapes only).

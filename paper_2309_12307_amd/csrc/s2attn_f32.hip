@@ -1,426 +1,485 @@
-// fp32 S2-Attn kernels (forward, delta pre-pass, dK/dV, dQ) for gfx950.
+// fp32 S2-Attn kernels (forward; backward) for gfx950 on the fp32 matrix instruction
+// v_mfma_f32_16x16x4_f32: fp32 operands, fp32 products and sums, twice the rate of the vector
+// unit's fp32 fma.  Any even group size and any shift (partial tiles are masked); the shift and
+// the grouping of LongLoRA Algorithm 1 are row-address arithmetic only (run_token).
 //
-// Plain LDS-tiled fp32 FMA kernels: every product and sum is fp32, so this mode
-// serves the tight-tolerance configuration (LongLoRA Section 3.2 / Algorithm 1 at
-// small shapes) and arbitrary even group sizes (partial tiles are masked).
-// The shift and the grouping are pure row-address arithmetic (token_of); no rolled
-// copy of q, k, v or o exists anywhere.
+// What bounds them: the matrix unit (256 flop per clock and CU).  An instruction takes 32
+// cycles, so LDS traffic, the softmax and the staging are all small beside it, and the layout
+// is chosen for few instructions per MFMA: every LDS operand is a 16-byte read that feeds four
+// MFMAs, and no accumulator is ever moved between lanes.
+//
+// Lane l: c16 = l % 16, q4 = l / 16.  Operand layout of the instruction: A row c16, B column
+// c16, contraction slot q4; C column c16, register v holds row 4 q4 + v.
+//   row-major operand (contraction over d): a lane reads X[row c16][16 i + 4 q4 .. +3] and
+//     element e feeds MFMA e of the four, so slot q4 of that MFMA is d = 16 i + 4 q4 + e; the
+//     other operand is loaded with the same pairing.
+//   accumulator fed back (P, dS): register v is the B operand of the MFMA whose slot q4 is row
+//     4 q4 + v.  The matching A operand is X[4 q4 + v][64 j + 4 c16 .. +3]: element e feeds the
+//     MFMA whose A row c16 is d = 64 j + 4 c16 + e, and C register w of accumulator (j, e) is
+//     d = 64 j + 16 q4 + 4 w + e: a lane ends with 16 consecutive d per j and stores float4s.
+// Both reads are free of bank conflicts with the sixteen-byte chunks of a row permuted by
+// chunk ^ (row & 7).  Tiles have 32 rows, two LDS stages, filled by direct global -> LDS loads.
+//
+// N = 4096, H = 8, D = 128, G = 1024, forward + backward: plain fp32 fma kernels with a pre-pass
+// for delta took 2890 us (10 TFLOP/s of the 14 D flops per pair), these 388 us (78; executed 100
+// of the 153 TFLOP/s that a library fp32 product of 8192^3 reaches).  N = 256, H = 4, D = 64,
+// G = 64: 119 -> 19 us, of which the two kernels take 7 and 13.
+#include "s2attn_bf16_common.h"
 #include "s2attn_device.h"
 #include "s2attn_launch.h"
 
 namespace s2 {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int BN = 64;   // keys per tile
-constexpr int SLD = 65;  // leading dimension of score tiles in LDS
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Loads rows [i0, i0+ROWS) of group g (in-group order) of one head into LDS,
-// zero-filling rows past the end of the group.
-template <int ROWS, int D>
-__device__ __forceinline__ void load_tile(float* dst, const float* src, const TStride& st, int b, int head,
-                                          int g, int i0, int s, int N, int G) {
-  constexpr int LD = D + 4;
-  constexpr int C4 = D / 4;
-  for (int idx = threadIdx.x; idx < ROWS * C4; idx += kThreads) {
-    int row = idx / C4, c4 = idx % C4;
-    int i = i0 + row;
-    float4 val = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (i < G) {
-      int tok = token_of(g * G + i, s, N);
-      val = *reinterpret_cast<const float4*>(src + row_off(st, b, tok, head) + 4 * c4);
+constexpr int kTile = 32;     // rows of a staged tile
+constexpr int kWgRows = 64;   // rows a workgroup owns: 16 per wave
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Sum / maximum over the four lanes that share a column (lanes c16 + 16 q4).
+__device__ __forceinline__ float sum_cols(float x) {
+  x += __shfl_xor(x, 16);
+  return x + __shfl_xor(x, 32);
+}
+__device__ __forceinline__ float max_cols(float x) {
+  x = fmaxf(x, __shfl_xor(x, 16));
+  return fmaxf(x, __shfl_xor(x, 32));
+}
+
+template <int D>
+struct Lanes {
+  static constexpr int kRow = D * 4;             // bytes of a tile row
+  static constexpr int kTileBytes = kTile * kRow;
+  int rm[2];   // row-major operand: byte offset for even / odd i, + 128 (i / 2)
+  int tr[4];   // transposed operand of register v, + 256 j
+  int st_row;  // staging: tile row of this lane's first 16 bytes, and its chunk
+  int st_chunk;
+
+  __device__ __forceinline__ void init(int lane, int w) {
+    const int c16 = lane & 15, q4 = lane >> 4;
+    rm[0] = c16 * kRow + ((q4 ^ (c16 & 7)) << 4);
+    rm[1] = c16 * kRow + (((4 + q4) ^ (c16 & 7)) << 4);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = 4 * q4 + v;
+      tr[v] = row * kRow + ((c16 ^ (row & 7)) << 4);
     }
-    *reinterpret_cast<float4*>(dst + row * LD + 4 * c4) = val;
+    constexpr int kChunks = D / 4;               // 16-byte chunks of a row: 16 or 32
+    constexpr int kRowsPer = 64 / kChunks;       // rows one wave instruction fills: 4 or 2
+    st_row = w * kRowsPer + lane / kChunks;
+    st_chunk = (lane % kChunks) ^ (st_row & 7);
+  }
+
+  // X[16 RB + c16][16 i + 4 q4 ..]
+  template <int RB>
+  __device__ __forceinline__ f32x4 row(const char* tile, int i) const {
+    return *reinterpret_cast<const f32x4*>(tile + rm[i & 1] + 16 * RB * kRow + 128 * (i >> 1));
+  }
+  // X[16 RB + 4 q4 + v][64 j + 4 c16 ..]
+  template <int RB>
+  __device__ __forceinline__ f32x4 col(const char* tile, int v, int j) const {
+    return *reinterpret_cast<const f32x4*>(tile + tr[v] + 16 * RB * kRow + 256 * j);
+  }
+
+  // Stages rows i0 .. i0 + 31 of a run (clamped to its last row) of one head.
+  __device__ __forceinline__ void stage(const KArgs& a, const Run& run, int s, const void* src, const TStride& st,
+                                        int b, int head, int i0, uint32_t lds, int w) const {
+    constexpr int kStep = 4 * (64 / (D / 4));    // rows the four waves fill together: 16 or 8
+#pragma unroll
+    for (int p = 0; p < kTile / kStep; ++p) {
+      const int tok = run_token(a, run, i0 + p * kStep + st_row, s);
+      dma16(static_cast<const char*>(src) + row_off(st, b, tok, head) * 4 + (st_chunk << 4), lds + (p * 4 + w) * 1024);
+    }
+  }
+};
+
+// acc[RB] += rows of the tile (16 RB + c16) against the wave's own 16 rows held in `own`.
+template <int D>
+__device__ __forceinline__ void scores(f32x4 (&acc)[2], const char* tile, const Lanes<D>& ln, const f32x4 (&own)[D / 16]) {
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i) {
+    const f32x4 x0 = ln.template row<0>(tile, i), x1 = ln.template row<1>(tile, i);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      acc[0] = mfma4(x0[e], own[i][e], acc[0]);
+      acc[1] = mfma4(x1[e], own[i][e], acc[1]);
+    }
   }
 }
 
-// acc[a][b] = sum_d A[(ty+16a)][d] * Bm[(tx+16b)][d]   (A: RA*16 rows, Bm: 64 rows)
-template <int RA, int D>
-__device__ __forceinline__ void tile_nt(float (&acc)[RA][4], const float* A, const float* Bm, int ty, int tx) {
-  constexpr int LD = D + 4;
+// acc[j][e] += X^T W for the 32 rows of a tile: W = P or dS as it stands in the accumulators.
+template <int D>
+__device__ __forceinline__ void accumulate(f32x4 (&acc)[D / 64][4], const char* tile, const Lanes<D>& ln, const f32x4 (&wt)[2]) {
 #pragma unroll
-  for (int a = 0; a < RA; ++a)
+  for (int v = 0; v < 4; ++v)
 #pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = 0.f;
-  for (int d = 0; d < D; d += 4) {
-    float4 av[RA], bv[4];
+    for (int j = 0; j < D / 64; ++j) {
+      const f32x4 x0 = ln.template col<0>(tile, v, j), x1 = ln.template col<1>(tile, v, j);
 #pragma unroll
-    for (int a = 0; a < RA; ++a) av[a] = *reinterpret_cast<const float4*>(A + (ty + 16 * a) * LD + d);
+      for (int e = 0; e < 4; ++e) acc[j][e] = mfma4(x0[e], wt[0][v], acc[j][e]);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) bv[b] = *reinterpret_cast<const float4*>(Bm + (tx + 16 * b) * LD + d);
+      for (int e = 0; e < 4; ++e) acc[j][e] = mfma4(x1[e], wt[1][v], acc[j][e]);
+    }
+}
+
+// The wave's own 16 rows as B operand: X[row][16 i + 4 q4 ..] straight from global memory.
+template <int D>
+__device__ __forceinline__ void load_own(f32x4 (&own)[D / 16], const void* src, size_t off, int q4) {
+  const float* p = static_cast<const float*>(src) + off + 4 * q4;
 #pragma unroll
-    for (int a = 0; a < RA; ++a)
+  for (int i = 0; i < D / 16; ++i) own[i] = *reinterpret_cast<const f32x4*>(p + 16 * i);
+}
+
+// Stores the accumulators of the lane's row (column c16 of C): 16 consecutive d per j.
+template <int D>
+__device__ __forceinline__ void store_row(float* dst, const f32x4 (&acc)[D / 64][4], float mul, int q4) {
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
-        acc[a][b] += av[a].x * bv[b].x + av[a].y * bv[b].y + av[a].z * bv[b].z + av[a].w * bv[b].w;
-  }
+  for (int j = 0; j < D / 64; ++j)
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      *reinterpret_cast<float4*>(dst + 64 * j + 16 * q4 + 4 * w) =
+          make_float4(acc[j][0][w] * mul, acc[j][1][w] * mul, acc[j][2][w] * mul, acc[j][3][w] * mul);
 }
 
 // ---------------------------------------------------------------------------
-// Forward: one block per (query tile of 64 rows, group, batch*head).
+// Forward.  A workgroup (4 waves) owns 64 query rows of one causal run, a wave 16 of them
+// (queries on C columns, keys on registers): S^T = K Q^T, online softmax, O^T += V^T P^T.
+// 64 rows and not 128: at D = 128 two such workgroups share a CU's LDS (64 KB each), and a
+// layer of a few hundred tokens still spreads over the chip.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(kThreads) fwd_f32_kernel(KArgs a) {
-  constexpr int BM = 64, LD = D + 4, DV = D / 64;
-  __shared__ float Qs[BM * LD];
-  __shared__ float Ks[BN * LD];
-  __shared__ float Vs[BN * LD];
-  __shared__ float Ss[BM * SLD];
-  __shared__ float row_m[BM], row_l[BM], row_alpha[BM];
+__global__ void __launch_bounds__(256, 2) fwd_f32_kernel(KArgs a, int T, int il, int n_seq) {
+  using L = Lanes<D>;
+  __shared__ __attribute__((aligned(1024))) char smem[4 * L::kTileBytes];   // [stage][K, V]
 
-  const int qt = blockIdx.x, g = blockIdx.y;
-  const int b = blockIdx.z / a.H, h = blockIdx.z % a.H;
-  const int c = h / a.r;
-  const int s = shift_of_head(a, h);
-  const int split = split_of_group(a, g, s);
-  const int i0 = qt * BM;
-  const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
-  const float* q = static_cast<const float*>(a.q);
-  const float* k = static_cast<const float*>(a.k);
-  const float* v = static_cast<const float*>(a.v);
+  const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
+  const int c16 = lane & 15, q4 = lane >> 4;
+  int seq, rank;
+  if (!decode_block(blockIdx.x, T, il, n_seq, seq, rank)) return;
+  const HeadPos at = head_of_seq(a, seq);
+  const int s = uni(shift_of_head(a, at.h));
+  Run run;
+  int qt = T - 1 - rank;
+  if (!run_of_tile(a, at.g, s, kWgRows, qt, run)) return;
+  run.p0 = uni(run.p0); run.len = uni(run.len);
+  const int i0 = uni(qt * kWgRows);
+  const int qw0 = i0 + 16 * w, qrow = qw0 + c16;
+  const int tok = run_token(a, run, qrow, s);
+  const float c2 = a.scale_log2;
 
-  load_tile<BM, D>(Qs, q, a.sq, b, h, g, i0, s, a.N, a.G);
-  if (tid < BM) { row_m[tid] = -1e30f; row_l[tid] = 0.f; }
-  float o[4][DV][4];
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int e = 0; e < DV; ++e)
-#pragma unroll
-      for (int y = 0; y < 4; ++y) o[x][e][y] = 0.f;
+  L ln;
+  ln.init(lane, w);
+  const uint32_t base = lds_addr(smem);
+  auto issue_tile = [&](int n) __attribute__((always_inline)) {
+    const uint32_t dst = base + (n & 1) * 2 * L::kTileBytes;
+    ln.stage(a, run, s, a.k, a.sk, at.b, at.c, n * kTile, dst, w);
+    ln.stage(a, run, s, a.v, a.sv, at.b, at.c, n * kTile, dst + L::kTileBytes, w);
+  };
+  issue_tile(0);
+  f32x4 qf[D / 16];
+  load_own<D>(qf, a.q, row_off(a.sq, at.b, tok, at.h), q4);
 
-  const int jt_first = (i0 >= split ? split : 0) / BN;
-  for (int jt = jt_first; jt <= qt; ++jt) {
-    const int j0 = jt * BN;
+  f32x4 o[D / 64][4];
+#pragma unroll
+  for (int j = 0; j < D / 64; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[j][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;    // scaled (base 2) row maximum; this lane's part of the row sum
+
+  const int n_tiles = uni((min(i0 + kWgRows, run.len) - 1) / kTile + 1);
+  for (int n = 0; n < n_tiles; ++n) {
+    wait_vmcnt0();
     __syncthreads();
-    load_tile<BN, D>(Ks, k, a.sk, b, c, g, j0, s, a.N, a.G);
-    load_tile<BN, D>(Vs, v, a.sv, b, c, g, j0, s, a.N, a.G);
-    __syncthreads();
-    float acc[4][4];
-    tile_nt<4, D>(acc, Qs, Ks, ty, tx);
+    if (n + 1 < n_tiles) issue_tile(n + 1);
+    const int j0 = n * kTile;
+    if (j0 > qw0 + 15 || qw0 >= run.len) continue;   // wholly after this wave's queries, or no query at all
+    const char* Ks = smem + (n & 1) * 2 * L::kTileBytes;
+    const char* Vs = Ks + L::kTileBytes;
+    f32x4 sc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    scores<D>(sc, Ks, ln, qf);
+    const bool masked = j0 + kTile - 1 > qw0;
+    float mx = -INFINITY;
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int y = 0; y < 4; ++y) {
-        int i = i0 + ty + 16 * x, j = j0 + tx + 16 * y;
-        int lo = i >= split ? split : 0;
-        bool vis = (j <= i) && (j >= lo);
-        Ss[(ty + 16 * x) * SLD + tx + 16 * y] = vis ? acc[x][y] * a.scale_log2 : -INFINITY;
+      for (int v = 0; v < 4; ++v) {
+        float x = sc[kb][v] * c2;
+        if (masked && j0 + 16 * kb + 4 * q4 + v > qrow) x = -INFINITY;
+        sc[kb][v] = x;
+        mx = fmaxf(mx, x);
       }
-    __syncthreads();
-    {  // online softmax: 4 threads per row
-      int row = tid / 4, part = tid % 4;
-      float mx = -INFINITY;
+    mx = max_cols(mx);
+    // the first tile holds key 0, which every row sees, so the maximum is finite from there on
+    if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = exp2f(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
 #pragma unroll
-      for (int x = 0; x < 16; ++x) mx = fmaxf(mx, Ss[row * SLD + part + 4 * x]);
-      mx = fmaxf(mx, __shfl_xor(mx, 1));
-      mx = fmaxf(mx, __shfl_xor(mx, 2));
-      float m_old = row_m[row];
-      float m_new = fmaxf(m_old, mx);
-      float sum = 0.f;
+      for (int j = 0; j < D / 64; ++j)
 #pragma unroll
-      for (int x = 0; x < 16; ++x) {
-        float p = exp2f(Ss[row * SLD + part + 4 * x] - m_new);
-        Ss[row * SLD + part + 4 * x] = p;
-        sum += p;
-      }
-      sum += __shfl_xor(sum, 1);
-      sum += __shfl_xor(sum, 2);
-      if (part == 0) {
-        float alpha = exp2f(m_old - m_new);
-        row_alpha[row] = alpha;
-        row_l[row] = row_l[row] * alpha + sum;
-        row_m[row] = m_new;
-      }
+        for (int e = 0; e < 4; ++e) o[j][e] *= alpha;
     }
-    __syncthreads();
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      float al = row_alpha[ty + 16 * x];
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int e = 0; e < DV; ++e)
+      for (int v = 0; v < 4; ++v) {
+        sc[kb][v] = exp2f(sc[kb][v] - m_run);
+        l_run += sc[kb][v];
+      }
+    accumulate<D>(o, Vs, ln, sc);
+  }
+
+  const float l_tot = sum_cols(l_run);
+  if (qrow >= run.len) return;
+  store_row<D>(static_cast<float*>(a.o) + row_off(a.so, at.b, tok, at.h), o, 1.f / l_tot, q4);
+  if (q4 == 0) a.lse[((size_t)at.b * a.H + at.h) * a.N + tok] = (m_run + log2f(l_tot)) * kLn2;
+}
+
+// ---------------------------------------------------------------------------
+// Backward, one launch: the first n_kv blocks are dK/dV workgroups, the others dQ workgroups
+// (independent of each other, and a small layer fills the chip with neither alone).
+//   dK/dV: 64 keys of one kv head and part of its query heads (part_heads), a wave 16 keys on
+//     the C columns with K and V in registers; walks the 32-row query tiles from the end of
+//     the run to the diagonal, heads innermost.  S = Q K^T, dP - delta = dO V^T - delta,
+//     dV^T += dO^T P, dK^T += Q^T dS.
+//   dQ: 64 queries, a wave 16 of them; S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T.
+// delta_i = dO_i . O_i is formed here and not by a pre-pass: a dQ lane has its dO row in
+// registers anyway, and a dK/dV workgroup forms the 32 sums of the next tile (8 threads a row)
+// while the matrix unit works on the present one, which costs an O tile from L2 per query tile
+// of 16 k MFMA cycles.  A launch saved is what counts at the small sizes.
+// ---------------------------------------------------------------------------
+template <int D>
+__device__ __forceinline__ void bwd_dkdv_block(const KArgs& a, char* smem, float* rows_s, int block, int T, int il, int n_seq) {
+  using L = Lanes<D>;
+  const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
+  const int c16 = lane & 15, q4 = lane >> 4;
+  int seq, kt;
+  if (!decode_block(block, T, il, n_seq, seq, kt)) return;   // key tile 0 is the heaviest
+  const KvPos at = kv_of_seq(a, seq);
+  int h_lo, nheads, s;
+  part_heads(a, at.c, at.part, h_lo, nheads, s);
+  Run run;
+  if (!run_of_tile(a, at.g, s, kWgRows, kt, run)) return;
+  run.p0 = uni(run.p0); run.len = uni(run.len);
+  const int j0 = uni(kt * kWgRows);
+  const int kw0 = j0 + 16 * w, key = kw0 + c16;
+  const int tok = run_token(a, run, key, s);
+  const int it_first = j0 / kTile, it_last = uni((run.len - 1) / kTile);
+  const int n_iter = nheads * (it_last - it_first + 1);
+  const float c2 = a.scale_log2;
+
+  L ln;
+  ln.init(lane, w);
+  const uint32_t base = lds_addr(smem);
+  auto issue_tile = [&](int hh, int it, int stage) __attribute__((always_inline)) {
+    const uint32_t dst = base + stage * 2 * L::kTileBytes;
+    ln.stage(a, run, s, a.q, a.sq, at.b, h_lo + hh, it * kTile, dst, w);
+    ln.stage(a, run, s, a.dout, a.so, at.b, h_lo + hh, it * kTile, dst + L::kTileBytes, w);
+  };
+  // row terms of a tile: thread -> (row tid / 8, every eighth float4 of it)
+  f32x4 ov[D / 32], gv[D / 32];
+  float lse = 0.f;
+  auto load_rows = [&](int hh, int it) __attribute__((always_inline)) {
+    const int t = run_token(a, run, it * kTile + (tid >> 3), s);
+    const size_t off = row_off(a.so, at.b, t, h_lo + hh) + 4 * (tid & 7);
 #pragma unroll
-        for (int y = 0; y < 4; ++y) o[x][e][y] *= al;
+    for (int k = 0; k < D / 32; ++k) {
+      ov[k] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(a.o) + off + 32 * k);
+      gv[k] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(a.dout) + off + 32 * k);
     }
-    for (int j = 0; j < BN; ++j) {
-      float4 vv[DV];
+    lse = a.lse[((size_t)at.b * a.H + h_lo + hh) * a.N + t];
+  };
+  auto finish_rows = [&](int stage) __attribute__((always_inline)) {
+    float x = 0.f;
 #pragma unroll
-      for (int e = 0; e < DV; ++e) vv[e] = *reinterpret_cast<const float4*>(Vs + j * LD + 4 * tx + 64 * e);
+    for (int k = 0; k < D / 32; ++k)
 #pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        float p = Ss[(ty + 16 * x) * SLD + j];
+      for (int e = 0; e < 4; ++e) x = fmaf(ov[k][e], gv[k][e], x);
+    x += __shfl_xor(x, 1);
+    x += __shfl_xor(x, 2);
+    x += __shfl_xor(x, 4);
+    if ((tid & 7) == 0) {
+      rows_s[stage * 2 * kTile + (tid >> 3)] = lse * kLog2e;
+      rows_s[stage * 2 * kTile + kTile + (tid >> 3)] = x;
+    }
+  };
+
+  f32x4 kf[D / 16], vf[D / 16], dk[D / 64][4], dv[D / 64][4];
+  load_own<D>(kf, a.k, row_off(a.sk, at.b, tok, at.c), q4);
+  load_own<D>(vf, a.v, row_off(a.sv, at.b, tok, at.c), q4);
 #pragma unroll
-        for (int e = 0; e < DV; ++e) {
-          o[x][e][0] += p * vv[e].x; o[x][e][1] += p * vv[e].y;
-          o[x][e][2] += p * vv[e].z; o[x][e][3] += p * vv[e].w;
+  for (int j = 0; j < D / 64; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { dk[j][e] = f32x4{0.f, 0.f, 0.f, 0.f}; dv[j][e] = dk[j][e]; }
+
+  int hh = 0, it = it_last;
+  if (n_iter > 0) {
+    issue_tile(0, it_last, 0);
+    load_rows(0, it_last);
+    finish_rows(0);
+  }
+  for (int n = 0; n < n_iter; ++n) {
+    const int stage = n & 1;
+    const int q0 = it * kTile;
+    if (++hh == nheads) { hh = 0; --it; }    // the next tile
+    wait_vmcnt0();
+    __syncthreads();
+    if (n + 1 < n_iter) {
+      issue_tile(hh, it, stage ^ 1);
+      load_rows(hh, it);
+    }
+    if (q0 + kTile - 1 >= kw0 && kw0 < run.len) {   // else: all queries of the tile before this wave's keys, or no key
+      const char* Qs = smem + stage * 2 * L::kTileBytes;
+      const char* dOs = Qs + L::kTileBytes;
+      const float* lse2 = rows_s + stage * 2 * kTile + 4 * q4;
+      f32x4 sc[2], dp[2];
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        sc[qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        dp[qb] = -*reinterpret_cast<const f32x4*>(lse2 + kTile + 16 * qb);
+      }
+      scores<D>(sc, Qs, ln, kf);
+      scores<D>(dp, dOs, ln, vf);
+      const bool masked = kw0 + 15 > q0 || q0 + kTile > run.len;
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse2 + 16 * qb);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int i = q0 + 16 * qb + 4 * q4 + v;
+          float p = exp2f(fmaf(sc[qb][v], c2, -l4[v]));
+          if (masked && (key > i || i >= run.len)) p = 0.f;
+          sc[qb][v] = p;
+          dp[qb][v] *= p;
         }
       }
+      accumulate<D>(dv, dOs, ln, sc);
+      accumulate<D>(dk, Qs, ln, dp);
     }
+    if (n + 1 < n_iter) finish_rows(stage ^ 1);
   }
-  __syncthreads();
-  float* out = static_cast<float*>(a.o);
-#pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    int row = ty + 16 * x, i = i0 + row;
-    if (i >= a.G) continue;
-    int tok = token_of(g * a.G + i, s, a.N);
-    float inv = 1.f / row_l[row];
-#pragma unroll
-    for (int e = 0; e < DV; ++e) {
-      float4 val = make_float4(o[x][e][0] * inv, o[x][e][1] * inv, o[x][e][2] * inv, o[x][e][3] * inv);
-      *reinterpret_cast<float4*>(out + row_off(a.so, b, tok, h) + 4 * tx + 64 * e) = val;
-    }
-    if (tx == 0)
-      a.lse[((size_t)b * a.H + h) * a.N + tok] = (row_m[row] + log2f(row_l[row])) * 0.6931471805599453f;
-  }
-}
 
-// ---------------------------------------------------------------------------
-// dK/dV: one block per (key tile of 64 rows, group, batch * kv head * class).
-// Loops over the query heads of the kv head that belong to the class (shifted or
-// not) and over query tiles at or below the diagonal.
-// ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(kThreads) bwd_dkdv_f32_kernel(KArgs a, int ncls) {
-  constexpr int BQ = 32, LD = D + 4, DV = D / 64;
-  __shared__ float Ks[BN * LD];
-  __shared__ float Vs[BN * LD];
-  __shared__ float Qs[BQ * LD];
-  __shared__ float dOs[BQ * LD];
-  __shared__ float Ps[BQ * SLD];
-  __shared__ float dSs[BQ * SLD];
-  __shared__ float row_lse[BQ], row_delta[BQ];
-
-  const int jt = blockIdx.x, g = blockIdx.y;
-  int z = blockIdx.z;
-  const int cls_slot = z % ncls; z /= ncls;
-  const int c = z % a.Hkv, b = z / a.Hkv;
-  // head range of this kv head in this class
-  int h_lo = c * a.r, h_hi = (c + 1) * a.r;
-  int cls;
-  if (ncls == 2) {
-    cls = cls_slot;
+  if (key >= run.len) return;
+  if (a.dkv_partial) {   // contiguous fp32 partial of this part, summed by the combine pass
+    const size_t elems = (size_t)a.B * a.N * a.Hkv * D;
+    float* dst = a.dkv_partial + at.part * elems + ((size_t)((size_t)at.b * a.N + tok) * a.Hkv + at.c) * D;
+    store_row<D>(dst, dk, a.scale, q4);
+    store_row<D>(dst + a.parts * elems, dv, 1.f, q4);
   } else {
-    cls = h_lo >= a.shifted_from ? 1 : 0;   // unmixed: every head of c is in one class
-  }
-  if (cls == 0) h_hi = min(h_hi, a.shifted_from); else h_lo = max(h_lo, a.shifted_from);
-  // (an empty class still writes its zero partial so that the combine pass can sum both)
-  const int s = cls ? a.shift : 0;
-  const int split = split_of_group(a, g, s);
-  const int j0 = jt * BN;
-  const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
-  const float* q = static_cast<const float*>(a.q);
-  const float* k = static_cast<const float*>(a.k);
-  const float* v = static_cast<const float*>(a.v);
-  const float* dout = static_cast<const float*>(a.dout);
-
-  load_tile<BN, D>(Ks, k, a.sk, b, c, g, j0, s, a.N, a.G);
-  load_tile<BN, D>(Vs, v, a.sv, b, c, g, j0, s, a.N, a.G);
-  float dk[4][DV][4], dv[4][DV][4];
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int e = 0; e < DV; ++e)
-#pragma unroll
-      for (int y = 0; y < 4; ++y) { dk[x][e][y] = 0.f; dv[x][e][y] = 0.f; }
-
-  const int n_qt = (a.G + BQ - 1) / BQ;
-  for (int h = h_lo; h < h_hi; ++h) {
-    for (int it = j0 / BQ; it < n_qt; ++it) {
-      const int i0 = it * BQ;
-      if (j0 + BN - 1 < split && i0 >= split) break;   // Variant 2: keys of the first block see no later rows
-      __syncthreads();
-      load_tile<BQ, D>(Qs, q, a.sq, b, h, g, i0, s, a.N, a.G);
-      load_tile<BQ, D>(dOs, dout, a.so, b, h, g, i0, s, a.N, a.G);
-      if (tid < BQ) {
-        int i = i0 + tid;
-        float l = 0.f, dl = 0.f;
-        if (i < a.G) {
-          int tok = token_of(g * a.G + i, s, a.N);
-          l = a.lse[((size_t)b * a.H + h) * a.N + tok];
-          dl = a.delta[((size_t)b * a.H + h) * a.N + tok];
-        }
-        row_lse[tid] = l * 1.4426950408889634f;
-        row_delta[tid] = dl;
-      }
-      __syncthreads();
-      float sacc[2][4], pacc[2][4];
-      tile_nt<2, D>(sacc, Qs, Ks, ty, tx);
-      tile_nt<2, D>(pacc, dOs, Vs, ty, tx);
-#pragma unroll
-      for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) {
-          int row = ty + 16 * x, col = tx + 16 * y;
-          int i = i0 + row, j = j0 + col;
-          int lo = i >= split ? split : 0;
-          bool vis = (j <= i) && (j >= lo) && (i < a.G);
-          float p = vis ? exp2f(sacc[x][y] * a.scale_log2 - row_lse[row]) : 0.f;
-          Ps[row * SLD + col] = p;
-          dSs[row * SLD + col] = p * (pacc[x][y] - row_delta[row]);
-        }
-      __syncthreads();
-      for (int i = 0; i < BQ; ++i) {
-        float4 dov[DV], qv[DV];
-#pragma unroll
-        for (int e = 0; e < DV; ++e) {
-          dov[e] = *reinterpret_cast<const float4*>(dOs + i * LD + 4 * tx + 64 * e);
-          qv[e] = *reinterpret_cast<const float4*>(Qs + i * LD + 4 * tx + 64 * e);
-        }
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-          float p = Ps[i * SLD + ty + 16 * x];
-          float ds = dSs[i * SLD + ty + 16 * x];
-#pragma unroll
-          for (int e = 0; e < DV; ++e) {
-            dv[x][e][0] += p * dov[e].x; dv[x][e][1] += p * dov[e].y;
-            dv[x][e][2] += p * dov[e].z; dv[x][e][3] += p * dov[e].w;
-            dk[x][e][0] += ds * qv[e].x; dk[x][e][1] += ds * qv[e].y;
-            dk[x][e][2] += ds * qv[e].z; dk[x][e][3] += ds * qv[e].w;
-          }
-        }
-      }
-    }
-  }
-  // store: directly, or as an fp32 partial of this class when kv heads are mixed
-  const size_t kv_elems = (size_t)a.B * a.N * a.Hkv * D;
-  float* dk_out = a.dkv_partial ? a.dkv_partial + (size_t)cls * kv_elems : static_cast<float*>(a.dk);
-  float* dv_out = a.dkv_partial ? a.dkv_partial + (size_t)(2 + cls) * kv_elems : static_cast<float*>(a.dv);
-#pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    int j = j0 + ty + 16 * x;
-    if (j >= a.G) continue;
-    int tok = token_of(g * a.G + j, s, a.N);
-    // fp32 partials of a mixed kv head are contiguous; final dk, dv may be strided views
-    const size_t cont = ((size_t)((size_t)b * a.N + tok) * a.Hkv + c) * D + 4 * tx;
-    const size_t base = a.dkv_partial ? cont : row_off(a.sdk, b, tok, c) + 4 * tx;
-    const size_t base_v = a.dkv_partial ? cont : row_off(a.sdv, b, tok, c) + 4 * tx;
-#pragma unroll
-    for (int e = 0; e < DV; ++e) {
-      *reinterpret_cast<float4*>(dk_out + base + 64 * e) =
-          make_float4(dk[x][e][0] * a.scale, dk[x][e][1] * a.scale, dk[x][e][2] * a.scale, dk[x][e][3] * a.scale);
-      *reinterpret_cast<float4*>(dv_out + base_v + 64 * e) =
-          make_float4(dv[x][e][0], dv[x][e][1], dv[x][e][2], dv[x][e][3]);
-    }
+    store_row<D>(static_cast<float*>(a.dk) + row_off(a.sdk, at.b, tok, at.c), dk, a.scale, q4);
+    store_row<D>(static_cast<float*>(a.dv) + row_off(a.sdv, at.b, tok, at.c), dv, 1.f, q4);
   }
 }
 
-// ---------------------------------------------------------------------------
-// dQ: one block per (query tile of 32 rows, group, batch*head).
-// ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(kThreads) bwd_dq_f32_kernel(KArgs a) {
-  constexpr int BQ = 32, LD = D + 4, DV = D / 64;
-  __shared__ float Ks[BN * LD];
-  __shared__ float Vs[BN * LD];
-  __shared__ float Qs[BQ * LD];
-  __shared__ float dOs[BQ * LD];
-  __shared__ float dSs[BQ * SLD];
-  __shared__ float row_lse[BQ], row_delta[BQ];
+__device__ __forceinline__ void bwd_dq_block(const KArgs& a, char* smem, int block, int T, int il, int n_seq) {
+  using L = Lanes<D>;
+  const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
+  const int c16 = lane & 15, q4 = lane >> 4;
+  int seq, rank;
+  if (!decode_block(block, T, il, n_seq, seq, rank)) return;
+  const HeadPos at = head_of_seq(a, seq);
+  const int s = uni(shift_of_head(a, at.h));
+  Run run;
+  int qt = T - 1 - rank;
+  if (!run_of_tile(a, at.g, s, kWgRows, qt, run)) return;
+  run.p0 = uni(run.p0); run.len = uni(run.len);
+  const int i0 = uni(qt * kWgRows);
+  const int qw0 = i0 + 16 * w, qrow = qw0 + c16;
+  const int tok = run_token(a, run, qrow, s);
+  const float c2 = a.scale_log2;
 
-  const int qt = blockIdx.x, g = blockIdx.y;
-  const int b = blockIdx.z / a.H, h = blockIdx.z % a.H;
-  const int c = h / a.r;
-  const int s = shift_of_head(a, h);
-  const int split = split_of_group(a, g, s);
-  const int i0 = qt * BQ;
-  const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
-  const float* q = static_cast<const float*>(a.q);
-  const float* k = static_cast<const float*>(a.k);
-  const float* v = static_cast<const float*>(a.v);
-  const float* dout = static_cast<const float*>(a.dout);
+  L ln;
+  ln.init(lane, w);
+  const uint32_t base = lds_addr(smem);
+  auto issue_tile = [&](int n) __attribute__((always_inline)) {
+    const uint32_t dst = base + (n & 1) * 2 * L::kTileBytes;
+    ln.stage(a, run, s, a.k, a.sk, at.b, at.c, n * kTile, dst, w);
+    ln.stage(a, run, s, a.v, a.sv, at.b, at.c, n * kTile, dst + L::kTileBytes, w);
+  };
+  issue_tile(0);
+  f32x4 qf[D / 16], gf[D / 16], dq[D / 64][4];
+  float delta = 0.f;
+  {
+    f32x4 of[D / 16];
+    load_own<D>(qf, a.q, row_off(a.sq, at.b, tok, at.h), q4);
+    load_own<D>(gf, a.dout, row_off(a.so, at.b, tok, at.h), q4);
+    load_own<D>(of, a.o, row_off(a.so, at.b, tok, at.h), q4);
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) delta = fmaf(of[i][e], gf[i][e], delta);
+    delta = sum_cols(delta);
+  }
+  const float lse2 = a.lse[((size_t)at.b * a.H + at.h) * a.N + tok] * kLog2e;
+#pragma unroll
+  for (int j = 0; j < D / 64; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dq[j][e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  load_tile<BQ, D>(Qs, q, a.sq, b, h, g, i0, s, a.N, a.G);
-  load_tile<BQ, D>(dOs, dout, a.so, b, h, g, i0, s, a.N, a.G);
-  if (tid < BQ) {
-    int i = i0 + tid;
-    float l = 0.f, dl = 0.f;
-    if (i < a.G) {
-      int tok = token_of(g * a.G + i, s, a.N);
-      l = a.lse[((size_t)b * a.H + h) * a.N + tok];
-      dl = a.delta[((size_t)b * a.H + h) * a.N + tok];
+  const int n_tiles = uni((min(i0 + kWgRows, run.len) - 1) / kTile + 1);
+  for (int n = 0; n < n_tiles; ++n) {
+    wait_vmcnt0();
+    __syncthreads();
+    if (n + 1 < n_tiles) issue_tile(n + 1);
+    const int j0 = n * kTile;
+    if (j0 > qw0 + 15 || qw0 >= run.len) continue;
+    const char* Ks = smem + (n & 1) * 2 * L::kTileBytes;
+    const char* Vs = Ks + L::kTileBytes;
+    f32x4 sc[2], dp[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      sc[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      dp[kb] = f32x4{-delta, -delta, -delta, -delta};
     }
-    row_lse[tid] = l * 1.4426950408889634f;
-    row_delta[tid] = dl;
+    scores<D>(sc, Ks, ln, qf);
+    scores<D>(dp, Vs, ln, gf);
+    const bool masked = j0 + kTile - 1 > qw0;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float p = exp2f(fmaf(sc[kb][v], c2, -lse2));
+        if (masked && j0 + 16 * kb + 4 * q4 + v > qrow) p = 0.f;
+        dp[kb][v] *= p;
+      }
+    accumulate<D>(dq, Ks, ln, dp);
   }
-  float dq[2][DV][4];
-#pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int e = 0; e < DV; ++e)
-#pragma unroll
-      for (int y = 0; y < 4; ++y) dq[x][e][y] = 0.f;
+  if (qrow >= run.len) return;
+  store_row<D>(static_cast<float*>(a.dq) + row_off(a.sdq, at.b, tok, at.h), dq, a.scale, q4);
+}
 
-  const int jt_first = (i0 >= split ? split : 0) / BN;
-  const int jt_last = min(i0 + BQ - 1, a.G - 1) / BN;
-  for (int jt = jt_first; jt <= jt_last; ++jt) {
-    const int j0 = jt * BN;
-    __syncthreads();
-    load_tile<BN, D>(Ks, k, a.sk, b, c, g, j0, s, a.N, a.G);
-    load_tile<BN, D>(Vs, v, a.sv, b, c, g, j0, s, a.N, a.G);
-    __syncthreads();
-    float sacc[2][4], pacc[2][4];
-    tile_nt<2, D>(sacc, Qs, Ks, ty, tx);
-    tile_nt<2, D>(pacc, dOs, Vs, ty, tx);
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int y = 0; y < 4; ++y) {
-        int row = ty + 16 * x, col = tx + 16 * y;
-        int i = i0 + row, j = j0 + col;
-        int lo = i >= split ? split : 0;
-        bool vis = (j <= i) && (j >= lo) && (i < a.G);
-        float p = vis ? exp2f(sacc[x][y] * a.scale_log2 - row_lse[row]) : 0.f;
-        dSs[row * SLD + col] = p * (pacc[x][y] - row_delta[row]);
-      }
-    __syncthreads();
-    for (int j = 0; j < BN; ++j) {
-      float4 kv[DV];
-#pragma unroll
-      for (int e = 0; e < DV; ++e) kv[e] = *reinterpret_cast<const float4*>(Ks + j * LD + 4 * tx + 64 * e);
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        float ds = dSs[(ty + 16 * x) * SLD + j];
-#pragma unroll
-        for (int e = 0; e < DV; ++e) {
-          dq[x][e][0] += ds * kv[e].x; dq[x][e][1] += ds * kv[e].y;
-          dq[x][e][2] += ds * kv[e].z; dq[x][e][3] += ds * kv[e].w;
-        }
-      }
-    }
-  }
-  float* out = static_cast<float*>(a.dq);
-#pragma unroll
-  for (int x = 0; x < 2; ++x) {
-    int i = i0 + ty + 16 * x;
-    if (i >= a.G) continue;
-    int tok = token_of(g * a.G + i, s, a.N);
-#pragma unroll
-    for (int e = 0; e < DV; ++e)
-      *reinterpret_cast<float4*>(out + row_off(a.sdq, b, tok, h) + 4 * tx + 64 * e) =
-          make_float4(dq[x][e][0] * a.scale, dq[x][e][1] * a.scale, dq[x][e][2] * a.scale, dq[x][e][3] * a.scale);
-  }
+template <int D>
+__global__ void __launch_bounds__(256, 2)
+bwd_f32_kernel(KArgs a, int n_kv, int T, int il_kv, int n_seq_kv, int il_q, int n_seq_q) {
+  __shared__ __attribute__((aligned(1024))) char smem[4 * Lanes<D>::kTileBytes];   // [stage][Q, dO] or [stage][K, V]
+  __shared__ __attribute__((aligned(16))) float rows_s[2 * 2 * kTile];             // [stage][lse * log2(e), delta]
+  if ((int)blockIdx.x < n_kv)
+    bwd_dkdv_block<D>(a, smem, rows_s, blockIdx.x, T, il_kv, n_seq_kv);
+  else
+    bwd_dq_block<D>(a, smem, blockIdx.x - n_kv, T, il_q, n_seq_q);
 }
 
 template <int D>
 int launch_fwd_t(const KArgs& a, hipStream_t st) {
-  dim3 grid((a.G + 63) / 64, a.N / a.G, a.B * a.H);
-  hipLaunchKernelGGL(fwd_f32_kernel<D>, grid, dim3(kThreads), 0, st, a);
+  const int T = ragged_tiles(a, kWgRows);
+  const Grid g = grid_of(T, a.B * a.H * (a.N / a.G), 64);
+  hipLaunchKernelGGL(fwd_f32_kernel<D>, dim3(g.blocks), dim3(256), 0, st, a, T, g.il, g.n_seq);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 template <int D>
-int launch_dkdv_t(const KArgs& a, hipStream_t st) {
-  const int ncls = a.mixed ? 2 : 1;
-  dim3 g1((a.G + 63) / 64, a.N / a.G, a.B * a.Hkv * ncls);
-  hipLaunchKernelGGL(bwd_dkdv_f32_kernel<D>, g1, dim3(kThreads), 0, st, a, ncls);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
-template <int D>
-int launch_dq_t(const KArgs& a, hipStream_t st) {
-  dim3 g2((a.G + 31) / 32, a.N / a.G, a.B * a.H);
-  hipLaunchKernelGGL(bwd_dq_f32_kernel<D>, g2, dim3(kThreads), 0, st, a);
+int launch_bwd_t(const KArgs& a, hipStream_t st) {
+  const int NG = a.N / a.G;
+  const int T = ragged_tiles(a, kWgRows);
+  const Grid kv = grid_of(T, a.B * a.Hkv * NG * a.parts, 64), q = grid_of(T, a.B * a.H * NG, 64);
+  hipLaunchKernelGGL(bwd_f32_kernel<D>, dim3(kv.blocks + q.blocks), dim3(256), 0, st, a, kv.blocks, T, kv.il, kv.n_seq,
+                     q.il, q.n_seq);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -430,12 +489,8 @@ int launch_fwd_f32(const KArgs& a, hipStream_t st) {
   return a.D == 64 ? launch_fwd_t<64>(a, st) : launch_fwd_t<128>(a, st);
 }
 
-int launch_bwd_dkdv_f32(const KArgs& a, hipStream_t st) {
-  return a.D == 64 ? launch_dkdv_t<64>(a, st) : launch_dkdv_t<128>(a, st);
-}
-
-int launch_bwd_dq_f32(const KArgs& a, hipStream_t st) {
-  return a.D == 64 ? launch_dq_t<64>(a, st) : launch_dq_t<128>(a, st);
+int launch_bwd_f32(const KArgs& a, hipStream_t st) {
+  return a.D == 64 ? launch_bwd_t<64>(a, st) : launch_bwd_t<128>(a, st);
 }
 
 }  // namespace s2
