@@ -108,7 +108,7 @@ typedef struct s2attn_params {
   void* dq;           /* backward only, overwritten */
   void* dk;           /* backward only, overwritten */
   void* dv;           /* backward only, overwritten */
-  void* workspace;    /* backward only: >= s2attn_bwd_workspace_bytes(...) bytes, 256-byte aligned */
+  void* workspace;    /* backward only: s2attn_bwd_workspace_bytes(...) bytes, 256-byte aligned */
   size_t workspace_bytes;
   int B, N, H, Hkv, D, G;
   int dtype;          /* S2ATTN_BF16 or S2ATTN_F32: element type of q,k,v,o,dout,dq,dk,dv */
@@ -139,10 +139,12 @@ typedef struct s2attn_params {
  * size when `backward` is non-zero).  Touches no GPU state. */
 S2ATTN_API int s2attn_check_args(const s2attn_params* p, int backward);
 
-/* Bytes of device workspace the backward needs, for the published defaults (shift G/2 on the
+/* Bytes of device workspace the backward wants, for the published defaults (shift G/2 on the
  * second half of the heads): the fp32 row term delta[b,h,t] = sum_d dout*o and a base-2 copy of
- * lse, plus fp32 partial dk/dv when a kv head serves both shifted and unshifted query heads
- * (odd Hkv). */
+ * lse, plus fp32 partial dk/dv when the query heads of a kv head are worked on in parts: always
+ * when one serves both shifted and unshifted query heads (odd Hkv), and where few kv heads would
+ * leave the chip idle otherwise.  It runs with less, down to the row terms and, for a kv head of
+ * both classes, two parts (16 * B * N * Hkv * D bytes). */
 S2ATTN_API size_t s2attn_bwd_workspace_bytes(int B, int N, int H, int Hkv, int D, int G, int dtype);
 
 /* Same for a parameter block (accounts for its shift rule and head sharding, which decide
@@ -180,10 +182,11 @@ S2ATTN_API int s2attn_bwd_ex(const s2attn_params* p, void* stream);
  * capture, tight serving loops, harnesses that forbid hipMalloc): s2attn_bwd_ex with the
  * workspace replaced by a device array of S2ATTN_STATIC_SCRATCH_BYTES that is part of the
  * library image (each GPU holds its own copy until the process ends).  p->workspace and
- * p->workspace_bytes are ignored; everything else, results included, is as in s2attn_bwd_ex.
+ * p->workspace_bytes are ignored; everything else is as in s2attn_bwd_ex on a workspace of that size
+ * (fewer parts of a kv head's query heads add up dk, dv in another order).
  * It always runs the recomputing backward (p->bwd_algo is ignored).
- * The call allocates nothing and frees nothing.  A problem whose
- * s2attn_bwd_workspace_bytes_ex (without stored dS) exceeds S2ATTN_STATIC_SCRATCH_BYTES
+ * The call allocates nothing and frees nothing.  A problem whose least workspace (see
+ * s2attn_bwd_workspace_bytes; without stored dS) exceeds S2ATTN_STATIC_SCRATCH_BYTES
  * (for MHA and even Hkv: B * H * N > 2097152 rows) is refused with S2ATTN_ERR_SCRATCH before anything is launched.
  * All calls on one GPU share that GPU's array: calls that may overlap in time on one GPU
  * (different streams, several host threads) race on it and must be serialised by the caller;

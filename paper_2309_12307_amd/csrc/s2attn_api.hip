@@ -47,10 +47,40 @@ bool kv_heads_mixed(int H, int Hkv, int from) {
 
 size_t delta_bytes(int B, int N, int H) { return round_up((size_t)B * H * N * sizeof(float), kAlign); }
 
-size_t workspace_bytes_for(int B, int N, int H, int Hkv, int D, bool mixed) {
-  size_t w = 2 * delta_bytes(B, N, H);   // delta and lse * log2(e)
-  if (mixed) w += round_up((size_t)4 * B * N * Hkv * D * sizeof(float), kAlign);
-  return w;
+// fp32 partial sums of dK and dV when the query heads of every kv head are cut into `parts`.
+size_t partial_bytes(int B, int N, int Hkv, int D, int parts) {
+  return parts > 1 ? round_up((size_t)2 * parts * B * N * Hkv * D * sizeof(float), kAlign) : 0;
+}
+
+// The least the backward can run with: delta and lse * log2(e), and two parts where a kv head
+// serves both head classes.
+size_t workspace_bytes_least(int B, int N, int H, int Hkv, int D, bool mixed) {
+  return 2 * delta_bytes(B, N, H) + partial_bytes(B, N, Hkv, D, mixed ? 2 : 1);
+}
+
+// Parts the dK/dV workgroups should cut the query heads of a kv head into.  Without cutting there
+// is one workgroup per 128 keys of a kv head, and with few kv heads most of the chip idles.  Two
+// workgroups per CU (512) are enough: they are dealt out heaviest first, so a CU gets one heavy and
+// one light one.  Each part costs a write and a read of 8 bytes per key element, so a part keeps
+// at least 1024 query rows (fp32, ten times the time per row: 256).  N = 8192, H = 32, Hkv = 1,
+// G = 2048: dK/dV 873 us with the two parts that the two head classes need, 273 us with 8.
+int parts_wanted(const s2attn_params* p, bool mixed) {
+  const int r = p->H / p->Hkv, least = mixed ? 2 : 1;
+  const long long groups = (long long)p->B * p->Hkv * (p->N / p->G) * ((p->G + 127) / 128);
+  const long long rows = (long long)r * p->G / (p->dtype == S2ATTN_F32 ? 256 : 1024);
+  const long long most = std::min<long long>(std::min<long long>((512 + groups - 1) / groups, rows), r);
+  int parts = 1;
+  for (int x = 2; x <= most; ++x)
+    if (r % x == 0) parts = x;
+  return std::max(parts, least);
+}
+
+// The largest number of parts, at most the one wanted, whose partial sums fit into `avail` bytes.
+int parts_that_fit(const s2attn_params* p, bool mixed, size_t avail) {
+  const int r = p->H / p->Hkv, least = mixed ? 2 : 1;
+  for (int x = parts_wanted(p, mixed); x > least; --x)
+    if (r % x == 0 && partial_bytes(p->B, p->N, p->Hkv, p->D, x) <= avail) return x;
+  return least;
 }
 
 // ---- stored-dS backward (tile-aligned bf16 shapes): the dK/dV kernel hands dS to the dQ
@@ -85,13 +115,18 @@ int ds_heads_per_pass(const s2attn_params* p, size_t avail) {
 size_t workspace_bytes_wanted(const s2attn_params* p) {
   const int shift = resolved_shift(p);
   const int from = shifted_from(p, shift);
-  size_t w = workspace_bytes_for(p->B, p->N, p->H, p->Hkv, p->D, kv_heads_mixed(p->H, p->Hkv, from));
+  const bool mixed = kv_heads_mixed(p->H, p->Hkv, from);
   if (p->bwd_algo == S2ATTN_BWD_STORED_DS && stored_ds_applies(p, shift, from)) {
     const size_t per_head = ds_bytes_per_kv_head(p);
     const size_t heads = std::max<size_t>(1, std::min<size_t>((size_t)p->Hkv, kDsSpillCap / per_head));
-    w += heads * per_head;
+    return workspace_bytes_least(p->B, p->N, p->H, p->Hkv, p->D, mixed) + heads * per_head;
   }
-  return w;
+  return 2 * delta_bytes(p->B, p->N, p->H) + partial_bytes(p->B, p->N, p->Hkv, p->D, parts_wanted(p, mixed));
+}
+
+// The shape fields make sense as far as the workspace sizes need it.
+bool shape_valid(const s2attn_params* p) {
+  return p->B > 0 && p->N > 0 && p->H > 0 && p->Hkv > 0 && p->D > 0 && p->G > 0 && p->H % p->Hkv == 0 && p->N % p->G == 0;
 }
 
 bool strides_ok(const long long (&st)[3], int B, int heads, int D, int align) {
@@ -170,7 +205,7 @@ int check_common(const s2attn_params* p, int backward) {
     }
     const int from = shifted_from(p, shift);
     const bool mixed = kv_heads_mixed(p->H, p->Hkv, from);
-    const size_t need = workspace_bytes_for(p->B, p->N, p->H, p->Hkv, p->D, mixed);
+    const size_t need = workspace_bytes_least(p->B, p->N, p->H, p->Hkv, p->D, mixed);
     if (!p->workspace || p->workspace_bytes < need) return S2ATTN_ERR_WORKSPACE;
     if ((reinterpret_cast<uintptr_t>(p->workspace) & (kAlign - 1)) != 0) return S2ATTN_ERR_ALIGN;
     if (p->bwd_algo == S2ATTN_BWD_STORED_DS) {
@@ -215,6 +250,7 @@ s2::KArgs make_kargs(const s2attn_params* p) {
   a.dout = p->dout; a.dq = p->dq; a.dk = p->dk; a.dv = p->dv;
   a.B = p->B; a.N = p->N; a.H = p->H; a.Hkv = p->Hkv; a.D = p->D; a.G = p->G;
   a.r = p->H / p->Hkv;
+  a.NG = p->N / p->G;
   a.sq = resolve_strides(p->q_strides, p->N, p->H, p->D);
   a.sk = resolve_strides(p->k_strides, p->N, p->Hkv, p->D);
   a.sv = resolve_strides(p->v_strides, p->N, p->Hkv, p->D);
@@ -227,12 +263,16 @@ s2::KArgs make_kargs(const s2attn_params* p) {
   a.shifted_from = shifted_from(p, a.shift);
   a.split = (p->wrap_variant == S2ATTN_WRAP_SPLIT && a.shift > 0) ? p->G - a.shift : p->G;
   a.mixed = kv_heads_mixed(p->H, p->Hkv, a.shifted_from) ? 1 : 0;
-  a.parts = a.mixed ? 2 : 1;
+  a.parts = 1;
   // the kernels built for partial tiles also take rows narrower than the 128-element tile (D = 64)
   a.ragged = (p->dtype == S2ATTN_BF16 && (p->D != 128 || p->G % 128 != 0 || a.shift % 64 != 0 ||
                                           (a.split < p->G && a.split % 128 != 0))) ? 1 : 0;
   a.c_begin = 0;
   a.c_count = p->Hkv;
+  a.by_r = s2::div_by(a.r);
+  a.by_NG = s2::div_by(a.NG);
+  a.by_parts = s2::div_by(a.parts);
+  a.by_c_count = s2::div_by(a.c_count);
   a.scale = p->scale > 0.f ? p->scale : 1.0f / std::sqrt((float)p->D);
   a.scale_log2 = a.scale * 1.4426950408889634f;
   return a;
@@ -265,10 +305,7 @@ size_t s2attn_bwd_workspace_bytes(int B, int N, int H, int Hkv, int D, int G, in
 }
 
 size_t s2attn_bwd_workspace_bytes_ex(const s2attn_params* p) {
-  if (!p || p->B <= 0 || p->N <= 0 || p->H <= 0 || p->Hkv <= 0 || p->D <= 0 || p->G <= 0 || p->H % p->Hkv != 0 ||
-      p->N % p->G != 0)
-    return 0;
-  return workspace_bytes_wanted(p);
+  return p && shape_valid(p) ? workspace_bytes_wanted(p) : 0;
 }
 
 int s2attn_fwd_ex(const s2attn_params* p, void* stream) {
@@ -290,15 +327,18 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
   s2::KArgs a = make_kargs(p);
   a.delta = static_cast<float*>(p->workspace);
   a.lse2 = reinterpret_cast<float*>(static_cast<char*>(p->workspace) + delta_bytes(p->B, p->N, p->H));
-  if (a.mixed)
-    a.dkv_partial = reinterpret_cast<float*>(static_cast<char*>(p->workspace) + 2 * delta_bytes(p->B, p->N, p->H));
+  const size_t rows = 2 * delta_bytes(p->B, p->N, p->H);
+  // the stored-dS backward writes its dS one kv head after the other and does not cut the heads
+  if (p->bwd_algo != S2ATTN_BWD_STORED_DS) a.parts = parts_that_fit(p, a.mixed != 0, p->workspace_bytes - rows);
+  a.by_parts = s2::div_by(a.parts);
+  if (a.parts > 1) a.dkv_partial = reinterpret_cast<float*>(static_cast<char*>(p->workspace) + rows);
   hipStream_t st = static_cast<hipStream_t>(stream);
   auto mark = [&](int i) {
     if (events && events[i]) (void)hipEventRecord(static_cast<hipEvent_t>(events[i]), st);
   };
   // stored-dS backward: only on request (check_common has made sure that the shape allows it
   // and that the workspace has room for the dS of at least one kv head beyond the row terms)
-  const size_t basic = workspace_bytes_for(p->B, p->N, p->H, p->Hkv, p->D, a.mixed != 0);
+  const size_t basic = workspace_bytes_least(p->B, p->N, p->H, p->Hkv, p->D, a.mixed != 0);
   int ds_heads = 0;
   if (p->bwd_algo == S2ATTN_BWD_STORED_DS) ds_heads = ds_heads_per_pass(p, p->workspace_bytes - basic);
   mark(0);
@@ -306,7 +346,7 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
     mark(1);
     if (s2::launch_bwd_f32(a, st) != 0) return S2ATTN_ERR_LAUNCH;
     mark(2);
-    if (a.mixed && s2::launch_combine_partials(a, p->dtype, st) != 0) return S2ATTN_ERR_LAUNCH;
+    if (a.parts > 1 && s2::launch_combine_partials(a, p->dtype, st) != 0) return S2ATTN_ERR_LAUNCH;
     mark(3);
     return S2ATTN_OK;
   }
@@ -318,6 +358,7 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
     for (int c0 = 0; c0 < p->Hkv; c0 += ds_heads) {
       a.c_begin = c0;
       a.c_count = std::min(ds_heads, p->Hkv - c0);
+      a.by_c_count = s2::div_by(a.c_count);
       if (s2::launch_bwd_dkdv_split_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
       if (c0 + ds_heads >= p->Hkv) mark(2);
       if (s2::launch_bwd_dq_spill_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
@@ -328,7 +369,7 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
   if (s2::launch_bwd_dkdv_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
   mark(2);
   if (s2::launch_bwd_dq_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
-  if (a.mixed && s2::launch_combine_partials(a, p->dtype, st) != 0) return S2ATTN_ERR_LAUNCH;
+  if (a.parts > 1 && s2::launch_combine_partials(a, p->dtype, st) != 0) return S2ATTN_ERR_LAUNCH;
   mark(3);
   return S2ATTN_OK;
 }
@@ -362,8 +403,11 @@ int s2attn_bwd_ex_static(const s2attn_params* p, void* stream) {
   local.bwd_algo = S2ATTN_BWD_RECOMPUTE;   // the stored-dS backward needs gigabytes of workspace
   // size check first: pure host arithmetic, nothing is looked up or launched for a problem
   // that does not fit
-  const size_t need = s2attn_bwd_workspace_bytes_ex(&local);
-  if (need > S2ATTN_STATIC_SCRATCH_BYTES) return S2ATTN_ERR_SCRATCH;
+  if (shape_valid(p)) {
+    const bool mixed = kv_heads_mixed(p->H, p->Hkv, shifted_from(p, resolved_shift(p)));
+    if (workspace_bytes_least(p->B, p->N, p->H, p->Hkv, p->D, mixed) > S2ATTN_STATIC_SCRATCH_BYTES)
+      return S2ATTN_ERR_SCRATCH;
+  }
   // the remaining argument errors do not depend on the workspace address
   local.workspace = reinterpret_cast<void*>(static_cast<uintptr_t>(kAlign));
   local.workspace_bytes = S2ATTN_STATIC_SCRATCH_BYTES;

@@ -194,55 +194,37 @@ __device__ __forceinline__ void dkdv_block(const DkdvTile& t, int mb, int q_firs
   mma_acc<1, DH>(fb, pq, dsq, dk_acc, dv_acc);
 }
 
-// RAGGED: G is not a multiple of 128 or the shift not of 64 -- tiles may be partial and
-// the wrap point may fall inside one, so every staged row finds its own token and the
-// padding rows of the last tile are masked.  The aligned instantiation carries none of it.
-// DH = 64 (only with RAGGED): the head dimension is 64 and the products skip the zero half.
-template <bool RAGGED, int DH = 128>
+// For the shapes the role-split kernel does not take: G not a multiple of 128, the shift not of
+// 64, or a head dimension of 64.  Tiles may be partial and the wrap point may fall inside one,
+// so every staged row finds its own token and the padding rows of the last tile are masked.
+// DH = 64: the head dimension is 64 and the products skip the zero half.
+template <int DH>
 __global__ void __launch_bounds__(256, 1)
-bwd_dkdv_bf16_kernel(KArgs a, int ncls, int T, int il, int n_rest) {
+bwd_dkdv_bf16_kernel(KArgs a, int T, Deal deal) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * kQTileBytes];            // [stage][Q,dO]
   __shared__ __attribute__((aligned(1024))) float rows_s[2][2][kQTileRows];        // [stage][lse * log2(e), delta]
 
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = thread_id(), lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g32 = lane >> 5, l32 = lane & 31;
 
-  // block -> (batch, kv head, class, group, key tile); heaviest key tiles (jt = 0) first
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  int y, jt;
-  decode_slot(slot, T, il, y, jt);
-  int rest = uni(y * 8 + xcd);
-  if (rest >= n_rest) return;
-  const int NG = uni(a.N / a.G);
-  const int gidx = uni(rest % NG); rest = uni(rest / NG);
-  const int cls_slot = uni(rest % ncls); rest = uni(rest / ncls);
-  const int c = uni(rest % a.Hkv);
-  const int b = uni(rest / a.Hkv);
-
-  int h_lo = c * a.r, h_hi = (c + 1) * a.r;
-  const int cls = ncls == 2 ? cls_slot : (h_lo >= a.shifted_from ? 1 : 0);
-  if (cls == 0) h_hi = min(h_hi, a.shifted_from); else h_lo = max(h_lo, a.shifted_from);
-  const int nheads = uni(max(h_hi - h_lo, 0));
-  h_lo = uni(h_lo);
-
-  const int s = uni(cls ? a.shift : 0);
-  // the causal run this block works in (see the forward kernel): the aligned kernel cuts the
-  // query range of a split wrap-around group at `split`, a multiple of the tile; the ragged
-  // one runs the two blocks as runs of their own
-  Run run{gidx * a.G, a.G};
-  int split = uni(split_of_group(a, gidx, s));
-  if constexpr (RAGGED) {
-    if (!run_of_tile(a, gidx, s, kQTileRows, jt, run)) return;
-    run.p0 = uni(run.p0); run.len = uni(run.len);
-    split = run.len;
-  }
+  // block -> (batch, kv head, part of its query heads, group, key tile); heaviest key tiles (jt = 0) first
+  int seq, jt;
+  if (!decode_block(block_id(), T, deal, seq, jt)) return;
+  const KvPos at = kv_of_seq(a, seq);
+  const int gidx = at.g, c = at.c, b = at.b;
+  int h_lo, nheads, s;
+  part_heads(a, c, at.part, h_lo, nheads, s);
+  // the causal run this block works in (the two blocks of a split wrap-around group are runs of
+  // their own)
+  Run run;
+  if (!run_of_tile(a, gidx, s, kQTileRows, jt, run)) return;
+  run.p0 = uni(run.p0); run.len = uni(run.len);
   const int j0 = jt * 128;
   const int kw0 = j0 + 32 * w;                       // first key of this wave
   const int key = kw0 + l32;
-  // query rows visible to this workgroup's keys: [j0, q_end)
-  const int q_end = uni((j0 < split) ? split : run.len);
+  // query rows visible to this workgroup's keys: [j0, run.len)
   const int it_begin = uni(j0 / kQTileRows);
-  const int nq = uni((q_end - j0 + kQTileRows - 1) / kQTileRows);
+  const int nq = uni((run.len - j0 + kQTileRows - 1) / kQTileRows);
   const int n_iter = nheads * nq;
   const float c2 = a.scale_log2;
 
@@ -259,52 +241,30 @@ bwd_dkdv_bf16_kernel(KArgs a, int ncls, int T, int il, int n_rest) {
     for (int st = 0; st < DH / 16; ++st) { kf[st] = ksrc[2 * st + g32]; vf[st] = -vsrc[2 * st + g32]; }
   }
 
-  // staging: wave w, pass p fills tile rows 16p + 4w .. +3 (1 KB); in the aligned case
-  // (shift and G multiples of 64) every 64 rows of a tile are one contiguous token run.
+  // staging: wave w, pass p fills tile rows 16p + 4w .. +3 (1 KB)
   const uint32_t smem_base = lds_addr(smem);
   const uint32_t rows_base = lds_addr(rows_s);
-  const uint64_t q_row_bytes = (uint64_t)a.sq.t * 2, do_row_bytes = (uint64_t)a.so.t * 2;
   const int st_row = 4 * w + (lane >> 4);
   const uint32_t st_chunk = (uint32_t)(((lane & 15) ^ swz(st_row)) << 4);
-  // aligned staging: scalar base of a 64-row token run plus these per-lane offsets
-  const uint32_t q_lane = (uint32_t)(st_row * q_row_bytes) + st_chunk;
-  const uint32_t do_lane = (uint32_t)(st_row * do_row_bytes) + st_chunk;
-  const uint64_t q_batch = uni64(reinterpret_cast<uint64_t>(qp) + (uint64_t)b * a.sq.b * 2);
-  const uint64_t do_batch = uni64(reinterpret_cast<uint64_t>(dop) + (uint64_t)b * a.so.b * 2);
   auto issue_tile = [&](int hh, int it, int stage) __attribute__((always_inline)) {
     const int h = h_lo + hh;
     const int q0 = (it_begin + it) * kQTileRows;
     const uint32_t qs = smem_base + stage * 2 * kQTileBytes + 4 * w * kRowBytes;
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) {
-      if constexpr (!RAGGED) {
-        const uint32_t tok0 = (uint32_t)token_of(run.p0 + q0 + 64 * hf, s, a.N);
-        const uint64_t qb = q_batch + tok0 * q_row_bytes + (uint64_t)h * a.sq.h * 2;
-        const uint64_t dob = do_batch + tok0 * do_row_bytes + (uint64_t)h * a.so.h * 2;
+      // every row finds its own token; padding rows repeat the last row of the run
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          dma16s(qb + p * 16 * q_row_bytes, q_lane, qs + (64 * hf + 16 * p) * kRowBytes);
-          dma16s(dob + p * 16 * do_row_bytes, do_lane, qs + (64 * hf + 16 * p) * kRowBytes + kQTileBytes);
-        }
-        if (w == hf) {   // wave 0 / 1: lse and delta of rows 64*hf .. +63
-          const uint64_t ro = (((uint64_t)b * a.H + h) * a.N + tok0) * 4;
-          dma4s(reinterpret_cast<uint64_t>(a.lse2) + ro, lane * 4, rows_base + ((stage * 2 + 0) * kQTileRows + 64 * hf) * 4);
-          dma4s(reinterpret_cast<uint64_t>(a.delta) + ro, lane * 4, rows_base + ((stage * 2 + 1) * kQTileRows + 64 * hf) * 4);
-        }
-      } else {   // every row finds its own token; padding rows repeat the last row of the run
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          const int tok = run_token(a, run, q0 + 64 * hf + 16 * p + st_row, s);
-          if (DH == 64 && st_chunk >= 2 * DH) continue;   // a 64-wide row fills the first eight chunks only
-          dma16(qp + row_off(a.sq, b, tok, h) * 2 + st_chunk, qs + (64 * hf + 16 * p) * kRowBytes);
-          dma16(dop + row_off(a.so, b, tok, h) * 2 + st_chunk,
-                qs + (64 * hf + 16 * p) * kRowBytes + kQTileBytes);
-        }
-        if (w == hf) {
-          const size_t ro = ((size_t)b * a.H + h) * a.N + run_token(a, run, q0 + 64 * hf + lane, s);
-          dma4(a.lse2 + ro, rows_base + ((stage * 2 + 0) * kQTileRows + 64 * hf) * 4);
-          dma4(a.delta + ro, rows_base + ((stage * 2 + 1) * kQTileRows + 64 * hf) * 4);
-        }
+      for (int p = 0; p < 4; ++p) {
+        const int tok = run_token(a, run, q0 + 64 * hf + 16 * p + st_row, s);
+        if (DH == 64 && st_chunk >= 2 * DH) continue;   // a 64-wide row fills the first eight chunks only
+        dma16(qp + row_off(a.sq, b, tok, h) * 2 + st_chunk, qs + (64 * hf + 16 * p) * kRowBytes);
+        dma16(dop + row_off(a.so, b, tok, h) * 2 + st_chunk,
+              qs + (64 * hf + 16 * p) * kRowBytes + kQTileBytes);
+      }
+      if (w == hf) {
+        const size_t ro = ((size_t)b * a.H + h) * a.N + run_token(a, run, q0 + 64 * hf + lane, s);
+        dma4(a.lse2 + ro, rows_base + ((stage * 2 + 0) * kQTileRows + 64 * hf) * 4);
+        dma4(a.delta + ro, rows_base + ((stage * 2 + 1) * kQTileRows + 64 * hf) * 4);
       }
     }
   };
@@ -326,7 +286,7 @@ bwd_dkdv_bf16_kernel(KArgs a, int ncls, int T, int il, int n_rest) {
       const bool wrap = hh + 1 == nheads;
       issue_tile(wrap ? 0 : hh + 1, wrap ? it - 1 : it, stage ^ 1);
     }
-    if constexpr (RAGGED) __builtin_amdgcn_sched_barrier(0);   // keeps the per-row addresses out of the tile body
+    __builtin_amdgcn_sched_barrier(0);   // keeps the per-row addresses out of the tile body
     DkdvTile t;
     t.Qs = smem + stage * 2 * kQTileBytes;
     t.dOs = t.Qs + kQTileBytes;
@@ -342,7 +302,7 @@ bwd_dkdv_bf16_kernel(KArgs a, int ncls, int T, int il, int n_rest) {
   // serves all but the first.  The partial last tile (a group size that is not a multiple of
   // the tile) comes first, the interior tiles follow in a loop of their own (the hot loop
   // holds nothing but the pipelined interior tile), the diagonal tiles come last.
-  const bool has_tail = RAGGED && (run.len % kQTileRows != 0);
+  const bool has_tail = run.len % kQTileRows != 0;
   const int n_full = has_tail ? nq - 1 : nq;           // tiles [0, n_full) are complete
   if (n_iter > 0) issue_tile(0, nq - 1, 0);
   int n = 0;
@@ -365,24 +325,18 @@ bwd_dkdv_bf16_kernel(KArgs a, int ncls, int T, int il, int n_rest) {
   }
   for (int hh = 0; hh < nheads; ++hh, ++n) {
     const DkdvTile t = begin_tile(n, hh, 0);
-    if constexpr (RAGGED) {
-      // query rows >= G (padding of a partial tile) give P = 0; blocks before this wave's
-      // keys are skipped
-      for (int mb = w; mb < 4; ++mb) dkdv_block<true, DH>(t, mb, j0 + 32 * mb, key, kf, vf, dk_acc, dv_acc, run.len);
-    } else {
-      // block mb < w is entirely before this wave's keys, block w is masked
-      dkdv_block<true>(t, w, j0 + 32 * w, key, kf, vf, dk_acc, dv_acc);
-      for (int mb = w + 1; mb < 4; ++mb) dkdv_block<false>(t, mb, 0, key, kf, vf, dk_acc, dv_acc);
-    }
+    // query rows >= run.len (padding of a partial tile) give P = 0; blocks before this wave's
+    // keys are skipped
+    for (int mb = w; mb < 4; ++mb) dkdv_block<true, DH>(t, mb, j0 + 32 * mb, key, kf, vf, dk_acc, dv_acc, run.len);
   }
   __syncthreads();
 
   // ---- store dK^T, dV^T blocks (keys lane-indexed) at un-rolled token rows
   if (a.dkv_partial) {
-    // kv head shared by both classes: fp32 partial of this class, summed by the combine pass
+    // query heads cut into parts: fp32 partial of this one, summed by the combine pass
     const size_t kv_elems = (size_t)a.B * a.N * a.Hkv * a.D;
-    float* dk_out = a.dkv_partial + (size_t)cls * kv_elems;
-    float* dv_out = a.dkv_partial + (size_t)(2 + cls) * kv_elems;
+    float* dk_out = a.dkv_partial + (size_t)at.part * kv_elems;
+    float* dv_out = dk_out + (size_t)a.parts * kv_elems;
     if (key >= run.len) return;   // padding key of a partial tile
     const int tok = token_of(run.p0 + key, s, a.N);
     const size_t base = ((size_t)((size_t)b * a.N + tok) * a.Hkv + c) * a.D;   // partials are contiguous
@@ -544,25 +498,18 @@ __device__ __forceinline__ void dq_tile64(f32x16 (&dq_acc)[4], const bf16x8 (&qf
 // DH = 64 (only with RAGGED): the head dimension is 64 and the products skip the zero half.
 template <bool RAGGED, int DH = 128>
 __global__ void __launch_bounds__(256, 2)
-bwd_dq_bf16_kernel(KArgs a, int T, int il, int n_rest) {
+bwd_dq_bf16_kernel(KArgs a, int T, Deal deal) {
   constexpr int BM = 128;
   __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes];   // [stage][K,V]
 
-  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = thread_id(), lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g32 = lane >> 5, l32 = lane & 31;
 
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  int y, rank;
-  decode_slot(slot, T, il, y, rank);
+  int seq, rank;
+  if (!decode_block(block_id(), T, deal, seq, rank)) return;
+  const HeadPos at = head_of_seq(a, seq);
+  const int gidx = at.g, c = at.c, b = at.b, h = at.h;
   int qt = T - 1 - rank;
-  const int hr = uni(y % a.r);
-  int rest = uni(uni(y / a.r) * 8 + xcd);
-  if (rest >= n_rest) return;
-  const int NG = uni(a.N / a.G);
-  const int gidx = uni(rest % NG); rest = uni(rest / NG);
-  const int c = uni(rest % a.Hkv);
-  const int b = uni(rest / a.Hkv);
-  const int h = c * a.r + hr;
 
   const int s = uni(shift_of_head(a, h));
   Run run{gidx * a.G, a.G};                        // the causal run of this block (see the forward kernel)
@@ -675,34 +622,25 @@ bwd_dq_bf16_kernel(KArgs a, int T, int il, int n_rest) {
 }  // namespace
 
 int launch_bwd_dkdv_bf16(const KArgs& a, hipStream_t st) {
-  if (dkdv_split_applies(a)) return launch_bwd_dkdv_split_bf16(a, st);
-  const int NG = a.N / a.G;
-  const int ncls = a.mixed ? 2 : 1;
-  const int T = a.ragged ? ragged_tiles(a, 128) : a.G / 128;
-  const int n_rest = a.B * a.Hkv * ncls * NG;
-  const int il = interleave_for(T, 32);   // 32 CUs per XCD, one workgroup each
-  const int blocks = 8 * T * pad_to((n_rest + 7) / 8, il);
+  if (!a.ragged) return launch_bwd_dkdv_split_bf16(a, st);
+  const int T = ragged_tiles(a, 128);
+  const Grid g = grid_of(T, a.B * a.Hkv * a.NG * a.parts, 1, 32);   // 32 CUs per XCD, one workgroup each
   if (a.D == 64)
-    hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<true, 64>), dim3(blocks), dim3(256), 0, st, a, ncls, T, il, n_rest);
-  else if (a.ragged)
-    hipLaunchKernelGGL(bwd_dkdv_bf16_kernel<true>, dim3(blocks), dim3(256), 0, st, a, ncls, T, il, n_rest);
+    hipLaunchKernelGGL(bwd_dkdv_bf16_kernel<64>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
   else
-    hipLaunchKernelGGL(bwd_dkdv_bf16_kernel<false>, dim3(blocks), dim3(256), 0, st, a, ncls, T, il, n_rest);
+    hipLaunchKernelGGL(bwd_dkdv_bf16_kernel<128>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 int launch_bwd_dq_bf16(const KArgs& a, hipStream_t st) {
-  const int NG = a.N / a.G;
   const int T = a.ragged ? ragged_tiles(a, 128) : a.G / 128;
-  const int n_rest = a.B * a.Hkv * NG;
-  const int il = interleave_for(T, 64);   // 32 CUs per XCD, two workgroups each
-  const int blocks = 8 * T * pad_to(a.r * ((n_rest + 7) / 8), il);
+  const Grid g = grid_of(T, a.B * a.H * a.NG, a.r, 64);               // 32 CUs per XCD, two workgroups each
   if (a.D == 64)
-    hipLaunchKernelGGL((bwd_dq_bf16_kernel<true, 64>), dim3(blocks), dim3(256), 0, st, a, T, il, n_rest);
+    hipLaunchKernelGGL((bwd_dq_bf16_kernel<true, 64>), dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
   else if (a.ragged)
-    hipLaunchKernelGGL(bwd_dq_bf16_kernel<true>, dim3(blocks), dim3(256), 0, st, a, T, il, n_rest);
+    hipLaunchKernelGGL(bwd_dq_bf16_kernel<true>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
   else
-    hipLaunchKernelGGL(bwd_dq_bf16_kernel<false>, dim3(blocks), dim3(256), 0, st, a, T, il, n_rest);
+    hipLaunchKernelGGL(bwd_dq_bf16_kernel<false>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

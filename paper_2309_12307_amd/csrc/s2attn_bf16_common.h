@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "s2attn_device.h"
+
 namespace s2 {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -141,7 +143,7 @@ __device__ __forceinline__ float other_half(float x) {
   const uint32_t u = __float_as_uint(x);
   auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   // lanes < 32 receive the partner in r[1], lanes >= 32 in r[0]
-  return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
+  return __uint_as_float((thread_id() & 32) ? r[0] : r[1]);
 }
 
 __device__ __forceinline__ float max_halves(float x) {

@@ -1,12 +1,12 @@
 // bf16 S2-Attn backward, dK/dV kernel for gfx950, two waves per SIMD ("role split").
-// Used for tile-aligned shapes (G % 128 == 0, shift % 64 == 0, a Variant 2 split that is a
-// multiple of 128) with every kv head wholly shifted or unshifted; everything else runs the
-// one-wave-per-SIMD kernel of s2attn_bf16_bwd.hip, which computes the same thing.
+// Used for tile-aligned shapes (D = 128, G % 128 == 0, shift % 64 == 0, a Variant 2 split that is
+// a multiple of 128); everything else runs the one-wave-per-SIMD kernel of s2attn_bf16_bwd.hip,
+// which computes the same thing.
 //
 // A workgroup (8 waves on one CU) owns 128 keys of one (batch, kv head, group) in the rolled
 // frame of the kv head's class (LongLoRA Algorithm 1: the shift is row addressing only) and
 // walks the 64-row query tiles at or below the diagonal (from the end of the group down to
-// the diagonal) for every query head of the kv head.  The four products of the
+// the diagonal) for every query head of the kv head, or of one part of them (part_heads).  The four products of the
 // softmax-Jacobian backward (dS = P * (dP - delta), P recomputed from the stored
 // log-sum-exp) are split between the two waves that share a SIMD and a 32-key block, so that
 // each fits in 256 registers with all accumulators in ordinary vector registers:
@@ -106,27 +106,21 @@ __device__ __forceinline__ void store_ds(char* dst, bf16x8 v) {
 // dK product) for the dQ kernel, which then needs neither S nor dP again.
 template <bool SPILL>
 __global__ void __launch_bounds__(512, 1)
-bwd_dkdv_split_kernel(KArgs a, int T, int il, int n_rest) {
+bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
   __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
 
-  const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
+  const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
   const int g32 = lane >> 5, l32 = lane & 31;
   const bool role_b = w >= 4;
   const int kb = w & 3;
 
-  // block -> (batch, kv head, group, key tile); heaviest key tiles (jt = 0) first
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  int y, jt;
-  decode_slot(slot, T, il, y, jt);
-  int rest = uni(y * 8 + xcd);
-  if (rest >= n_rest) return;
-  const int NG = uni(a.N / a.G);
-  const int gidx = uni(rest % NG); rest = uni(rest / NG);
-  const int c = uni(a.c_begin + rest % a.c_count);
-  const int b = uni(rest / a.c_count);
-
-  const int h_lo = c * a.r;
-  const int s = uni(h_lo >= a.shifted_from ? a.shift : 0);
+  // block -> (batch, kv head, part of its query heads, group, key tile); heaviest key tiles (jt = 0) first
+  int seq, jt;
+  if (!decode_block(block_id(), T, deal, seq, jt)) return;
+  const KvPos at = kv_of_seq(a, seq);
+  const int gidx = at.g, c = at.c, b = at.b;
+  int h_lo, nheads, s;                               // query heads [h_lo, h_lo + nheads), all of one class
+  part_heads(a, c, at.part, h_lo, nheads, s);
   const int j0 = jt * 128;
   const int kw0 = j0 + 32 * kb;                      // first key of this wave
   const int key = kw0 + l32;
@@ -134,7 +128,7 @@ bwd_dkdv_split_kernel(KArgs a, int T, int il, int n_rest) {
   // wrap-around group (Variant 2, Appendix B.3; the split is a multiple of the key tile here)
   const int split = uni(split_of_group(a, gidx, s));
   const int nq = uni(((j0 < split ? split : a.G) - j0) / kQT);   // query tiles of one head, >= 2
-  const int n_iter = a.r * nq;
+  const int n_iter = nheads * nq;
   const float c2 = a.scale_log2;
 
   // loop-invariant B operand of this wave's 32 keys: K^T (role A) or -V^T (role B, so that
@@ -185,7 +179,7 @@ bwd_dkdv_split_kernel(KArgs a, int T, int il, int n_rest) {
 #pragma unroll
   for (int db = 0; db < 4; ++db) acc[db] = zero16();
 
-  // The flattened tile sequence n = 0 .. r * nq - 1 runs over the query tiles from the end of
+  // The flattened tile sequence n = 0 .. n_iter - 1 runs over the query tiles from the end of
   // the group down to the diagonal, all query heads of a tile one after the other.  Every
   // workgroup of a (kv head, group) starts at the last query tile whatever its key tile, so the
   // workgroups that run together read the same Q and dO tile at about the same time and the
@@ -194,11 +188,11 @@ bwd_dkdv_split_kernel(KArgs a, int T, int il, int n_rest) {
   // over r heads' worth of Q and dO: at r = 8 the kernel then reads 8 times as much from HBM
   // and takes 7 % longer; at r = 1 it is 2 % slower.)
   auto advance = [&](int& hh, int& it) {
-    if (++hh == a.r) { hh = 0; --it; }
+    if (++hh == nheads) { hh = 0; --it; }
   };
   const int it_first = nq - 1;
   int hh_next = 0, it_next = it_first;     // tile n + 1 (to be staged)
-  issue_tile(0, it_first, 0, 0);
+  if (n_iter > 0) issue_tile(0, it_first, 0, 0);   // (a part may be empty)
   advance(hh_next, it_next);
 
   if (!role_b) {
@@ -276,10 +270,10 @@ bwd_dkdv_split_kernel(KArgs a, int T, int il, int n_rest) {
     int hh_cur = 0, it_cur = it_first;   // tile n
     if constexpr (SPILL) {
       const long long per_group = ds_blobs_per_group(T);
-      const long long first = ((long long)(b * a.c_count * a.r + (h_lo - a.c_begin * a.r)) * NG + gidx) * per_group +
+      const long long first = ((long long)(b * a.c_count * a.r + (h_lo - a.c_begin * a.r)) * a.NG + gidx) * per_group +
                               ds_blob_index(T, jt, 0);
       ds_lane = static_cast<char*>(a.ds_spill) + first * kDsBlobBytes + kb * 4096 + lane * 16;
-      ds_head_stride = (long long)NG * per_group * kDsBlobBytes;
+      ds_head_stride = (long long)a.NG * per_group * kDsBlobBytes;
     }
     for (int n = 0; n <= n_iter; ++n) {
       const int o_st = n & 1;
@@ -347,6 +341,20 @@ bwd_dkdv_split_kernel(KArgs a, int T, int il, int n_rest) {
       q_st = q_st == 2 ? 0 : q_st + 1;
     }
   }
+  if (a.dkv_partial) {   // contiguous fp32 partial of this part, summed by the combine pass
+    const size_t elems = (size_t)a.B * a.N * a.Hkv * 128;
+    const int tok = token_of(gidx * a.G + key, s, a.N);
+    float* dst = a.dkv_partial + (size_t)((role_b ? 0 : a.parts) + at.part) * elems +
+                 ((size_t)((size_t)b * a.N + tok) * a.Hkv + c) * 128 + 4 * g32;
+    const float mul = role_b ? a.scale : 1.f;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int vv = 0; vv < 4; ++vv)
+        *reinterpret_cast<float4*>(dst + 32 * db + 8 * vv) =
+            make_float4(acc[db][4 * vv] * mul, acc[db][4 * vv + 1] * mul, acc[db][4 * vv + 2] * mul, acc[db][4 * vv + 3] * mul);
+    return;
+  }
   __syncthreads();
 
   // ---- store this wave's 32 x 128 block (dV for role A, dK for role B) at un-rolled rows
@@ -366,20 +374,13 @@ bwd_dkdv_split_kernel(KArgs a, int T, int il, int n_rest) {
 
 }  // namespace
 
-bool dkdv_split_applies(const KArgs& a) {
-  return !a.ragged && !a.mixed;
-}
-
 int launch_bwd_dkdv_split_bf16(const KArgs& a, hipStream_t st) {
-  const int NG = a.N / a.G;
   const int T = a.G / 128;
-  const int n_rest = a.B * a.c_count * NG;
-  const int il = interleave_for(T, 32);   // 32 CUs per XCD, one workgroup each
-  const int blocks = 8 * T * pad_to((n_rest + 7) / 8, il);
+  const Grid g = grid_of(T, a.B * a.c_count * a.NG * a.parts, 1, 32);   // 32 CUs per XCD, one workgroup each
   if (a.ds_spill)
-    hipLaunchKernelGGL(bwd_dkdv_split_kernel<true>, dim3(blocks), dim3(512), 0, st, a, T, il, n_rest);
+    hipLaunchKernelGGL(bwd_dkdv_split_kernel<true>, dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
   else
-    hipLaunchKernelGGL(bwd_dkdv_split_kernel<false>, dim3(blocks), dim3(512), 0, st, a, T, il, n_rest);
+    hipLaunchKernelGGL(bwd_dkdv_split_kernel<false>, dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -33,27 +33,20 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 
 __global__ void __launch_bounds__(256, 1)
-bwd_dq_spill_kernel(KArgs a, int T, int il, int n_rest) {
+bwd_dq_spill_kernel(KArgs a, int T, Deal deal) {
   constexpr int BM = 128;
   __shared__ __attribute__((aligned(1024))) char smem[kStages * 2 * kTileBytes];   // [stage][K, dS^T]
 
-  const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
+  const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
   const int g32 = lane >> 5, l32 = lane & 31;
 
   // block -> (batch, head, group, query tile), as in the other kernels: every XCD walks its
   // own (batch, kv head, group) triples, heaviest query tiles first
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  int y, rank;
-  decode_slot(slot, T, il, y, rank);
+  int seq, rank;
+  if (!decode_block(block_id(), T, deal, seq, rank)) return;
+  const HeadPos at = head_of_seq(a, seq);
+  const int gidx = at.g, c = at.c, b = at.b, h = at.h;
   const int qt = T - 1 - rank;
-  const int hr = uni(y % a.r);
-  int rest = uni(uni(y / a.r) * 8 + xcd);
-  if (rest >= n_rest) return;
-  const int NG = uni(a.N / a.G);
-  const int gidx = uni(rest % NG); rest = uni(rest / NG);
-  const int c = uni(a.c_begin + rest % a.c_count);
-  const int b = uni(rest / a.c_count);
-  const int h = c * a.r + hr;
 
   const int s = uni(shift_of_head(a, h));
   const int split = uni(split_of_group(a, gidx, s));   // Variant 2: a multiple of 128 here
@@ -78,7 +71,7 @@ bwd_dq_spill_kernel(KArgs a, int T, int il, int n_rest) {
                                       (st_chunk & 1) * 512 + st_row * 16);
   const long long per_group = ds_blobs_per_group(T);
   const uint64_t ds_group = uni64(reinterpret_cast<uint64_t>(a.ds_spill) +
-      (uint64_t)(((long long)(b * a.c_count * a.r + (h - a.c_begin * a.r)) * NG + gidx) * per_group) * kDsBlobBytes);
+      (uint64_t)(((long long)(b * a.c_count * a.r + (h - a.c_begin * a.r)) * a.NG + gidx) * per_group) * kDsBlobBytes);
   auto issue_step = [&](int n, int stage) {
     const int jt = jt_first + (n >> 1), half = n & 1;
     const uint32_t tok0 = (uint32_t)token_of(gidx * a.G + jt * 128 + half * BK, s, a.N);
@@ -173,12 +166,9 @@ bwd_dq_spill_kernel(KArgs a, int T, int il, int n_rest) {
 }  // namespace
 
 int launch_bwd_dq_spill_bf16(const KArgs& a, hipStream_t st) {
-  const int NG = a.N / a.G;
   const int T = a.G / 128;
-  const int n_rest = a.B * a.c_count * NG;
-  const int il = interleave_for(T, 32);   // 32 CUs per XCD, one workgroup each
-  const int blocks = 8 * T * pad_to(a.r * ((n_rest + 7) / 8), il);
-  hipLaunchKernelGGL(bwd_dq_spill_kernel, dim3(blocks), dim3(256), 0, st, a, T, il, n_rest);
+  const Grid g = grid_of(T, a.B * a.c_count * a.r * a.NG, a.r, 32);   // 32 CUs per XCD, one workgroup each
+  hipLaunchKernelGGL(bwd_dq_spill_kernel, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

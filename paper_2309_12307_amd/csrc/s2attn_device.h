@@ -11,6 +11,27 @@ struct TStride {
   long long b, t, h;
 };
 
+// Block and thread index (all launches are one-dimensional).  threadIdx and blockIdx go through
+// functions of the device library that this build's floating-point flags keep from being inlined:
+// a real call each, with its answer in a vector register even where it is the same for all lanes.
+__device__ __forceinline__ int block_id() { return (int)__builtin_amdgcn_workgroup_id_x(); }
+__device__ __forceinline__ int thread_id() { return (int)__builtin_amdgcn_workitem_id_x(); }
+
+// Division of a number below 2^31 by a divisor known on the host: one multiplication on the
+// scalar unit.  The compiler's division of two run-time numbers is some forty vector
+// instructions, and a block's position takes about ten divisions before its first load.
+struct Div {
+  uint32_t mul, shift;
+};
+inline Div div_by(uint32_t d) {
+  uint32_t shift = 0;
+  while ((1ull << shift) < d) ++shift;
+  return Div{(uint32_t)((((1ull << shift) - d) << 32) / d + 1), shift};
+}
+__device__ __forceinline__ int quot(int n, const Div& d) {
+  return (int)(((uint32_t)(((uint64_t)(uint32_t)n * d.mul) >> 32) + (uint32_t)n) >> d.shift);
+}
+
 struct KArgs {
   const void* q; const void* k; const void* v;
   void* o; float* lse;                       // forward outputs / backward inputs
@@ -25,6 +46,8 @@ struct KArgs {
   TStride so;                                // o and dout: contiguous (B,N,H,D)
   int B, N, H, Hkv, D, G;
   int r;                                     // H / Hkv
+  int NG;                                    // N / G
+  Div by_r, by_NG, by_parts, by_c_count;
   int shift;                                 // tokens, 0 <= shift < G
   int shifted_from;                          // heads >= shifted_from use the shifted partition
   int split;                                 // Variant 2: rows [0,split) | [split,G) of the wrap group; G = off
@@ -69,35 +92,33 @@ __device__ __forceinline__ int shift_of_head(const KArgs& a, int h) {
 // First visible key index for query row i of group g (0 except under Variant 2
 // in the wrap-around group of a shifted head, Appendix B.3).
 __device__ __forceinline__ int split_of_group(const KArgs& a, int g, int s) {
-  return (s > 0 && g == a.N / a.G - 1) ? a.split : a.G;   // a.split == G means "no split"
+  return (s > 0 && g == a.NG - 1) ? a.split : a.G;   // a.split == G means "no split"
 }
 
-// Block slot of one XCD -> (y, rank): y numbers the independent tile sequences of the launch
-// (one per batch, head, group ...), rank orders the T tiles of a sequence from heaviest (0)
-// to lightest.  `il` sequences are walked together, heaviest tiles of all of them first:
-// when a sequence has fewer tiles than the XCD has workgroup slots, several sequences are
-// resident anyway, and this order hands every slot about the same total work (a plain
+// How a launch deals its tile sequences out: bundles of `bundle` neighbouring sequences, which
+// share K and V and so want one L2, go round the eight XCDs (as the block ids do).
+struct Deal {
+  int n_seq, bundle;
+  int il;   // sequences of an XCD walked together
+  Div by_bundle, by_il, by_span;   // span: T * il
+};
+
+// Block -> (sequence, rank): rank orders the T tiles of a sequence from heaviest (0) to lightest.
+// `il` sequences of an XCD are walked together, heaviest tiles of all of them first: when a
+// sequence has fewer tiles than the XCD has workgroup slots, several sequences are resident
+// anyway, and this order hands every slot about the same total work (a plain
 // sequence-by-sequence order leaves the slots that drew heavy tiles running at the end).
-__device__ __forceinline__ void decode_slot(int slot, int T, int il, int& y, int& rank) {
-  const int span = T * il;
-  const int chunk = __builtin_amdgcn_readfirstlane(slot / span);
-  const int within = slot - chunk * span;
-  rank = __builtin_amdgcn_readfirstlane(within / il);
-  y = chunk * il + (within - rank * il);
-}
-
-// Block -> (sequence, rank) when a launch has n_seq tile sequences: XCD x (block ids go round
-// the eight XCDs) walks sequences [x n_seq / 8, (x + 1) n_seq / 8), so that neighbours, which
-// share K and V (or Q and dO), meet in one L2, and no XCD has more than one sequence more than
-// another.  False: the block has no tile (sequence counts are padded to a multiple of il).
-__device__ __forceinline__ bool decode_block(int block, int T, int il, int n_seq, int& seq, int& rank) {
-  const int xcd = block & 7;
-  int y;
-  decode_slot(block >> 3, T, il, y, rank);
-  const int each = n_seq >> 3, more = n_seq & 7;
-  seq = __builtin_amdgcn_readfirstlane(xcd * each + min(xcd, more) + y);
-  rank = __builtin_amdgcn_readfirstlane(rank);
-  return __builtin_amdgcn_readfirstlane(y) < each + (xcd < more ? 1 : 0);
+// False: the block has no tile (the grid is padded to whole bundles for every XCD and to a
+// multiple of il).
+__device__ __forceinline__ bool decode_block(int block, int T, const Deal& d, int& seq, int& rank) {
+  const int slot = block >> 3;
+  const int chunk = quot(slot, d.by_span);
+  const int within = slot - chunk * T * d.il;
+  rank = quot(within, d.by_il);
+  const int y = chunk * d.il + within - rank * d.il;
+  const int yb = quot(y, d.by_bundle);
+  seq = (yb * 8 + (block & 7)) * d.bundle + y - yb * d.bundle;
+  return seq < d.n_seq;
 }
 
 // Sequence number -> (batch, head, group), query heads of one (kv head, group) next to each other.
@@ -106,14 +127,12 @@ struct HeadPos {
 };
 __device__ __forceinline__ HeadPos head_of_seq(const KArgs& a, int seq) {
   HeadPos p;
-  const int NG = __builtin_amdgcn_readfirstlane(a.N / a.G);
-  int t = __builtin_amdgcn_readfirstlane(seq / a.r);
-  const int hr = seq - t * a.r;
-  int u = __builtin_amdgcn_readfirstlane(t / NG);
-  p.g = t - u * NG;
-  p.b = __builtin_amdgcn_readfirstlane(u / a.Hkv);
-  p.c = u - p.b * a.Hkv;
-  p.h = p.c * a.r + hr;
+  const int t = quot(seq, a.by_r);
+  const int u = quot(t, a.by_NG);
+  p.g = t - u * a.NG;
+  p.b = quot(u, a.by_c_count);
+  p.c = a.c_begin + u - p.b * a.c_count;
+  p.h = p.c * a.r + seq - t * a.r;
   return p;
 }
 
@@ -123,13 +142,12 @@ struct KvPos {
 };
 __device__ __forceinline__ KvPos kv_of_seq(const KArgs& a, int seq) {
   KvPos p;
-  const int NG = __builtin_amdgcn_readfirstlane(a.N / a.G);
-  int t = __builtin_amdgcn_readfirstlane(seq / a.parts);
+  const int t = quot(seq, a.by_parts);
   p.part = seq - t * a.parts;
-  int u = __builtin_amdgcn_readfirstlane(t / NG);
-  p.g = t - u * NG;
-  p.b = __builtin_amdgcn_readfirstlane(u / a.Hkv);
-  p.c = u - p.b * a.Hkv;
+  const int u = quot(t, a.by_NG);
+  p.g = t - u * a.NG;
+  p.b = quot(u, a.by_c_count);
+  p.c = a.c_begin + u - p.b * a.c_count;
   return p;
 }
 
@@ -138,6 +156,12 @@ __device__ __forceinline__ KvPos kv_of_seq(const KArgs& a, int seq) {
 // is at least 2 there); a part may be empty.
 __device__ __forceinline__ void part_heads(const KArgs& a, int c, int part, int& h_lo, int& n, int& shift) {
   int lo = c * a.r, hi = lo + a.r, p = part, np = a.parts;
+  if (np == 1) {
+    h_lo = lo;
+    n = a.r;
+    shift = lo >= a.shifted_from ? a.shift : 0;
+    return;
+  }
   const int f = min(max(a.shifted_from, lo), hi);
   const bool both = f > lo && f < hi;
   if (both) {

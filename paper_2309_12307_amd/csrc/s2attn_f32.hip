@@ -152,14 +152,14 @@ __device__ __forceinline__ void store_row(float* dst, const f32x4 (&acc)[D / 64]
 // layer of a few hundred tokens still spreads over the chip.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(256, 2) fwd_f32_kernel(KArgs a, int T, int il, int n_seq) {
+__global__ void __launch_bounds__(256, 2) fwd_f32_kernel(KArgs a, int T, Deal deal) {
   using L = Lanes<D>;
   __shared__ __attribute__((aligned(1024))) char smem[4 * L::kTileBytes];   // [stage][K, V]
 
-  const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
+  const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
   const int c16 = lane & 15, q4 = lane >> 4;
   int seq, rank;
-  if (!decode_block(blockIdx.x, T, il, n_seq, seq, rank)) return;
+  if (!decode_block(block_id(), T, deal, seq, rank)) return;
   const HeadPos at = head_of_seq(a, seq);
   const int s = uni(shift_of_head(a, at.h));
   Run run;
@@ -254,12 +254,12 @@ __global__ void __launch_bounds__(256, 2) fwd_f32_kernel(KArgs a, int T, int il,
 // of 16 k MFMA cycles.  A launch saved is what counts at the small sizes.
 // ---------------------------------------------------------------------------
 template <int D>
-__device__ __forceinline__ void bwd_dkdv_block(const KArgs& a, char* smem, float* rows_s, int block, int T, int il, int n_seq) {
+__device__ __forceinline__ void bwd_dkdv_block(const KArgs& a, char* smem, float* rows_s, int block, int T, const Deal& deal) {
   using L = Lanes<D>;
-  const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
+  const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
   const int c16 = lane & 15, q4 = lane >> 4;
   int seq, kt;
-  if (!decode_block(block, T, il, n_seq, seq, kt)) return;   // key tile 0 is the heaviest
+  if (!decode_block(block, T, deal, seq, kt)) return;   // key tile 0 is the heaviest
   const KvPos at = kv_of_seq(a, seq);
   int h_lo, nheads, s;
   part_heads(a, at.c, at.part, h_lo, nheads, s);
@@ -377,12 +377,12 @@ __device__ __forceinline__ void bwd_dkdv_block(const KArgs& a, char* smem, float
 }
 
 template <int D>
-__device__ __forceinline__ void bwd_dq_block(const KArgs& a, char* smem, int block, int T, int il, int n_seq) {
+__device__ __forceinline__ void bwd_dq_block(const KArgs& a, char* smem, int block, int T, const Deal& deal) {
   using L = Lanes<D>;
-  const int tid = threadIdx.x, lane = tid & 63, w = uni(tid >> 6);
+  const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
   const int c16 = lane & 15, q4 = lane >> 4;
   int seq, rank;
-  if (!decode_block(block, T, il, n_seq, seq, rank)) return;
+  if (!decode_block(block, T, deal, seq, rank)) return;
   const HeadPos at = head_of_seq(a, seq);
   const int s = uni(shift_of_head(a, at.h));
   Run run;
@@ -456,30 +456,29 @@ __device__ __forceinline__ void bwd_dq_block(const KArgs& a, char* smem, int blo
 
 template <int D>
 __global__ void __launch_bounds__(256, 2)
-bwd_f32_kernel(KArgs a, int n_kv, int T, int il_kv, int n_seq_kv, int il_q, int n_seq_q) {
+bwd_f32_kernel(KArgs a, int n_kv, int T, Deal deal_kv, Deal deal_q) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * Lanes<D>::kTileBytes];   // [stage][Q, dO] or [stage][K, V]
   __shared__ __attribute__((aligned(16))) float rows_s[2 * 2 * kTile];             // [stage][lse * log2(e), delta]
-  if ((int)blockIdx.x < n_kv)
-    bwd_dkdv_block<D>(a, smem, rows_s, blockIdx.x, T, il_kv, n_seq_kv);
+  if (block_id() < n_kv)
+    bwd_dkdv_block<D>(a, smem, rows_s, block_id(), T, deal_kv);
   else
-    bwd_dq_block<D>(a, smem, blockIdx.x - n_kv, T, il_q, n_seq_q);
+    bwd_dq_block<D>(a, smem, block_id() - n_kv, T, deal_q);
 }
 
 template <int D>
 int launch_fwd_t(const KArgs& a, hipStream_t st) {
   const int T = ragged_tiles(a, kWgRows);
-  const Grid g = grid_of(T, a.B * a.H * (a.N / a.G), 64);
-  hipLaunchKernelGGL(fwd_f32_kernel<D>, dim3(g.blocks), dim3(256), 0, st, a, T, g.il, g.n_seq);
+  const Grid g = grid_of(T, a.B * a.H * a.NG, a.r, 64);
+  hipLaunchKernelGGL(fwd_f32_kernel<D>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 template <int D>
 int launch_bwd_t(const KArgs& a, hipStream_t st) {
-  const int NG = a.N / a.G;
   const int T = ragged_tiles(a, kWgRows);
-  const Grid kv = grid_of(T, a.B * a.Hkv * NG * a.parts, 64), q = grid_of(T, a.B * a.H * NG, 64);
-  hipLaunchKernelGGL(bwd_f32_kernel<D>, dim3(kv.blocks + q.blocks), dim3(256), 0, st, a, kv.blocks, T, kv.il, kv.n_seq,
-                     q.il, q.n_seq);
+  const Grid kv = grid_of(T, a.B * a.Hkv * a.NG * a.parts, 1, 64), q = grid_of(T, a.B * a.H * a.NG, a.r, 64);
+  hipLaunchKernelGGL(bwd_f32_kernel<D>, dim3(kv.blocks + q.blocks), dim3(256), 0, st, a, kv.blocks, T, kv.deal,
+                     q.deal);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

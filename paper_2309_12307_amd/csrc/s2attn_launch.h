@@ -11,10 +11,9 @@ int launch_bwd_f32(const KArgs& a, hipStream_t st);        // dQ, dK and dV (or 
 int launch_fwd_bf16(const KArgs& a, hipStream_t st);
 int launch_bwd_dkdv_bf16(const KArgs& a, hipStream_t st);  // delta must be ready
 int launch_bwd_dq_bf16(const KArgs& a, hipStream_t st);
-// two-waves-per-SIMD dK/dV kernel for the shapes dkdv_split_applies() accepts
-bool dkdv_split_applies(const KArgs& a);
+// two-waves-per-SIMD dK/dV kernel for tile-aligned shapes (not a.ragged)
 int launch_bwd_dkdv_split_bf16(const KArgs& a, hipStream_t st);   // a.ds_spill set: also stores the dS blobs
-// dQ from the dS blobs the dK/dV kernel stored (same shapes as dkdv_split_applies)
+// dQ from the dS blobs the dK/dV kernel stored (same shapes)
 int launch_bwd_dq_spill_bf16(const KArgs& a, hipStream_t st);
 
 // delta[b,h,t] = sum_d dout[b,t,h,d] * o[b,t,h,d], fp32, and lse2
@@ -22,20 +21,27 @@ int launch_delta_bf16(const KArgs& a, hipStream_t st);
 // dk = sum of the partials of all parts (same for dv), cast to the output type
 int launch_combine_partials(const KArgs& a, int dtype, hipStream_t st);
 
-// Number of tile sequences walked together (see decode_slot) for a kernel whose XCD holds
+// Number of tile sequences walked together (see decode_block) for a kernel whose XCD holds
 // `slots` workgroups at a time, and the sequence count padded to a multiple of it.
 inline int interleave_for(int T, int slots) { return T >= slots ? 1 : (slots + T - 1) / T; }
 inline int pad_to(int n, int il) { return (n + il - 1) / il * il; }
 
-// Grid of a launch with n_seq sequences of T tiles under decode_block.
+// Grid of a launch with n_seq sequences of T tiles, neighbouring `share` of which (a divisor of
+// n_seq) read the same K and V, on XCDs that hold `slots` workgroups at a time.  A bundle is the
+// largest piece of the `share` that deals every XCD the same number of sequences; one sequence
+// where no piece does.
 struct Grid {
-  int blocks, il, n_seq;
+  int blocks;
+  Deal deal;
 };
-inline Grid grid_of(int T, int n_seq, int slots) {
-  const int each = (n_seq + 7) / 8;   // sequences of one XCD
+inline Grid grid_of(int T, int n_seq, int share, int slots) {
+  int bundle = 1;
+  for (int m = share; m > 1; --m)
+    if (share % m == 0 && n_seq / m % 8 == 0) { bundle = m; break; }
+  const int each = (n_seq / bundle + 7) / 8 * bundle;   // sequences of one XCD
   const int want = interleave_for(T, slots);
   const int il = want < each ? want : each;
-  return Grid{8 * T * pad_to(each, il), il, n_seq};
+  return Grid{8 * T * pad_to(each, il), Deal{n_seq, bundle, il, div_by(bundle), div_by(il), div_by(T * il)}};
 }
 
 }  // namespace s2

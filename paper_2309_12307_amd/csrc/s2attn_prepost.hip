@@ -22,8 +22,8 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {   // round to ne
 // 16 lanes per (b,t,h) row; each lane reads 16-byte chunks.
 __global__ void __launch_bounds__(256) delta_kernel(const void* o, const void* dout, const float* lse,
                                                     float* delta, float* lse2, int B, int N, int H, int D) {
-  const size_t row = (size_t)blockIdx.x * 16 + threadIdx.x / 16;
-  const int lane = threadIdx.x % 16;
+  const size_t row = (size_t)block_id() * 16 + thread_id() / 16;
+  const int lane = thread_id() % 16;
   const size_t rows = (size_t)B * N * H;
   float acc = 0.f;
   if (row < rows) {
@@ -56,7 +56,7 @@ __global__ void __launch_bounds__(256) delta_kernel(const void* o, const void* d
 template <bool BF16>
 __global__ void __launch_bounds__(256) combine_kernel(const float* partial, void* dk, void* dv, TStride sdk,
                                                       TStride sdv, int N, int Hkv, int D, int parts, size_t elems) {
-  const size_t i4 = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  const size_t i4 = ((size_t)block_id() * 256 + thread_id()) * 4;
   if (i4 >= elems) return;
   // contiguous (b, t, c, d) index of the partials -> row of the (possibly strided) output
   const int d = (int)(i4 % D);
