@@ -48,7 +48,7 @@ def test_class_boundary_off_the_middle_of_a_kv_head():
     from test_gpu_parity_bf16 import compare
     B, N, H, Hkv, D, G = 1, 2048, 16, 2, 128, 1024
     inp = inputs.make_inputs(B, N, H, Hkv, D, seed=611, dtype="bf16")
-    out = run_hip(inp, G, "bf16", heads_total=20, head_offset=8)
+    out = run_hip(inp, G, "bf16", heads_total=36, head_offset=16)
     halves = [orc.s2attn_fwd_bwd(inp["q"][:, :, a:b], np.repeat(inp["k"], 8, axis=2)[:, :, a:b],
                                  np.repeat(inp["v"], 8, axis=2)[:, :, a:b], inp["do"][:, :, a:b], G, shift_heads=name)
               for a, b, name in ((0, 2, "none"), (2, 16, "all"))]
