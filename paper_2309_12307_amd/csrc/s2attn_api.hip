@@ -264,8 +264,7 @@ s2::KArgs make_kargs(const s2attn_params* p) {
   a.split = (p->wrap_variant == S2ATTN_WRAP_SPLIT && a.shift > 0) ? p->G - a.shift : p->G;
   a.mixed = kv_heads_mixed(p->H, p->Hkv, a.shifted_from) ? 1 : 0;
   a.parts = 1;
-  // the kernels built for partial tiles also take rows narrower than the 128-element tile (D = 64)
-  a.ragged = (p->dtype == S2ATTN_BF16 && (p->D != 128 || p->G % 128 != 0 || a.shift % 64 != 0 ||
+  a.ragged = (p->dtype == S2ATTN_BF16 && (p->G % 128 != 0 || a.shift % 64 != 0 ||
                                           (a.split < p->G && a.split % 128 != 0))) ? 1 : 0;
   a.c_begin = 0;
   a.c_count = p->Hkv;

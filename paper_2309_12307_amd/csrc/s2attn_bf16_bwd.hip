@@ -64,23 +64,21 @@ __device__ __forceinline__ void mma_sc(const bf16x8 (&buf)[8], DkdvBlock& blk, c
   }
 }
 // accumulate phase (block MB, queries 16T..16T+15 of it): dV^T += dO^T P, dK^T += Q^T dS.
-// DH: head dimension the products run over (128, or 64 when the upper half of every tile row is
-// zero padding).
-template <int MB, int T, int DH = 128>
+template <int MB, int T>
 __device__ __forceinline__ void load_acc(bf16x8 (&buf)[8], const DkdvTile& t) {
 #pragma unroll
-  for (int db = 0; db < DH / 32; ++db) {
+  for (int db = 0; db < 4; ++db) {
     buf[db] = frag_tr<32 * MB + 16 * T>(t.dOs, t.lo, db);
     buf[4 + db] = frag_tr<32 * MB + 16 * T>(t.Qs, t.lo, db);
   }
 }
-template <int T, int DH = 128>
+template <int T>
 __device__ __forceinline__ void mma_acc(const bf16x8 (&buf)[8], const bf16x4 (&pq)[4], const bf16x4 (&dsq)[4],
                                         f32x16 (&dk_acc)[4], f32x16 (&dv_acc)[4]) {
   const bf16x8 pf = __builtin_shufflevector(pq[2 * T], pq[2 * T + 1], 0, 1, 2, 3, 4, 5, 6, 7);
   const bf16x8 dsf = __builtin_shufflevector(dsq[2 * T], dsq[2 * T + 1], 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
-  for (int db = 0; db < DH / 32; ++db) {
+  for (int db = 0; db < 4; ++db) {
     dv_acc[db] = mfma32(buf[db], pf, dv_acc[db]);
     dk_acc[db] = mfma32(buf[4 + db], dsf, dk_acc[db]);
   }
@@ -167,8 +165,8 @@ __device__ __forceinline__ void dkdv_interior_tile(const DkdvTile& t, const bf16
 #undef S2_PHASE_END
 }
 
-// One 32-query block without pipelining (diagonal tiles; every tile when the head dimension is 64).
-template <bool MASK, int DH = 128>
+// One 32-query block without pipelining (diagonal tiles).
+template <bool MASK>
 __device__ __forceinline__ void dkdv_block(const DkdvTile& t, int mb, int q_first, int key, const bf16x8 (&kf)[8],
                                            const bf16x8 (&vf)[8], f32x16 (&dk_acc)[4], f32x16 (&dv_acc)[4],
                                            int q_lim = INT32_MAX) {
@@ -182,23 +180,21 @@ __device__ __forceinline__ void dkdv_block(const DkdvTile& t, int mb, int q_firs
   bf16x4 pq[4], dsq[4];
   blk.s = zero16(); init_dp<0>(blk, tt);
   load_sc<0, 0>(fa, tt);
-  if constexpr (DH == 128) load_sc<0, 1>(fb, tt);
+  load_sc<0, 1>(fb, tt);
   mma_sc<0>(fa, blk, kf, vf);
-  if constexpr (DH == 128) mma_sc<1>(fb, blk, kf, vf);
-  load_acc<0, 0, DH>(fa, tt); load_acc<0, 1, DH>(fb, tt);
+  mma_sc<1>(fb, blk, kf, vf);
+  load_acc<0, 0>(fa, tt); load_acc<0, 1>(fb, tt);
   sm_quarter<0, 0, MASK>(blk, tt, pq[0], dsq[0], q_first, key, q_lim);
   sm_quarter<0, 1, MASK>(blk, tt, pq[1], dsq[1], q_first, key, q_lim);
   sm_quarter<0, 2, MASK>(blk, tt, pq[2], dsq[2], q_first, key, q_lim);
   sm_quarter<0, 3, MASK>(blk, tt, pq[3], dsq[3], q_first, key, q_lim);
-  mma_acc<0, DH>(fa, pq, dsq, dk_acc, dv_acc);
-  mma_acc<1, DH>(fb, pq, dsq, dk_acc, dv_acc);
+  mma_acc<0>(fa, pq, dsq, dk_acc, dv_acc);
+  mma_acc<1>(fb, pq, dsq, dk_acc, dv_acc);
 }
 
 // For the shapes the role-split kernel does not take: G not a multiple of 128, the shift not of
-// 64, or a head dimension of 64.  Tiles may be partial and the wrap point may fall inside one,
+// 64.  Tiles may be partial and the wrap point may fall inside one,
 // so every staged row finds its own token and the padding rows of the last tile are masked.
-// DH = 64: the head dimension is 64 and the products skip the zero half.
-template <int DH>
 __global__ void __launch_bounds__(256, 1)
 bwd_dkdv_bf16_kernel(KArgs a, int T, Deal deal) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * kQTileBytes];            // [stage][Q,dO]
@@ -238,7 +234,7 @@ bwd_dkdv_bf16_kernel(KArgs a, int T, Deal deal) {
     const bf16x8* ksrc = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(a.k) + row_off(a.sk, b, tok, c));
     const bf16x8* vsrc = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(a.v) + row_off(a.sv, b, tok, c));
 #pragma unroll
-    for (int st = 0; st < DH / 16; ++st) { kf[st] = ksrc[2 * st + g32]; vf[st] = -vsrc[2 * st + g32]; }
+    for (int st = 0; st < 8; ++st) { kf[st] = ksrc[2 * st + g32]; vf[st] = -vsrc[2 * st + g32]; }
   }
 
   // staging: wave w, pass p fills tile rows 16p + 4w .. +3 (1 KB)
@@ -256,7 +252,6 @@ bwd_dkdv_bf16_kernel(KArgs a, int T, Deal deal) {
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
         const int tok = run_token(a, run, q0 + 64 * hf + 16 * p + st_row, s);
-        if (DH == 64 && st_chunk >= 2 * DH) continue;   // a 64-wide row fills the first eight chunks only
         dma16(qp + row_off(a.sq, b, tok, h) * 2 + st_chunk, qs + (64 * hf + 16 * p) * kRowBytes);
         dma16(dop + row_off(a.so, b, tok, h) * 2 + st_chunk,
               qs + (64 * hf + 16 * p) * kRowBytes + kQTileBytes);
@@ -310,24 +305,20 @@ bwd_dkdv_bf16_kernel(KArgs a, int T, Deal deal) {
     const int q0 = j0 + (nq - 1) * kQTileRows;
     for (int hh = 0; hh < nheads; ++hh, ++n) {
       const DkdvTile t = begin_tile(n, hh, nq - 1);
-      for (int mb = 0; mb < 4; ++mb) dkdv_block<true, DH>(t, mb, q0 + 32 * mb, key, kf, vf, dk_acc, dv_acc, run.len);
+      for (int mb = 0; mb < 4; ++mb) dkdv_block<true>(t, mb, q0 + 32 * mb, key, kf, vf, dk_acc, dv_acc, run.len);
     }
   }
   for (int it = n_full - 1; it >= 1; --it) {
     for (int hh = 0; hh < nheads; ++hh, ++n) {
       const DkdvTile t = begin_tile(n, hh, it);
-      if constexpr (DH == 128) {
-        dkdv_interior_tile(t, kf, vf, dk_acc, dv_acc);
-      } else {
-        for (int mb = 0; mb < 4; ++mb) dkdv_block<false, DH>(t, mb, 0, key, kf, vf, dk_acc, dv_acc);
-      }
+      dkdv_interior_tile(t, kf, vf, dk_acc, dv_acc);
     }
   }
   for (int hh = 0; hh < nheads; ++hh, ++n) {
     const DkdvTile t = begin_tile(n, hh, 0);
     // query rows >= run.len (padding of a partial tile) give P = 0; blocks before this wave's
     // keys are skipped
-    for (int mb = w; mb < 4; ++mb) dkdv_block<true, DH>(t, mb, j0 + 32 * mb, key, kf, vf, dk_acc, dv_acc, run.len);
+    for (int mb = w; mb < 4; ++mb) dkdv_block<true>(t, mb, j0 + 32 * mb, key, kf, vf, dk_acc, dv_acc, run.len);
   }
   __syncthreads();
 
@@ -345,7 +336,6 @@ bwd_dkdv_bf16_kernel(KArgs a, int T, Deal deal) {
 #pragma unroll
       for (int vv = 0; vv < 4; ++vv) {
         const int d = 32 * db + 8 * vv + 4 * g32;
-        if (d >= a.D) continue;   // head dimension 64: the upper half of the tile is padding
         *reinterpret_cast<float4*>(dk_out + base + d) =
             make_float4(dk_acc[db][4 * vv] * a.scale, dk_acc[db][4 * vv + 1] * a.scale,
                         dk_acc[db][4 * vv + 2] * a.scale, dk_acc[db][4 * vv + 3] * a.scale);
@@ -364,7 +354,7 @@ bwd_dkdv_bf16_kernel(KArgs a, int T, Deal deal) {
 #pragma unroll
   for (int it = 0; it < 8; ++it) {
     const int row = it * 4 + (lane >> 4), ch = lane & 15;
-    if (kw0 + row >= run.len || ch * 8 >= a.D) continue;   // padding key of a partial tile, padding of a narrow row
+    if (kw0 + row >= run.len) continue;   // padding key of a partial tile
     const int tok = token_of(run.p0 + kw0 + row, s, a.N);
     *reinterpret_cast<uint4*>(dkp + row_off(a.sdk, b, tok, c) + ch * 8) =
         *reinterpret_cast<const uint4*>(rk + tile_off(row, ch));
@@ -462,41 +452,7 @@ __device__ __forceinline__ void dq_tile(f32x16 (&dq_acc)[4], const bf16x8 (&qf)[
 #undef S2_DQ_STEP
 }
 
-// Head dimension 64 (the upper half of every tile row is zero padding): the same three
-// products over d = 0 .. 63 only, one 32-key block after the other, without the step pipeline.
-template <int ROW0>
-__device__ __forceinline__ void dq_scores64(f32x16& sa, f32x16& pa, const bf16x8 (&qf)[8], const bf16x8 (&dof)[8],
-                                            const char* Ks, const char* Vs, const LaneOffsets& lo) {
-  bf16x8 kfr[4], vfr[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) { kfr[k] = frag_rm<ROW0>(Ks, lo, k); vfr[k] = frag_rm<ROW0>(Vs, lo, k); }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) { sa = mfma32(kfr[k], qf[k], sa); pa = mfma32(vfr[k], dof[k], pa); }
-}
-template <int KROW0>
-__device__ __forceinline__ void dq_acc64(f32x16 (&dq_acc)[4], const char* Ks, const LaneOffsets& lo, bf16x8 dsf) {
-#pragma unroll
-  for (int db = 0; db < 2; ++db) dq_acc[db] = mfma32(frag_tr<KROW0>(Ks, lo, db), dsf, dq_acc[db]);
-}
-__device__ __forceinline__ void dq_tile64(f32x16 (&dq_acc)[4], const bf16x8 (&qf)[8], const bf16x8 (&dof)[8],
-                                          const char* Ks, const char* Vs, const LaneOffsets& lo, int j0,
-                                          int qrow, float c2, float lse2, float delta, int g32, bool masked) {
-  bf16x8 dsf[4];
-  f32x16 sa = zero16(), pa = zero16();
-  dq_scores64<0>(sa, pa, qf, dof, Ks, Vs, lo);
-  dq_ds<0>(sa, pa, dsf[0], dsf[1], j0, qrow, c2, lse2, delta, g32, masked);
-  sa = zero16();
-  pa = zero16();
-  dq_scores64<32>(sa, pa, qf, dof, Ks, Vs, lo);
-  dq_ds<32>(sa, pa, dsf[2], dsf[3], j0, qrow, c2, lse2, delta, g32, masked);
-  dq_acc64<0>(dq_acc, Ks, lo, dsf[0]);
-  dq_acc64<16>(dq_acc, Ks, lo, dsf[1]);
-  dq_acc64<32>(dq_acc, Ks, lo, dsf[2]);
-  dq_acc64<48>(dq_acc, Ks, lo, dsf[3]);
-}
-
-// DH = 64 (only with RAGGED): the head dimension is 64 and the products skip the zero half.
-template <bool RAGGED, int DH = 128>
+template <bool RAGGED>
 __global__ void __launch_bounds__(256, 2)
 bwd_dq_bf16_kernel(KArgs a, int T, Deal deal) {
   constexpr int BM = 128;
@@ -537,7 +493,7 @@ bwd_dq_bf16_kernel(KArgs a, int T, Deal deal) {
     const bf16x8* qsrc = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(a.q) + row_off(a.sq, b, tok, h));
     const bf16x8* dsrc = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(a.dout) + row_off(a.so, b, tok, h));
 #pragma unroll
-    for (int st = 0; st < DH / 16; ++st) { qf[st] = qsrc[2 * st + g32]; dof[st] = dsrc[2 * st + g32]; }
+    for (int st = 0; st < 8; ++st) { qf[st] = qsrc[2 * st + g32]; dof[st] = dsrc[2 * st + g32]; }
     const size_t ro = ((size_t)b * a.H + h) * a.N + tok;
     lse2 = a.lse2[ro];
     delta = a.delta[ro];
@@ -566,10 +522,8 @@ bwd_dq_bf16_kernel(KArgs a, int T, Deal deal) {
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
         const int tok = run_token(a, run, jt * BN + 16 * p + st_row, s);
-        if (DH == 128 || st_chunk < 2 * DH) {   // a 64-wide row fills the first eight chunks only
-          dma16(kp + row_off(a.sk, b, tok, c) * 2 + st_chunk, ks + 16 * p * kRowBytes);
-          dma16(vp + row_off(a.sv, b, tok, c) * 2 + st_chunk, ks + 16 * p * kRowBytes + kTileBytes);
-        }
+        dma16(kp + row_off(a.sk, b, tok, c) * 2 + st_chunk, ks + 16 * p * kRowBytes);
+        dma16(vp + row_off(a.sv, b, tok, c) * 2 + st_chunk, ks + 16 * p * kRowBytes + kTileBytes);
       }
     }
   };
@@ -594,10 +548,7 @@ bwd_dq_bf16_kernel(KArgs a, int T, Deal deal) {
     const char* Ks = smem + STAGE * 2 * kTileBytes;
     const char* Vs = Ks + kTileBytes;
     if (j0 > qw0 + 31 || j0 + BN - 1 < lo_w) return;   // wholly outside this wave's visible keys
-    if constexpr (DH == 128)
-      dq_tile(dq_acc, qf, dof, Ks, Vs, lo, j0, qrow, c2, lse2, delta, g32, j0 + BN - 1 > qw0);
-    else
-      dq_tile64(dq_acc, qf, dof, Ks, Vs, lo, j0, qrow, c2, lse2, delta, g32, j0 + BN - 1 > qw0);
+    dq_tile(dq_acc, qf, dof, Ks, Vs, lo, j0, qrow, c2, lse2, delta, g32, j0 + BN - 1 > qw0);
   };
   for (int n = 0; n < n_tiles; n += 2) {
     body(std::integral_constant<int, 0>{}, n);
@@ -612,7 +563,7 @@ bwd_dq_bf16_kernel(KArgs a, int T, Deal deal) {
 #pragma unroll
   for (int it = 0; it < 8; ++it) {
     const int row = it * 4 + (lane >> 4), ch = lane & 15;
-    if (qw0 + row >= run.len || ch * 8 >= a.D) continue;   // padding row of a partial tile, padding of a narrow row
+    if (qw0 + row >= run.len) continue;   // padding row of a partial tile
     const int tok = token_of(run.p0 + qw0 + row, s, a.N);
     *reinterpret_cast<uint4*>(dqp + row_off(a.sdq, b, tok, h) + ch * 8) =
         *reinterpret_cast<const uint4*>(region + tile_off(row, ch));
@@ -622,22 +573,19 @@ bwd_dq_bf16_kernel(KArgs a, int T, Deal deal) {
 }  // namespace
 
 int launch_bwd_dkdv_bf16(const KArgs& a, hipStream_t st) {
+  if (a.D == 64) return launch_bwd_dkdv_d64(a, st);
   if (!a.ragged) return launch_bwd_dkdv_split_bf16(a, st);
   const int T = ragged_tiles(a, 128);
   const Grid g = grid_of(T, a.B * a.Hkv * a.NG * a.parts, 1, 32);   // 32 CUs per XCD, one workgroup each
-  if (a.D == 64)
-    hipLaunchKernelGGL(bwd_dkdv_bf16_kernel<64>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
-  else
-    hipLaunchKernelGGL(bwd_dkdv_bf16_kernel<128>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
+  hipLaunchKernelGGL(bwd_dkdv_bf16_kernel, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 int launch_bwd_dq_bf16(const KArgs& a, hipStream_t st) {
+  if (a.D == 64) return launch_bwd_dq_d64(a, st);
   const int T = a.ragged ? ragged_tiles(a, 128) : a.G / 128;
   const Grid g = grid_of(T, a.B * a.H * a.NG, a.r, 64);               // 32 CUs per XCD, two workgroups each
-  if (a.D == 64)
-    hipLaunchKernelGGL((bwd_dq_bf16_kernel<true, 64>), dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
-  else if (a.ragged)
+  if (a.ragged)
     hipLaunchKernelGGL(bwd_dq_bf16_kernel<true>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
   else
     hipLaunchKernelGGL(bwd_dq_bf16_kernel<false>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);

@@ -87,12 +87,6 @@ __device__ __forceinline__ bf16x8 frag_tr(const char* tile, const LaneOffsets& o
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// Rows narrower than the 128-element tile (head dimension 64): the kernels built for partial
-// tiles have a second instantiation (DH = 64) that stages only the first eight 16-byte chunks
-// of every tile row, loads only the first four register fragments of a row, runs its products
-// over d = 0 .. 63 and stores the first half of the output tiles; the upper half of the LDS
-// rows is never read.
-
 // Direct global -> LDS copy of 16 bytes per lane (global_load_lds_dwordx4): lane i of
 // the wave fetches the 16 bytes at its own global address `g`, and they land at LDS byte
 // address lds_base + 16*i, where lds_base must be wave-uniform.  Issued as inline
