@@ -358,7 +358,7 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
       a.c_begin = c0;
       a.c_count = std::min(ds_heads, p->Hkv - c0);
       a.by_c_count = s2::div_by(a.c_count);
-      if (s2::launch_bwd_dkdv_split_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
+      if (s2::launch_bwd_dkdv_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
       if (c0 + ds_heads >= p->Hkv) mark(2);
       if (s2::launch_bwd_dq_spill_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
     }

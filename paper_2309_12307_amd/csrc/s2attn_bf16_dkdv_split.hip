@@ -1,7 +1,4 @@
-// bf16 S2-Attn backward, dK/dV kernel for gfx950, two waves per SIMD ("role split").
-// Used for tile-aligned shapes (D = 128, G % 128 == 0, shift % 64 == 0, a Variant 2 split that is
-// a multiple of 128); everything else runs the one-wave-per-SIMD kernel of s2attn_bf16_bwd.hip,
-// which computes the same thing.
+// bf16 S2-Attn backward, dK/dV kernel for gfx950 (D = 128), two waves per SIMD ("role split").
 //
 // A workgroup (8 waves on one CU) owns 128 keys of one (batch, kv head, group) in the rolled
 // frame of the kv head's class (LongLoRA Algorithm 1: the shift is row addressing only) and
@@ -104,7 +101,13 @@ __device__ __forceinline__ void store_ds(char* dst, bf16x8 v) {
 
 // SPILL: role B also stores dS of every tile it finishes (bf16, the operand it feeds to the
 // dK product) for the dQ kernel, which then needs neither S nor dP again.
-template <bool SPILL>
+// RAGGED: G is not a multiple of 128, the shift not of 64 or a Variant 2 split not of 128: the last
+// tiles of a run may be partial and the wrap point may fall inside a tile.  Such a tile is staged
+// row by row; every other tile is 64 consecutive tokens, wherever it starts, and takes the aligned
+// path.  N = 100000, H = 32, G = 25000: forward + backward 86.9 ms with a dK/dV kernel of its own for
+// these shapes (one wave per SIMD, every row staged by itself) and the four-wave forward, 82.1 ms
+// with this one and the eight-wave forward.
+template <bool SPILL, bool RAGGED>
 __global__ void __launch_bounds__(512, 1)
 bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
   __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
@@ -121,13 +124,20 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
   const int gidx = at.g, c = at.c, b = at.b;
   int h_lo, nheads, s;                               // query heads [h_lo, h_lo + nheads), all of one class
   part_heads(a, c, at.part, h_lo, nheads, s);
+  // the causal run of these keys and the query rows [j0, q_end) of it that see them: up to the end
+  // of the group, or up to the split for the first block of a split wrap-around group (Variant 2,
+  // Appendix B.3).  An aligned split is a multiple of the key tile; a ragged one makes two runs.
+  Run run{gidx * a.G, a.G};
+  if constexpr (RAGGED) {
+    if (!run_of_tile(a, gidx, s, 128, jt, run)) return;
+    jt = uni(jt); run.p0 = uni(run.p0); run.len = uni(run.len);
+  }
   const int j0 = jt * 128;
   const int kw0 = j0 + 32 * kb;                      // first key of this wave
   const int key = kw0 + l32;
-  // query rows visible to these keys: [j0, G), or [j0, split) for the first block of a split
-  // wrap-around group (Variant 2, Appendix B.3; the split is a multiple of the key tile here)
   const int split = uni(split_of_group(a, gidx, s));
-  const int nq = uni(((j0 < split ? split : a.G) - j0) / kQT);   // query tiles of one head, >= 2
+  const int q_end = RAGGED ? run.len : (j0 < split ? split : a.G);
+  const int nq = uni((q_end - j0 + kQT - 1) / kQT);   // query tiles of one head
   const int n_iter = nheads * nq;
   const float c2 = a.scale_log2;
 
@@ -135,7 +145,7 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
   // the accumulator that starts at delta ends as delta - dP)
   bf16x8 bfrag[8];
   {
-    const int tok = token_of(gidx * a.G + key, s, a.N);
+    const int tok = run_token(a, run, key, s);
     const bf16x8* src = reinterpret_cast<const bf16x8*>(
         role_b ? static_cast<const __bf16*>(a.v) + row_off(a.sv, b, tok, c)
                : static_cast<const __bf16*>(a.k) + row_off(a.sk, b, tok, c));
@@ -156,11 +166,25 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
   // tile (hh, it) of the flattened sequence n = hh * nq + it; q_stage = n mod 3, o_stage = n mod 2
   auto issue_tile = [&](int hh, int it, int q_stage, int o_stage) {
     const int h = h_lo + hh;
-    const uint32_t tok0 = (uint32_t)token_of(gidx * a.G + j0 + it * kQT, s, a.N);
-    const uint64_t qb = uni64(q_batch + tok0 * q_row_bytes + (uint64_t)h * a.sq.h * 2);
-    const uint64_t dob = uni64(do_batch + tok0 * do_row_bytes + (uint64_t)h * a.so.h * 2);
+    const int row0 = j0 + it * kQT;
+    const uint32_t tok0 = (uint32_t)token_of(run.p0 + row0, s, a.N);
     const uint32_t qs = smem_base + kOffQ + q_stage * kQTBytes + 4 * w * kRowBytes;
     const uint32_t dos = smem_base + kOffdO + o_stage * kQTBytes + 4 * w * kRowBytes;
+    const uint32_t rows_dst = smem_base + kOffRows + ((o_stage * 2 + w) * kQT) * 4;
+    if (RAGGED && (row0 + kQT > run.len || (int)tok0 + kQT > a.N)) {
+      // rows past the end of the run repeat its last row; their P is set to zero
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int tok = run_token(a, run, row0 + 32 * p + st_row, s);
+        dma16(static_cast<const char*>(a.q) + row_off(a.sq, b, tok, h) * 2 + st_chunk, qs + 32 * p * kRowBytes);
+        dma16(static_cast<const char*>(a.dout) + row_off(a.so, b, tok, h) * 2 + st_chunk, dos + 32 * p * kRowBytes);
+      }
+      if (w < 2)
+        dma4((w == 0 ? a.lse2 : a.delta) + ((size_t)b * a.H + h) * a.N + run_token(a, run, row0 + lane, s), rows_dst);
+      return;
+    }
+    const uint64_t qb = uni64(q_batch + tok0 * q_row_bytes + (uint64_t)h * a.sq.h * 2);
+    const uint64_t dob = uni64(do_batch + tok0 * do_row_bytes + (uint64_t)h * a.so.h * 2);
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       dma16s(qb + p * 32 * q_row_bytes, q_lane, qs + 32 * p * kRowBytes);
@@ -168,8 +192,7 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
     }
     if (w < 2) {   // wave 0: lse * log2(e), wave 1: delta; 64 rows each
       const uint64_t ro = (((uint64_t)b * a.H + h) * a.N + tok0) * 4;
-      const uint32_t dst = smem_base + kOffRows + ((o_stage * 2 + w) * kQT) * 4;
-      dma4s(uni64(reinterpret_cast<uint64_t>(w == 0 ? a.lse2 : a.delta) + ro), lane * 4, dst);
+      dma4s(uni64(reinterpret_cast<uint64_t>(w == 0 ? a.lse2 : a.delta) + ro), lane * 4, rows_dst);
     }
   };
 
@@ -213,7 +236,8 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
         const float* lse2_s = reinterpret_cast<const float*>(smem + kOffRows) + (o_st * 2) * kQT;
         char* Px = smem + kOffP + o_st * kPBufBytes + kb * 2 * kPBlockBytes + lane * 16;
         const int q0 = j0 + it * kQT;
-        const bool masked = it < 2;   // tiles 0 and 1 touch the diagonal of the 128 keys
+        // tiles 0 and 1 touch the diagonal of the 128 keys, a partial last tile holds padding rows
+        const bool masked = it < 2 || (RAGGED && q0 + kQT > run.len);
         // lse rows of both blocks (queries are register-indexed: 16 values per block and lane
         // half), fetched ahead of the scores so that the vector work below never waits on LDS
         float4 lr[2][4];
@@ -236,7 +260,10 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               float p = __builtin_amdgcn_exp2f(fmaf(sx[4 * vv + e], c2, -ls[e]));
-              if (MASKED && key > q0 + 32 * mb + 8 * vv + 4 * g32 + e) p = 0.f;
+              if constexpr (MASKED) {
+                const int row = q0 + 32 * mb + 8 * vv + 4 * g32 + e;
+                if (key > row || (RAGGED && row >= run.len)) p = 0.f;
+              }
               sx[4 * vv + e] = p;
             }
             *reinterpret_cast<float4*>(Px + mb * kPBlockBytes + vv * 1024) =
@@ -343,7 +370,8 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
   }
   if (a.dkv_partial) {   // contiguous fp32 partial of this part, summed by the combine pass
     const size_t elems = (size_t)a.B * a.N * a.Hkv * 128;
-    const int tok = token_of(gidx * a.G + key, s, a.N);
+    if (RAGGED && key >= run.len) return;   // padding key of a partial tile
+    const int tok = token_of(run.p0 + key, s, a.N);
     float* dst = a.dkv_partial + (size_t)((role_b ? 0 : a.parts) + at.part) * elems +
                  ((size_t)((size_t)b * a.N + tok) * a.Hkv + c) * 128 + 4 * g32;
     const float mul = role_b ? a.scale : 1.f;
@@ -366,7 +394,8 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
 #pragma unroll
   for (int it = 0; it < 8; ++it) {
     const int row = it * 4 + (lane >> 4), ch = lane & 15;
-    const int tok = token_of(gidx * a.G + kw0 + row, s, a.N);
+    if (RAGGED && kw0 + row >= run.len) continue;   // padding key of a partial tile
+    const int tok = token_of(run.p0 + kw0 + row, s, a.N);
     *reinterpret_cast<uint4*>(outp + row_off(so, b, tok, c) + ch * 8) =
         *reinterpret_cast<const uint4*>(region + tile_off(row, ch));
   }
@@ -374,13 +403,16 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
 
 }  // namespace
 
-int launch_bwd_dkdv_split_bf16(const KArgs& a, hipStream_t st) {
-  const int T = a.G / 128;
+int launch_bwd_dkdv_bf16(const KArgs& a, hipStream_t st) {
+  if (a.D == 64) return launch_bwd_dkdv_d64(a, st);
+  const int T = a.ragged ? ragged_tiles(a, 128) : a.G / 128;
   const Grid g = grid_of(T, a.B * a.c_count * a.NG * a.parts, 1, 32);   // 32 CUs per XCD, one workgroup each
   if (a.ds_spill)
-    hipLaunchKernelGGL(bwd_dkdv_split_kernel<true>, dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
+    hipLaunchKernelGGL((bwd_dkdv_split_kernel<true, false>), dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
+  else if (a.ragged)
+    hipLaunchKernelGGL((bwd_dkdv_split_kernel<false, true>), dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
   else
-    hipLaunchKernelGGL(bwd_dkdv_split_kernel<false>, dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
+    hipLaunchKernelGGL((bwd_dkdv_split_kernel<false, false>), dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

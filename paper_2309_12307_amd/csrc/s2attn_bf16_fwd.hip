@@ -325,14 +325,17 @@ __device__ __forceinline__ void mask_scores(f32x16& s0, f32x16& s1, int j0, int 
 }
 
 // ---------------------------------------------------------------------------
-// Eight-wave variant (G a multiple of 256): a workgroup owns 256 query rows and keeps
+// Eight-wave variant (groups of 2048 and more): a workgroup owns 256 query rows and keeps
 // three K/V stages in LDS, one workgroup per CU, two waves per SIMD.  Each wave runs
 // the tile loop software-pipelined across tiles: the matrix block of an iteration is
 // P(n) V(n) followed by S(n+1) = K(n+1) Q^T, the vector block is the softmax of one
 // tile.  Waves 0-3 run the vector block after the matrix block, waves 4-7 before it,
 // so the two waves that share a SIMD alternate between the matrix and vector units
 // instead of competing for them ("ping-pong"), with a single barrier per tile.
+// RAGGED: tiles of 256 rows that are not full, a wrap point inside a tile or a split off the tiles;
+// only the key tiles that are not 64 consecutive tokens are staged row by row.
 // ---------------------------------------------------------------------------
+template <bool RAGGED>
 __global__ void __launch_bounds__(512, 1)
 fwd_bf16_pp_kernel(KArgs a, int T, Deal deal) {
   constexpr int BM = 256;
@@ -347,18 +350,24 @@ fwd_bf16_pp_kernel(KArgs a, int T, Deal deal) {
   if (!decode_block(block_id(), T, deal, seq, rank)) return;
   const HeadPos at = head_of_seq(a, seq);
   const int gidx = at.g, c = at.c, b = at.b, h = at.h;
-  const int qt = T - 1 - rank;
+  int qt = T - 1 - rank;
 
   const int s = uni(shift_of_head(a, h));
-  const int split = uni(split_of_group(a, gidx, s));
+  Run run{gidx * a.G, a.G};
+  int split = uni(split_of_group(a, gidx, s));
+  if constexpr (RAGGED) {
+    if (!run_of_tile(a, gidx, s, BM, qt, run)) return;
+    qt = uni(qt); run.p0 = uni(run.p0); run.len = uni(run.len);
+    split = run.len + BM;   // no split inside a run
+  }
   const int i0 = qt * BM;
   const int qw0 = i0 + w * 32;
   const int qrow = qw0 + l32;
   const int jt_first = uni((i0 >= split ? split : 0) / BN);     // first tile any wave needs
-  const int nt = uni((i0 + BM - 1) / BN - jt_first + 1);   // tiles the workgroup walks
+  const int nt = uni((RAGGED ? min(i0 + BM, run.len) - 1 : i0 + BM - 1) / BN - jt_first + 1);   // tiles the workgroup walks
   // this wave's own tile range, relative to jt_first
   const int n_lo = uni((qw0 >= split ? split : 0) / BN - jt_first);
-  const int n_hi = uni((qw0 + 31) / BN - jt_first);
+  const int n_hi = uni(RAGGED && qw0 >= run.len ? -1 : (qw0 + 31) / BN - jt_first);   // -1: padding rows only
   const float c2 = a.scale_log2;
 
   const __bf16* qp = static_cast<const __bf16*>(a.q);
@@ -367,7 +376,7 @@ fwd_bf16_pp_kernel(KArgs a, int T, Deal deal) {
 
   bf16x8 qf[8];
   {
-    const int tok = token_of(gidx * a.G + qrow, s, a.N);
+    const int tok = run_token(a, run, qrow, s);
     const bf16x8* src = reinterpret_cast<const bf16x8*>(qp + row_off(a.sq, b, tok, h));
 #pragma unroll
     for (int st = 0; st < 8; ++st) qf[st] = src[2 * st + g32];
@@ -385,9 +394,19 @@ fwd_bf16_pp_kernel(KArgs a, int T, Deal deal) {
   const uint64_t k_head = uni64(reinterpret_cast<uint64_t>(kp) + row_off(a.sk, b, 0, c) * 2);
   const uint64_t v_head = uni64(reinterpret_cast<uint64_t>(vp) + row_off(a.sv, b, 0, c) * 2);
   auto issue_tile = [&](int n, int stage) {
-    const uint32_t tok0 = (uint32_t)token_of(gidx * a.G + (jt_first + n) * BN, s, a.N);
-    const uint64_t kb = k_head + tok0 * k_row_bytes, vb = v_head + tok0 * v_row_bytes;
+    const int row0 = (jt_first + n) * BN;
+    const uint32_t tok0 = (uint32_t)token_of(run.p0 + row0, s, a.N);
     const uint32_t ks = smem_base + stage * kStageBytes + 4 * w * kRowBytes;
+    if (RAGGED && (row0 + BN > run.len || (int)tok0 + BN > a.N)) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int tok = run_token(a, run, row0 + 32 * p + st_row, s);
+        dma16(kp + row_off(a.sk, b, tok, c) * 2 + st_chunk, ks + 32 * p * kRowBytes);
+        dma16(vp + row_off(a.sv, b, tok, c) * 2 + st_chunk, ks + 32 * p * kRowBytes + kTileBytes);
+      }
+      return;
+    }
+    const uint64_t kb = k_head + tok0 * k_row_bytes, vb = v_head + tok0 * v_row_bytes;
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       dma16s(kb + p * 32 * k_row_bytes, k_lane, ks + 32 * p * kRowBytes);
@@ -479,7 +498,7 @@ fwd_bf16_pp_kernel(KArgs a, int T, Deal deal) {
     const int t = st_cur; st_cur = st_nxt; st_nxt = st_free; st_free = t;
   }
   __syncthreads();
-  fwd_epilogue(a, st, smem + w * (32 * kRowBytes), b, h, Run{gidx * a.G, a.G}, s, qw0, c2, lane, l32, g32);
+  fwd_epilogue(a, st, smem + w * (32 * kRowBytes), b, h, run, s, qw0, c2, lane, l32, g32);
 }
 
 }  // namespace
@@ -490,10 +509,14 @@ int launch_fwd_bf16(const KArgs& a, hipStream_t st) {
   // groups of 2048 tokens or more: the eight-wave kernel; shorter tile sequences run a little
   // faster (4-9 % at G = 512 ... 1024) with two independent four-wave workgroups per CU, whose
   // prologues and epilogues overlap
-  if (a.G % 256 == 0 && a.G >= 2048 && !a.ragged) {
-    const int T = a.G / 256;
+  const bool partial = a.ragged || a.G % 256 != 0;   // tiles of 256 rows that are not full
+  if (a.G >= 2048) {
+    const int T = partial ? ragged_tiles(a, 256) : a.G / 256;
     const Grid g = grid_of(T, n_seq, a.r, 32);   // 32 CUs per XCD, one workgroup each
-    hipLaunchKernelGGL(fwd_bf16_pp_kernel, dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
+    if (partial)
+      hipLaunchKernelGGL(fwd_bf16_pp_kernel<true>, dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
+    else
+      hipLaunchKernelGGL(fwd_bf16_pp_kernel<false>, dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
     return hipGetLastError() == hipSuccess ? 0 : -1;
   }
   const int T = a.ragged ? ragged_tiles(a, 128) : a.G / 128;

@@ -9,14 +9,12 @@ int launch_fwd_f32(const KArgs& a, hipStream_t st);
 int launch_bwd_f32(const KArgs& a, hipStream_t st);        // dQ, dK and dV (or partials), delta included
 
 int launch_fwd_bf16(const KArgs& a, hipStream_t st);
-int launch_bwd_dkdv_bf16(const KArgs& a, hipStream_t st);  // delta must be ready
+int launch_bwd_dkdv_bf16(const KArgs& a, hipStream_t st);  // delta must be ready; a.ds_spill set: also stores the dS blobs
 int launch_bwd_dq_bf16(const KArgs& a, hipStream_t st);
 // head dimension 64, any shape (the three entry points above hand such calls on)
 int launch_fwd_d64(const KArgs& a, hipStream_t st);
 int launch_bwd_dkdv_d64(const KArgs& a, hipStream_t st);
 int launch_bwd_dq_d64(const KArgs& a, hipStream_t st);
-// two-waves-per-SIMD dK/dV kernel for tile-aligned shapes (not a.ragged)
-int launch_bwd_dkdv_split_bf16(const KArgs& a, hipStream_t st);   // a.ds_spill set: also stores the dS blobs
 // dQ from the dS blobs the dK/dV kernel stored (same shapes)
 int launch_bwd_dq_spill_bf16(const KArgs& a, hipStream_t st);
 

@@ -1,0 +1,35 @@
+"""Head dimension 128, runs that no tile divides: dK/dV (64 query rows a tile, 128 keys a workgroup)
+at group sizes one step below, at and above each edge, the eight-wave forward (32 rows a wave, 256 a
+workgroup, groups of 2048 and more) likewise, with the wrap point of the roll at a tile's edge and
+inside one, and the wrap-around group cut at its seam, against the oracle.  Bounds: those of the
+parity tests."""
+import pytest
+
+from oracle import s2attn_oracle as orc
+from paper_2309_12307_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def check(G, groups, shift, split):
+    from gpu_util import run_hip
+    from test_gpu_parity_bf16 import compare
+    inp = inputs.make_inputs(1, groups * G, 4, 2, 128, seed=700 + G + shift, dtype="bf16")
+    out = run_hip(inp, G, "bf16", shift=shift, wrap_variant=2 if split else 0)
+    compare(out, orc.s2attn_fwd_bwd(inp["q"], inp["k"], inp["v"], inp["do"], G, shift=shift, variant2=split))
+
+
+@pytest.mark.parametrize("G", [2, 62, 64, 66, 126, 128, 130, 190, 192, 194, 258, 322])
+@pytest.mark.parametrize("shift", ["half", "odd", "tile"])
+def test_dkdv_group_sizes_around_the_tiles(G, shift):
+    s = {"half": G // 2, "odd": G // 2 + 1, "tile": 64}[shift]
+    if s >= G:
+        pytest.skip("the shift is smaller than the group")
+    for split in (False, True):
+        check(G, 3, s, split)
+
+
+@pytest.mark.parametrize("G", [2046, 2048, 2050, 2078, 2082, 2110, 2112, 2114, 2176, 2302, 2306])
+@pytest.mark.parametrize("shift,split", [("half", False), ("odd", False), ("odd", True), (128, True)])
+def test_eight_wave_forward_group_sizes_around_the_tiles(G, shift, split):
+    check(G, 2, {"half": G // 2, "odd": G // 2 + 1}.get(shift, shift), split)
