@@ -324,7 +324,7 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
   rc = check_device();
   if (rc != S2ATTN_OK) return rc;
   s2::KArgs a = make_kargs(p);
-  a.delta = static_cast<float*>(p->workspace);
+  a.neg_delta = static_cast<float*>(p->workspace);
   a.lse2 = reinterpret_cast<float*>(static_cast<char*>(p->workspace) + delta_bytes(p->B, p->N, p->H));
   const size_t rows = 2 * delta_bytes(p->B, p->N, p->H);
   // the stored-dS backward writes its dS one kv head after the other and does not cut the heads

@@ -144,7 +144,7 @@ bwd_dq_bf16_kernel(KArgs a, int T, Deal deal) {
     for (int st = 0; st < 8; ++st) { qf[st] = qsrc[2 * st + g32]; dof[st] = dsrc[2 * st + g32]; }
     const size_t ro = ((size_t)b * a.H + h) * a.N + tok;
     lse2 = a.lse2[ro];
-    delta = a.delta[ro];
+    delta = -a.neg_delta[ro];
   }
 
   const uint32_t smem_base = lds_addr(smem);
@@ -206,7 +206,7 @@ bwd_dq_bf16_kernel(KArgs a, int T, Deal deal) {
 
   char* region = smem + w * (32 * kRowBytes);
   acc_to_lds(region, dq_acc, a.scale, l32, g32);
-  __syncthreads();
+  wave_lds_order();
   __bf16* dqp = static_cast<__bf16*>(a.dq);
 #pragma unroll
   for (int it = 0; it < 8; ++it) {

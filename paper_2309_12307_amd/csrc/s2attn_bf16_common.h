@@ -190,6 +190,13 @@ __device__ __forceinline__ f32x16 zero16() {
   return z;
 }
 
+// Between a wave's writes to and its lanes' reads from LDS that no other wave touches: LDS serves
+// the instructions of a wave in order, so only the compiler has to keep them so.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Transposes a wave's 32 x 128 accumulator block (rows lane-indexed, columns
 // register-indexed) through its private 8 KB LDS region.
 __device__ __forceinline__ void acc_to_lds(char* region, const f32x16 (&acc)[4], float mul, int l32, int g32) {

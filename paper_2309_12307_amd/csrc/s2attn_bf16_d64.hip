@@ -253,10 +253,10 @@ fwd_d64_kernel(KArgs a, int T, Deal deal) {
 // masked tiles: 2720 us at the size above, 2256 now.
 // ===========================================================================
 struct RowTerms {
-  float lse2[kTR], delta[kTR];
+  float lse2[kTR], neg_delta[kTR];
 };
 
-// One 32-query block (MB) of a tile: scores and delta - dP, and the operands made of them.
+// One 32-query block (MB) of a tile: scores and dP - delta, and the operands made of them.
 struct Block64 {
   f32x16 s, dp;
 };
@@ -267,10 +267,10 @@ __device__ __forceinline__ void sc_load64(bf16x8 (&buf)[8], const char* Qs, cons
 }
 template <int MB>
 __device__ __forceinline__ void dp_init64(Block64& x, const RowTerms& rows, int g32) {
-  // starts at delta, and V is negated: ends as delta - dP
+  // starts at -delta: ends as dP - delta
 #pragma unroll
   for (int vv = 0; vv < 4; ++vv) {
-    const float4 d4 = *reinterpret_cast<const float4*>(&rows.delta[32 * MB + 8 * vv + 4 * g32]);
+    const float4 d4 = *reinterpret_cast<const float4*>(&rows.neg_delta[32 * MB + 8 * vv + 4 * g32]);
     x.dp[4 * vv] = d4.x; x.dp[4 * vv + 1] = d4.y; x.dp[4 * vv + 2] = d4.z; x.dp[4 * vv + 3] = d4.w;
   }
 }
@@ -320,7 +320,7 @@ __device__ __forceinline__ void softmax64(Block64& x, const RowTerms& rows, bf16
         if (key > q || q >= q_lim) p = 0.f;
       }
       x.s[v] = p;
-      x.dp[v] = p * -x.dp[v];
+      x.dp[v] *= p;
     }
   }
 #pragma unroll
@@ -398,16 +398,13 @@ bwd_dkdv_d64_kernel(KArgs a, int T, Deal deal) {
   const int n_iter = nheads * nq;
   const float c2 = a.scale_log2;
 
-  bf16x8 kf[4], vf[4];   // K^T and -V^T of this wave's keys
+  bf16x8 kf[4], vf[4];   // K^T and V^T of this wave's keys
   {
     const int tok = run_token(a, run, key, s);
     const bf16x8* ks = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(a.k) + row_off(a.sk, b, tok, c));
     const bf16x8* vs = reinterpret_cast<const bf16x8*>(static_cast<const __bf16*>(a.v) + row_off(a.sv, b, tok, c));
 #pragma unroll
-    for (int k = 0; k < 4; ++k) { kf[k] = ks[2 * k + g32]; vf[k] = -vs[2 * k + g32]; }
-    // the sign is flipped here, once: the compiler otherwise does it in every tile (48 instructions)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(vf[k]));
+    for (int k = 0; k < 4; ++k) { kf[k] = ks[2 * k + g32]; vf[k] = vs[2 * k + g32]; }
   }
   const uint64_t q_rb = (uint64_t)a.sq.t * 2, do_rb = (uint64_t)a.so.t * 2;
   const uint64_t q_batch = uni64(reinterpret_cast<uint64_t>(a.q) + row_off(a.sq, b, 0, 0) * 2);
@@ -418,8 +415,8 @@ bwd_dkdv_d64_kernel(KArgs a, int T, Deal deal) {
     const int h = h_lo + hh, t0 = j0 + it * kTR;
     stage_pair(a, run, s, t0, sg, w, q_batch + (uint64_t)h * a.sq.h * 2, q_rb, do_batch + (uint64_t)h * a.so.h * 2,
                do_rb, base + stage * 2 * kTile, base + stage * 2 * kTile + kTile);
-    if (w < 2) {   // wave 0: lse * log2(e), wave 1: delta
-      const float* src = (w == 0 ? a.lse2 : a.delta) + ((size_t)b * a.H + h) * a.N + run_token(a, run, t0 + lane, s);
+    if (w < 2) {   // wave 0: lse * log2(e), wave 1: -delta
+      const float* src = (w == 0 ? a.lse2 : a.neg_delta) + ((size_t)b * a.H + h) * a.N + run_token(a, run, t0 + lane, s);
       dma4(src, rows_base + stage * (uint32_t)sizeof(RowTerms) + w * kTR * 4);
     }
   };
@@ -551,7 +548,7 @@ bwd_dq_d64_kernel(KArgs a, int T, Deal deal) {
     for (int k = 0; k < 4; ++k) { qf[k] = qs[2 * k + g32]; dof[k] = ds[2 * k + g32]; }
     const size_t ro = ((size_t)b * a.H + h) * a.N + tok;
     lse2 = a.lse2[ro];
-    const float nd = -a.delta[ro];
+    const float nd = a.neg_delta[ro];
 #pragma unroll
     for (int v = 0; v < 16; ++v) neg_delta[v] = nd;
   }

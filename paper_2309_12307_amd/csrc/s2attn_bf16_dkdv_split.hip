@@ -8,7 +8,7 @@
 // log-sum-exp) are split between the two waves that share a SIMD and a 32-key block, so that
 // each fits in 256 registers with all accumulators in ordinary vector registers:
 //   wave A (0-3):  S = Q K^T,  P = exp2(c S - lse2)  ->  LDS (fp32),   dV^T += dO^T P
-//   wave B (4-7):  delta - dP = delta - dO V^T,  P <- LDS,  dS = P (dP - delta),  dK^T += Q^T dS
+//   wave B (4-7):  dP - delta = dO V^T - delta,  P <- LDS,  dS = P (dP - delta),  dK^T += Q^T dS
 // B finishes tile n-1 (dS, dK) at the start of iteration n, after the barrier that also
 // publishes the staged tile n, so the hand-over of P costs no barrier of its own, and the
 // two waves of a SIMD alternate between the matrix and the vector unit.  Keys are
@@ -33,12 +33,12 @@ constexpr int kOffdO = 3 * kQTBytes;               // 2 stages of dO
 constexpr int kOffP = 5 * kQTBytes;                // 2 buffers x 4 key blocks x 2 query blocks x 4 KB (fp32 P)
 constexpr int kPBlockBytes = 4096;
 constexpr int kPBufBytes = 4 * 2 * kPBlockBytes;   // 32 KB
-constexpr int kOffRows = kOffP + 2 * kPBufBytes;   // [2 stages][lse2, delta][64] floats
+constexpr int kOffRows = kOffP + 2 * kPBufBytes;   // [2 stages][lse2, -delta][64] floats
 constexpr int kSmemBytes = kOffRows + 2 * 2 * kQT * 4;
 
 // Scores of both 32-query blocks of a tile against this wave's 32 keys: acc0/acc1 +=
 // X[block] Bf^T, X = Q (role A) or dO (role B) read row-major from LDS, Bf = the wave's
-// K^T or -V^T fragments.  Steps of 4 MFMAs; every step first issues the reads of the next.
+// K^T or V^T fragments.  Steps of 4 MFMAs; every step first issues the reads of the next.
 template <int STEP>
 __device__ __forceinline__ void sc_load(bf16x8 (&buf)[4], const char* Xs, const LaneOffsets& lo) {
   buf[0] = frag_rm<0>(Xs, lo, 2 * STEP);
@@ -141,8 +141,7 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
   const int n_iter = nheads * nq;
   const float c2 = a.scale_log2;
 
-  // loop-invariant B operand of this wave's 32 keys: K^T (role A) or -V^T (role B, so that
-  // the accumulator that starts at delta ends as delta - dP)
+  // loop-invariant B operand of this wave's 32 keys: K^T (role A) or V^T (role B)
   bf16x8 bfrag[8];
   {
     const int tok = run_token(a, run, key, s);
@@ -150,7 +149,7 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
         role_b ? static_cast<const __bf16*>(a.v) + row_off(a.sv, b, tok, c)
                : static_cast<const __bf16*>(a.k) + row_off(a.sk, b, tok, c));
 #pragma unroll
-    for (int st = 0; st < 8; ++st) bfrag[st] = role_b ? -src[2 * st + g32] : src[2 * st + g32];
+    for (int st = 0; st < 8; ++st) bfrag[st] = src[2 * st + g32];
   }
 
   // staging: wave w fills tile rows 4w .. 4w+3 and 32+4w .. 32+4w+3 of Q and of dO; a tile is
@@ -180,7 +179,7 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
         dma16(static_cast<const char*>(a.dout) + row_off(a.so, b, tok, h) * 2 + st_chunk, dos + 32 * p * kRowBytes);
       }
       if (w < 2)
-        dma4((w == 0 ? a.lse2 : a.delta) + ((size_t)b * a.H + h) * a.N + run_token(a, run, row0 + lane, s), rows_dst);
+        dma4((w == 0 ? a.lse2 : a.neg_delta) + ((size_t)b * a.H + h) * a.N + run_token(a, run, row0 + lane, s), rows_dst);
       return;
     }
     const uint64_t qb = uni64(q_batch + tok0 * q_row_bytes + (uint64_t)h * a.sq.h * 2);
@@ -190,9 +189,9 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
       dma16s(qb + p * 32 * q_row_bytes, q_lane, qs + 32 * p * kRowBytes);
       dma16s(dob + p * 32 * do_row_bytes, do_lane, dos + 32 * p * kRowBytes);
     }
-    if (w < 2) {   // wave 0: lse * log2(e), wave 1: delta; 64 rows each
+    if (w < 2) {   // wave 0: lse * log2(e), wave 1: -delta; 64 rows each
       const uint64_t ro = (((uint64_t)b * a.H + h) * a.N + tok0) * 4;
-      dma4s(uni64(reinterpret_cast<uint64_t>(w == 0 ? a.lse2 : a.delta) + ro), lane * 4, rows_dst);
+      dma4s(uni64(reinterpret_cast<uint64_t>(w == 0 ? a.lse2 : a.neg_delta) + ro), lane * 4, rows_dst);
     }
   };
 
@@ -222,7 +221,8 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
     // ------------------------------------------------------------------ role A
     int hh_cur = 0, it = it_first;    // tile n
     int q_st = 0;                     // n mod 3
-    for (int n = 0; n <= n_iter; ++n) {
+    int n = 0;
+    do {
       const int o_st = n & 1;
       wait_vmcnt0();        // this wave's part of tile n has landed
       __syncthreads();      // tile n is complete; everyone has left iteration n-1
@@ -284,11 +284,11 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
       }
       advance(hh_cur, it);
       q_st = q_st == 2 ? 0 : q_st + 1;
-    }
+    } while (++n <= n_iter);
   } else {
     // ------------------------------------------------------------------ role B
     int q_st = 0;                     // n mod 3
-    f32x16 dp0 = zero16(), dp1 = zero16();   // delta - dP of the pending tile
+    f32x16 dp0 = zero16(), dp1 = zero16();   // dP - delta of the pending tile
     // dS blobs of this workgroup: those of key tile jt of head h_lo, one after the other along
     // the query tiles; the next head's are a whole (head, group-count) block further on
     char* ds_lane = nullptr;
@@ -302,7 +302,8 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
       ds_lane = static_cast<char*>(a.ds_spill) + first * kDsBlobBytes + kb * 4096 + lane * 16;
       ds_head_stride = (long long)a.NG * per_group * kDsBlobBytes;
     }
-    for (int n = 0; n <= n_iter; ++n) {
+    int n = 0;
+    do {
       const int o_st = n & 1;
       wait_vmcnt0();
       __syncthreads();      // also publishes the P of tile n-1
@@ -330,10 +331,10 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
 #pragma unroll
           for (int vv = 0; vv < 4; ++vv) {
             const float4 p4 = pr[mb][vv];
-            dx[4 * vv + 0] = p4.x * -dx[4 * vv + 0];
-            dx[4 * vv + 1] = p4.y * -dx[4 * vv + 1];
-            dx[4 * vv + 2] = p4.z * -dx[4 * vv + 2];
-            dx[4 * vv + 3] = p4.w * -dx[4 * vv + 3];
+            dx[4 * vv + 0] = p4.x * dx[4 * vv + 0];
+            dx[4 * vv + 1] = p4.y * dx[4 * vv + 1];
+            dx[4 * vv + 2] = p4.z * dx[4 * vv + 2];
+            dx[4 * vv + 3] = p4.w * dx[4 * vv + 3];
           }
           dsf[2 * mb] = pack8(dx[0], dx[1], dx[2], dx[3], dx[4], dx[5], dx[6], dx[7]);
           dsf[2 * mb + 1] = pack8(dx[8], dx[9], dx[10], dx[11], dx[12], dx[13], dx[14], dx[15]);
@@ -351,13 +352,13 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
         advance(hh_cur, it_cur);
       }
       if (has_cur) {
-        // delta - dP of tile n: the accumulators start at delta (per query row = per register);
+        // dP - delta of tile n: the accumulators start at -delta (per query row = per register);
         // the rows are fetched here so that they arrive during the matrix work below
-        const float* delta_s = reinterpret_cast<const float*>(smem + kOffRows) + (o_st * 2 + 1) * kQT;
+        const float* nd_s = reinterpret_cast<const float*>(smem + kOffRows) + (o_st * 2 + 1) * kQT;
 #pragma unroll
         for (int vv = 0; vv < 4; ++vv) {
-          const float4 d0 = *reinterpret_cast<const float4*>(delta_s + 8 * vv + 4 * g32);
-          const float4 d1 = *reinterpret_cast<const float4*>(delta_s + 32 + 8 * vv + 4 * g32);
+          const float4 d0 = *reinterpret_cast<const float4*>(nd_s + 8 * vv + 4 * g32);
+          const float4 d1 = *reinterpret_cast<const float4*>(nd_s + 32 + 8 * vv + 4 * g32);
           dp0[4 * vv] = d0.x; dp0[4 * vv + 1] = d0.y; dp0[4 * vv + 2] = d0.z; dp0[4 * vv + 3] = d0.w;
           dp1[4 * vv] = d1.x; dp1[4 * vv + 1] = d1.y; dp1[4 * vv + 2] = d1.z; dp1[4 * vv + 3] = d1.w;
         }
@@ -366,7 +367,7 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
       if (has_prev) accumulate(acc, fa, fb, Qs, lo, dsf);   // dK^T += Q^T dS
       if (has_cur) scores(dp0, dp1, smem + kOffdO + o_st * kQTBytes, lo, bfrag);
       q_st = q_st == 2 ? 0 : q_st + 1;
-    }
+    } while (++n <= n_iter);
   }
   if (a.dkv_partial) {   // contiguous fp32 partial of this part, summed by the combine pass
     const size_t elems = (size_t)a.B * a.N * a.Hkv * 128;
@@ -383,12 +384,19 @@ bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
             make_float4(acc[db][4 * vv] * mul, acc[db][4 * vv + 1] * mul, acc[db][4 * vv + 2] * mul, acc[db][4 * vv + 3] * mul);
     return;
   }
-  __syncthreads();
 
-  // ---- store this wave's 32 x 128 block (dV for role A, dK for role B) at un-rolled rows
-  char* region = smem + w * (32 * kRowBytes);
+  // ---- store this wave's 32 x 128 block (dV for role A, dK for role B) at un-rolled rows, turned
+  // through LDS that nobody else touches after the barrier of the last iteration, so that no
+  // further barrier is needed and A stores dV while B still works on the last tile: A the dO
+  // stages (read up to iteration n_iter - 1), B its part of the P buffer that this iteration's A
+  // would have filled.
+  // What a workgroup does before its first and after its last tile is a sixth of its time at
+  // G = 2048: this, V without the sign it was once loaded with and the set-up moved ahead of the
+  // wait for the key fragments take 1.4 % off forward + backward at N = 8192, H = 32, G = 2048.
+  static_assert(2 * kQTBytes == 4 * 32 * kRowBytes && 2 * kPBlockBytes == 32 * kRowBytes, "one block per wave");
+  char* region = smem + (role_b ? kOffP + (n_iter & 1) * kPBufBytes : kOffdO) + kb * (32 * kRowBytes);
   acc_to_lds(region, acc, role_b ? a.scale : 1.f, l32, g32);
-  __syncthreads();
+  wave_lds_order();
   __bf16* outp = static_cast<__bf16*>(role_b ? a.dk : a.dv);
   const TStride so = role_b ? a.sdk : a.sdv;
 #pragma unroll

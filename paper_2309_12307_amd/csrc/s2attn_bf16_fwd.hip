@@ -133,8 +133,7 @@ __device__ __forceinline__ void fwd_tile(FwdState& st, const bf16x8 (&qf)[8], co
 }
 
 // Normalises a wave's 32 x 128 output block, transposes it through the wave's private
-// 8 KB LDS region and stores it (and lse) at the un-rolled token rows.  Contains one
-// workgroup barrier between the LDS writes and reads.
+// 8 KB LDS region and stores it (and lse) at the un-rolled token rows.
 __device__ __forceinline__ void fwd_epilogue(const KArgs& a, FwdState& st, char* Os, int b, int h, const Run& run, int s,
                                              int qw0, float c2, int lane, int l32, int g32) {
   __bf16* op = static_cast<__bf16*>(a.o);
@@ -148,7 +147,7 @@ __device__ __forceinline__ void fwd_epilogue(const KArgs& a, FwdState& st, char*
                               st.o_acc[db][4 * vv + 2] * inv, st.o_acc[db][4 * vv + 3] * inv);
       *reinterpret_cast<bf16x4*>(Os + tile_off(l32, 4 * db + vv) + 8 * g32) = pk;
     }
-  __syncthreads();
+  wave_lds_order();
 #pragma unroll
   for (int it = 0; it < 8; ++it) {
     const int row = it * 4 + (lane >> 4), ch = lane & 15;

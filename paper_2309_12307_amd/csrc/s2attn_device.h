@@ -37,7 +37,7 @@ struct KArgs {
   void* o; float* lse;                       // forward outputs / backward inputs
   const void* dout;
   void* dq; void* dk; void* dv;
-  float* delta;                              // (B,H,N) fp32
+  float* neg_delta;                          // (B,H,N) fp32: -delta, written by the pre-pass
   float* lse2;                               // (B,H,N) fp32: lse * log2(e), written by the pre-pass
   float* dkv_partial;                        // fp32 [dk, dv][parts][B,N,Hkv,D] or null
   void* ds_spill;                            // bf16 dS tiles handed from the dK/dV kernel to the dQ kernel, or null

@@ -1,6 +1,7 @@
 // Backward pre-pass of the bf16 path and post-pass of both paths.
 //   delta:   the row term of the softmax Jacobian, delta_i = sum_j P_ij dP_ij = dO_i . O_i;
-//            the same pass rescales lse to base 2 for the kernels' exp2
+//            stored negated, as the dP accumulators of dK/dV start with it; the same pass
+//            rescales lse to base 2 for the kernels' exp2
 //   combine: sum of the fp32 partials of dK/dV when the query heads of a kv head are cut into
 //            parts (always when one kv head serves both shifted and unshifted query heads).
 // Both are pure streaming kernels (HBM-bound, 16-byte coalesced accesses).
@@ -21,7 +22,7 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {   // round to ne
 
 // 16 lanes per (b,t,h) row; each lane reads 16-byte chunks.
 __global__ void __launch_bounds__(256) delta_kernel(const void* o, const void* dout, const float* lse,
-                                                    float* delta, float* lse2, int B, int N, int H, int D) {
+                                                    float* neg_delta, float* lse2, int B, int N, int H, int D) {
   const size_t row = (size_t)block_id() * 16 + thread_id() / 16;
   const int lane = thread_id() % 16;
   const size_t rows = (size_t)B * N * H;
@@ -47,7 +48,7 @@ __global__ void __launch_bounds__(256) delta_kernel(const void* o, const void* d
     const size_t bt = row / H;
     const int h = (int)(row % H);
     const size_t b = bt / N, t = bt % N;
-    delta[(b * H + h) * N + t] = acc;
+    neg_delta[(b * H + h) * N + t] = -acc;
     lse2[(b * H + h) * N + t] = lse[(b * H + h) * N + t] * 1.4426950408889634f;
   }
 }
@@ -90,7 +91,7 @@ __global__ void __launch_bounds__(256) combine_kernel(const float* partial, void
 int launch_delta_bf16(const KArgs& a, hipStream_t st) {
   const size_t rows = (size_t)a.B * a.N * a.H;
   dim3 grid((unsigned)((rows + 15) / 16));
-  hipLaunchKernelGGL(delta_kernel, grid, dim3(256), 0, st, a.o, a.dout, a.lse, a.delta, a.lse2, a.B, a.N, a.H, a.D);
+  hipLaunchKernelGGL(delta_kernel, grid, dim3(256), 0, st, a.o, a.dout, a.lse, a.neg_delta, a.lse2, a.B, a.N, a.H, a.D);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
