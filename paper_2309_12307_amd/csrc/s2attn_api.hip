@@ -365,9 +365,11 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
     mark(3);
     return S2ATTN_OK;
   }
-  if (s2::launch_bwd_dkdv_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
+  const int both = s2::launch_bwd_both_bf16(a, st);
+  if (both < 0) return S2ATTN_ERR_LAUNCH;
+  if (both > 0 && s2::launch_bwd_dkdv_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
   mark(2);
-  if (s2::launch_bwd_dq_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
+  if (both > 0 && s2::launch_bwd_dq_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
   if (a.parts > 1 && s2::launch_combine_partials(a, p->dtype, st) != 0) return S2ATTN_ERR_LAUNCH;
   mark(3);
   return S2ATTN_OK;

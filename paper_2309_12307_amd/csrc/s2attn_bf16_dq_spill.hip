@@ -1,5 +1,5 @@
 // bf16 S2-Attn backward, dQ from stored dS (gfx950).  Tile-aligned shapes only: the dK/dV
-// kernel of s2attn_bf16_dkdv_split.hip has stored dS = P * (dP - delta) of every tile it
+// kernel of s2attn_bf16_bwd.hip has stored dS = P * (dP - delta) of every tile it
 // visited (layout: s2attn_device.h), so dQ = scale * dS K is a plain product here, with
 // neither the scores nor the softmax recomputed: 2 D flops per (query, key) pair instead of
 // the 6 D of the recomputing dQ kernel.  The kernel is bound by reading dS once from HBM

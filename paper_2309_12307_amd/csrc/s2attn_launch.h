@@ -11,6 +11,8 @@ int launch_bwd_f32(const KArgs& a, hipStream_t st);        // dQ, dK and dV (or 
 int launch_fwd_bf16(const KArgs& a, hipStream_t st);
 int launch_bwd_dkdv_bf16(const KArgs& a, hipStream_t st);  // delta must be ready; a.ds_spill set: also stores the dS blobs
 int launch_bwd_dq_bf16(const KArgs& a, hipStream_t st);
+// both in one launch for the shapes that gain by it; 1 and no launch for the others
+int launch_bwd_both_bf16(const KArgs& a, hipStream_t st);
 // head dimension 64, any shape (the three entry points above hand such calls on)
 int launch_fwd_d64(const KArgs& a, hipStream_t st);
 int launch_bwd_dkdv_d64(const KArgs& a, hipStream_t st);

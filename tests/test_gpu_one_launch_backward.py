@@ -1,0 +1,31 @@
+"""dK/dV and dQ in one launch (few workgroups) and one by one: group sizes at the edges of the 256-row
+dQ tile, dK/dV first and dQ first (one or several query heads to a kv head), the largest grid that
+takes one launch (1536 workgroups of 512 threads) and the next one, against the oracle.  Bounds:
+those of the parity tests."""
+import pytest
+
+from oracle import s2attn_oracle as orc
+from paper_2309_12307_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def check(B, N, H, Hkv, G, **kw):
+    from gpu_util import run_hip
+    from test_gpu_parity_bf16 import compare
+    inp = inputs.make_inputs(B, N, H, Hkv, 128, seed=800 + N + H + Hkv, dtype="bf16")
+    out = run_hip(inp, G, "bf16", **kw)
+    compare(out, orc.s2attn_fwd_bwd(inp["q"], inp["k"], inp["v"], inp["do"], G, variant2=bool(kw)))
+
+
+@pytest.mark.parametrize("Hkv", [4, 1])
+@pytest.mark.parametrize("G", [128, 254, 256, 258, 384, 512, 514, 640])
+@pytest.mark.parametrize("split", [False, True])
+def test_group_sizes_around_the_dq_tile(G, Hkv, split):
+    check(1, 3 * G, 4, Hkv, G, **(dict(wrap_variant=2) if split else {}))
+
+
+# 256 keys and 256 query rows a group: two workgroups of dK/dV and one of dQ per group and head
+@pytest.mark.parametrize("groups", [16, 17])
+def test_largest_grid_of_one_launch_and_the_next(groups):
+    check(4, 256 * groups, 8, 8, 256)
