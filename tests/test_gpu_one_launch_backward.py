@@ -11,11 +11,16 @@ pytestmark = pytest.mark.gpu
 
 
 def check(B, N, H, Hkv, G, **kw):
-    from gpu_util import run_hip
-    from test_gpu_parity_bf16 import compare
+    from gpu_util import check_bf16_tensor, max_abs, run_hip
     inp = inputs.make_inputs(B, N, H, Hkv, 128, seed=800 + N + H + Hkv, dtype="bf16")
     out = run_hip(inp, G, "bf16", **kw)
-    compare(out, orc.s2attn_fwd_bwd(inp["q"], inp["k"], inp["v"], inp["do"], G, variant2=bool(kw)))
+    o, lse, dq, dk, dv = orc.s2attn_fwd_bwd(inp["q"], inp["k"], inp["v"], inp["do"], G, variant2=bool(kw))
+    assert max_abs(out["lse"], lse) <= 2e-3
+    # 2e-2 + the rounding of the value to its bf16 output (2^-8 |value| at most), element by element.  The
+    # plain 2e-2 that the parity tests also ask of o and dq holds for elements below 1; the 16.8 million
+    # of dq in the last test, in groups of 256, have larger ones (0.0230 off, 0.0039 of it rounding).
+    for name, r in (("o", o), ("dq", dq), ("dk", dk), ("dv", dv)):
+        check_bf16_tensor(name, out[name], r)
 
 
 @pytest.mark.parametrize("Hkv", [4, 1])
