@@ -395,16 +395,7 @@ __device__ __forceinline__ void dkdv_workgroup(const KArgs& a, int T, const Deal
   char* region = smem + (role_b ? kOffP + (n_iter & 1) * kPBufBytes : kOffdO) + kb * (32 * kRowBytes);
   acc_to_lds(region, acc, role_b ? a.scale : 1.f, l32, g32);
   wave_lds_order();
-  __bf16* outp = static_cast<__bf16*>(role_b ? a.dk : a.dv);
-  const TStride so = role_b ? a.sdk : a.sdv;
-#pragma unroll
-  for (int it = 0; it < 8; ++it) {
-    const int row = it * 4 + (lane >> 4), ch = lane & 15;
-    if (RAGGED && kw0 + row >= run.len) continue;   // padding key of a partial tile
-    const int tok = token_of(run.p0 + kw0 + row, s, a.N);
-    *reinterpret_cast<uint4*>(outp + row_off(so, b, tok, c) + ch * 8) =
-        *reinterpret_cast<const uint4*>(region + tile_off(row, ch));
-  }
+  store_wave_rows<RAGGED>(a, role_b ? a.dk : a.dv, role_b ? a.sdk : a.sdv, region, run, kw0, s, b, c, lane);
 }
 
 template <bool SPILL, bool RAGGED>

@@ -210,4 +210,30 @@ __device__ __forceinline__ void acc_to_lds(char* region, const f32x16 (&acc)[4],
     }
 }
 
+// Stores the 32 rows that acc_to_lds left in a wave's region at the un-rolled token rows of run rows
+// row0 .. row0 + 31.  Aligned: 32 consecutive tokens, all inside the run, so one address and a
+// stride; asked row by row whether it is inside the run, the eight reads from LDS each waited for
+// the store before.
+template <bool RAGGED>
+__device__ __forceinline__ void store_wave_rows(const KArgs& a, void* out, const TStride& st, const char* region,
+                                                const Run& run, int row0, int s, int b, int h, int lane) {
+  const int sub = lane >> 4, ch = lane & 15;
+  uint4 val[8];
+#pragma unroll
+  for (int it = 0; it < 8; ++it) val[it] = *reinterpret_cast<const uint4*>(region + tile_off(it * 4 + sub, ch));
+  __bf16* head = static_cast<__bf16*>(out) + row_off(st, b, 0, h) + ch * 8;
+  if constexpr (!RAGGED) {
+    __bf16* p = head + (long long)(token_of(run.p0 + row0, s, a.N) + sub) * st.t;
+#pragma unroll
+    for (int it = 0; it < 8; ++it) *reinterpret_cast<uint4*>(p + it * 4 * st.t) = val[it];
+  } else {
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+      const int row = row0 + it * 4 + sub;
+      if (row < run.len)   // rows past the end of the run are padding of a partial tile
+        *reinterpret_cast<uint4*>(head + (long long)token_of(run.p0 + row, s, a.N) * st.t) = val[it];
+    }
+  }
+}
+
 }  // namespace s2

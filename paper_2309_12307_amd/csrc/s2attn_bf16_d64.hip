@@ -116,13 +116,16 @@ __device__ __forceinline__ void wave_rows(char* region, const f32x16 (&acc)[2], 
 }
 __device__ __forceinline__ void store_rows(const KArgs& a, void* out, const TStride& so, const char* region,
                                            const Run& run, int row0, int s, int b, int h, int lane) {
+  const int sub = lane >> 3, ch = lane & 7;
+  uint4 val[4];   // all read before the first store: a store behind a test otherwise holds up the next read
+#pragma unroll
+  for (int it = 0; it < 4; ++it) val[it] = *reinterpret_cast<const uint4*>(region + tile_off64(it * 8 + sub, ch));
+  __bf16* head = static_cast<__bf16*>(out) + row_off(so, b, 0, h) + ch * 8;
 #pragma unroll
   for (int it = 0; it < 4; ++it) {
-    const int row = it * 8 + (lane >> 3), ch = lane & 7;
-    if (row0 + row >= run.len) continue;   // padding of a partial tile
-    const int tok = token_of(run.p0 + row0 + row, s, a.N);
-    *reinterpret_cast<uint4*>(static_cast<__bf16*>(out) + row_off(so, b, tok, h) + ch * 8) =
-        *reinterpret_cast<const uint4*>(region + tile_off64(row, ch));
+    const int row = row0 + it * 8 + sub;
+    if (row < run.len)   // not padding of a partial tile
+      *reinterpret_cast<uint4*>(head + (long long)token_of(run.p0 + row, s, a.N) * so.t) = val[it];
   }
 }
 

@@ -214,15 +214,7 @@ __device__ __forceinline__ void dq_workgroup(const KArgs& a, int T, const Deal& 
   char* region = smem + w * (32 * kRowBytes);
   acc_to_lds(region, dq_acc, a.scale, l32, g32);
   wave_lds_order();
-  __bf16* dqp = static_cast<__bf16*>(a.dq);
-#pragma unroll
-  for (int it = 0; it < 8; ++it) {
-    const int row = it * 4 + (lane >> 4), ch = lane & 15;
-    if (qw0 + row >= run.len) continue;   // padding row of a partial tile
-    const int tok = token_of(run.p0 + qw0 + row, s, a.N);
-    *reinterpret_cast<uint4*>(dqp + row_off(a.sdq, b, tok, h) + ch * 8) =
-        *reinterpret_cast<const uint4*>(region + tile_off(row, ch));
-  }
+  store_wave_rows<RAGGED>(a, a.dq, a.sdq, region, run, qw0, s, b, h, lane);
 }
 
 template <bool RAGGED>

@@ -134,9 +134,9 @@ __device__ __forceinline__ void fwd_tile(FwdState& st, const bf16x8 (&qf)[8], co
 
 // Normalises a wave's 32 x 128 output block, transposes it through the wave's private
 // 8 KB LDS region and stores it (and lse) at the un-rolled token rows.
+template <bool RAGGED>
 __device__ __forceinline__ void fwd_epilogue(const KArgs& a, FwdState& st, char* Os, int b, int h, const Run& run, int s,
                                              int qw0, float c2, int lane, int l32, int g32) {
-  __bf16* op = static_cast<__bf16*>(a.o);
   const float l_tot = sum_halves(st.l_run);
   const float inv = 1.f / l_tot;
 #pragma unroll
@@ -148,16 +148,8 @@ __device__ __forceinline__ void fwd_epilogue(const KArgs& a, FwdState& st, char*
       *reinterpret_cast<bf16x4*>(Os + tile_off(l32, 4 * db + vv) + 8 * g32) = pk;
     }
   wave_lds_order();
-#pragma unroll
-  for (int it = 0; it < 8; ++it) {
-    const int row = it * 4 + (lane >> 4), ch = lane & 15;
-    const uint4 val = *reinterpret_cast<const uint4*>(Os + tile_off(row, ch));
-    if (qw0 + row < run.len) {   // rows past the end of the run are padding of a partial tile
-      const int tok = token_of(run.p0 + qw0 + row, s, a.N);
-      *reinterpret_cast<uint4*>(op + row_off(a.so, b, tok, h) + ch * 8) = val;
-    }
-  }
-  if (g32 == 0 && qw0 + l32 < run.len) {
+  store_wave_rows<RAGGED>(a, a.o, a.so, Os, run, qw0, s, b, h, lane);
+  if (g32 == 0 && (!RAGGED || qw0 + l32 < run.len)) {
     const int tok = token_of(run.p0 + qw0 + l32, s, a.N);
     a.lse[((size_t)b * a.H + h) * a.N + tok] = (st.m_run * c2 + __builtin_amdgcn_logf(l_tot)) * kLn2;
   }
@@ -279,7 +271,7 @@ fwd_bf16_kernel(KArgs a, int T, Deal deal) {
   __syncthreads();
 
   // ---- epilogue: normalise, transpose through LDS, store at un-rolled token rows
-  fwd_epilogue(a, st, smem + w * (32 * kRowBytes), b, h, run, s, qw0, c2, lane, l32, g32);
+  fwd_epilogue<RAGGED>(a, st, smem + w * (32 * kRowBytes), b, h, run, s, qw0, c2, lane, l32, g32);
 }
 
 // ---- the matrix block of the eight-wave kernel as 8 steps of 4 MFMAs, each fed by 4
@@ -497,7 +489,7 @@ fwd_bf16_pp_kernel(KArgs a, int T, Deal deal) {
     const int t = st_cur; st_cur = st_nxt; st_nxt = st_free; st_free = t;
   }
   __syncthreads();
-  fwd_epilogue(a, st, smem + w * (32 * kRowBytes), b, h, run, s, qw0, c2, lane, l32, g32);
+  fwd_epilogue<RAGGED>(a, st, smem + w * (32 * kRowBytes), b, h, run, s, qw0, c2, lane, l32, g32);
 }
 
 }  // namespace
