@@ -226,21 +226,23 @@ fwd_bf16_kernel(KArgs a, int T, Deal deal) {
   const uint64_t v_head = uni64(reinterpret_cast<uint64_t>(vp) + row_off(a.sv, b, 0, c) * 2);
   auto issue_tile = [&](int jt, int stage) {
     const uint32_t ks = smem_base + stage * 2 * kTileBytes + 4 * w * kRowBytes;
-    if constexpr (!RAGGED) {
-      const uint32_t tok0 = (uint32_t)token_of(run.p0 + jt * BN, s, a.N);   // an aligned tile never straddles the wrap
-      const uint64_t kb = k_head + tok0 * k_row_bytes, vb = v_head + tok0 * v_row_bytes;
+    const int row0 = jt * BN;
+    const uint32_t tok0 = (uint32_t)token_of(run.p0 + row0, s, a.N);
+    if (RAGGED && (row0 + BN > run.len || (int)tok0 + BN > a.N)) {
+      // not 64 consecutive tokens: row by row, rows past the end of the run repeat its last row
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
-        dma16s(kb + p * 16 * k_row_bytes, k_lane, ks + 16 * p * kRowBytes);
-        dma16s(vb + p * 16 * v_row_bytes, v_lane, ks + 16 * p * kRowBytes + kTileBytes);
-      }
-    } else {   // every row finds its own token; padding rows repeat the last row of the group
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const int tok = run_token(a, run, jt * BN + 16 * p + st_row, s);
+        const int tok = run_token(a, run, row0 + 16 * p + st_row, s);
         dma16(kp + row_off(a.sk, b, tok, c) * 2 + st_chunk, ks + 16 * p * kRowBytes);
         dma16(vp + row_off(a.sv, b, tok, c) * 2 + st_chunk, ks + 16 * p * kRowBytes + kTileBytes);
       }
+      return;
+    }
+    const uint64_t kb = k_head + tok0 * k_row_bytes, vb = v_head + tok0 * v_row_bytes;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      dma16s(kb + p * 16 * k_row_bytes, k_lane, ks + 16 * p * kRowBytes);
+      dma16s(vb + p * 16 * v_row_bytes, v_lane, ks + 16 * p * kRowBytes + kTileBytes);
     }
   };
 
