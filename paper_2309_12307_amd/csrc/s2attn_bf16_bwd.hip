@@ -465,7 +465,7 @@ int launch_bwd_dq_bf16(const KArgs& a, hipStream_t st) {
 // one for every query head of the part (H = 8, N = 4096: 77.2 us with dK/dV first).
 int launch_bwd_both_bf16(const KArgs& a, hipStream_t st) {
   if (a.ds_spill) return 1;
-  if (a.D == 64) return 1;
+  if (a.D == 64) return launch_bwd_both_d64(a, st);
   const bool partial = a.ragged || a.G % 256 != 0 || (a.split < a.G && a.split % 256 != 0);
   const int T_kv = partial ? ragged_tiles(a, 128) : a.G / 128, T_q = partial ? ragged_tiles(a, 256) : a.G / 256;
   const Grid kv = grid_of(T_kv, a.B * a.Hkv * a.NG * a.parts, 1, 32);

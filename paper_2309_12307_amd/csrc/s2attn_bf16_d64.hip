@@ -378,15 +378,14 @@ __device__ __forceinline__ void dkdv64_masked(const char* Qs, const char* dOs, c
   ac_mma64(f, pf, df, dk, dv);
 }
 
-__global__ void __launch_bounds__(256, 2)
-bwd_dkdv_d64_kernel(KArgs a, int T, Deal deal) {
-  __shared__ __attribute__((aligned(1024))) char smem[4 * kTile];   // [stage][Q,dO]
-  __shared__ __attribute__((aligned(1024))) RowTerms rows_s[2];
-  const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
+// smem: [stage][Q,dO]
+__device__ __forceinline__ void dkdv64_workgroup(const KArgs& a, int T, const Deal& deal, int block, int tid, char* smem,
+                                                 RowTerms (&rows_s)[2]) {
+  const int lane = tid & 63, w = uni(tid >> 6);
   const int g32 = lane >> 5, l32 = lane & 31;
 
   int seq, jt;
-  if (!decode_block(block_id(), T, deal, seq, jt)) return;
+  if (!decode_block(block, T, deal, seq, jt)) return;
   const KvPos at = kv_of_seq(a, seq);
   const int c = at.c, b = at.b;
   int h_lo, nheads, s;
@@ -520,14 +519,13 @@ __device__ __forceinline__ void dq64_block(const char* Ks, const char* Vs, const
   }
 }
 
-__global__ void __launch_bounds__(256, 3)
-bwd_dq_d64_kernel(KArgs a, int T, Deal deal) {
-  __shared__ __attribute__((aligned(1024))) char smem[4 * kTile];   // [stage][K,V]
-  const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
+// smem: [stage][K,V]
+__device__ __forceinline__ void dq64_workgroup(const KArgs& a, int T, const Deal& deal, int block, int tid, char* smem) {
+  const int lane = tid & 63, w = uni(tid >> 6);
   const int g32 = lane >> 5, l32 = lane & 31;
 
   int seq, rank;
-  if (!decode_block(block_id(), T, deal, seq, rank)) return;
+  if (!decode_block(block, T, deal, seq, rank)) return;
   const HeadPos at = head_of_seq(a, seq);
   const int c = at.c, b = at.b, h = at.h;
   int qt = T - 1 - rank;
@@ -588,6 +586,31 @@ bwd_dq_d64_kernel(KArgs a, int T, Deal deal) {
   store_rows(a, a.dq, a.sdq, region, run, qw0, s, b, h, lane);
 }
 
+__global__ void __launch_bounds__(256, 2)
+bwd_dkdv_d64_kernel(KArgs a, int T, Deal deal) {
+  __shared__ __attribute__((aligned(1024))) char smem[4 * kTile];
+  __shared__ __attribute__((aligned(1024))) RowTerms rows_s[2];
+  dkdv64_workgroup(a, T, deal, block_id(), thread_id(), smem, rows_s);
+}
+
+__global__ void __launch_bounds__(256, 3)
+bwd_dq_d64_kernel(KArgs a, int T, Deal deal) {
+  __shared__ __attribute__((aligned(1024))) char smem[4 * kTile];
+  dq64_workgroup(a, T, deal, block_id(), thread_id(), smem);
+}
+
+// Both in one launch, dK/dV first: neither needs the other, and where they do not fill the chip their
+// chains of tiles run side by side.
+__global__ void __launch_bounds__(256, 2)
+bwd_both_d64_kernel(KArgs a, int n_kv, int T, Deal deal_kv, Deal deal_q) {
+  __shared__ __attribute__((aligned(1024))) char smem[4 * kTile];
+  __shared__ __attribute__((aligned(1024))) RowTerms rows_s[2];
+  if (block_id() < n_kv)
+    dkdv64_workgroup(a, T, deal_kv, block_id(), thread_id(), smem, rows_s);
+  else
+    dq64_workgroup(a, T, deal_q, block_id() - n_kv, thread_id(), smem);
+}
+
 }  // namespace
 
 int launch_fwd_d64(const KArgs& a, hipStream_t st) {
@@ -601,6 +624,22 @@ int launch_bwd_dkdv_d64(const KArgs& a, hipStream_t st) {
   const int T = ragged_tiles(a, kOwn);
   const Grid g = grid_of(T, a.B * a.Hkv * a.NG * a.parts, 1, 64);
   hipLaunchKernelGGL(bwd_dkdv_d64_kernel, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// dK/dV and dQ in one launch, dK/dV first; 1 and no launch where one by one is better.  Up to twenty
+// workgroups per CU, ten rounds of two: dQ fills the tail of dK/dV, whose workgroups are few and
+// uneven with several query heads to a kv head.  Forward + backward, one by one and in one launch:
+// N = 1024, H = 4, Hkv = 2 34.7 and 26.4 us; N = 8192, H = 32, Hkv = 32 / 1 377 / 413 and 364 / 357;
+// N = 8192, H = 64, Hkv = 8 (4608 workgroups) 801 and 698.  Beyond, dQ's third workgroup on a CU is
+// worth more: N = 16384, H = 32 (8192 workgroups) 1398 and 1406.  dQ first: 242 us where dK/dV first
+// takes 205 and one by one 229 (B = 2, N = 4096, H = 32, Hkv = 8), at best even elsewhere.
+int launch_bwd_both_d64(const KArgs& a, hipStream_t st) {
+  const int T = ragged_tiles(a, kOwn);
+  const Grid kv = grid_of(T, a.B * a.Hkv * a.NG * a.parts, 1, 64), q = grid_of(T, a.B * a.H * a.NG, a.r, 64);
+  if (kv.blocks + q.blocks > 20 * 256) return 1;
+  hipLaunchKernelGGL(bwd_both_d64_kernel, dim3(kv.blocks + q.blocks), dim3(256), 0, st, a,
+                     kv.blocks, T, kv.deal, q.deal);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -16,6 +16,7 @@ int launch_bwd_both_bf16(const KArgs& a, hipStream_t st);
 // head dimension 64, any shape (the three entry points above hand such calls on)
 int launch_fwd_d64(const KArgs& a, hipStream_t st);
 int launch_bwd_dkdv_d64(const KArgs& a, hipStream_t st);
+int launch_bwd_both_d64(const KArgs& a, hipStream_t st);
 int launch_bwd_dq_d64(const KArgs& a, hipStream_t st);
 // dQ from the dS blobs the dK/dV kernel stored (same shapes)
 int launch_bwd_dq_spill_bf16(const KArgs& a, hipStream_t st);

@@ -10,9 +10,9 @@ from paper_2309_12307_amd import inputs
 pytestmark = pytest.mark.gpu
 
 
-def check(B, N, H, Hkv, G, **kw):
+def check(B, N, H, Hkv, G, D=128, **kw):
     from gpu_util import check_bf16_tensor, max_abs, run_hip
-    inp = inputs.make_inputs(B, N, H, Hkv, 128, seed=800 + N + H + Hkv, dtype="bf16")
+    inp = inputs.make_inputs(B, N, H, Hkv, D, seed=800 + N + H + Hkv, dtype="bf16")
     out = run_hip(inp, G, "bf16", **kw)
     o, lse, dq, dk, dv = orc.s2attn_fwd_bwd(inp["q"], inp["k"], inp["v"], inp["do"], G, variant2=bool(kw))
     assert max_abs(out["lse"], lse) <= 2e-3
@@ -34,3 +34,9 @@ def test_group_sizes_around_the_dq_tile(G, Hkv, split):
 @pytest.mark.parametrize("groups", [16, 17])
 def test_largest_grid_of_one_launch_and_the_next(groups):
     check(4, 256 * groups, 8, 8, 256)
+
+
+# D = 64: one workgroup of each kernel per group and head, 5120 in one launch
+@pytest.mark.parametrize("groups", [40, 41])
+def test_largest_grid_of_one_launch_and_the_next_d64(groups):
+    check(4, 128 * groups, 16, 16, 128, D=64)
