@@ -140,7 +140,7 @@ typedef struct s2attn_params {
 S2ATTN_API int s2attn_check_args(const s2attn_params* p, int backward);
 
 /* Bytes of device workspace the backward wants, for the published defaults (shift G/2 on the
- * second half of the heads): the fp32 row term delta[b,h,t] = sum_d dout*o and a base-2 copy of
+ * second half of the heads): the fp32 row term -delta[b,h,t] = -sum_d dout*o and a base-2 copy of
  * lse, plus fp32 partial dk/dv when the query heads of a kv head are worked on in parts: always
  * when one serves both shifted and unshifted query heads (odd Hkv), and where few kv heads would
  * leave the chip idle otherwise.  It runs with less, down to the row terms and, for a kv head of
