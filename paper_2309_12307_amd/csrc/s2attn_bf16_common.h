@@ -193,7 +193,7 @@ __device__ __forceinline__ f32x16 zero16() {
 // Between a wave's writes to and its lanes' reads from LDS that no other wave touches: LDS serves
 // the instructions of a wave in order, so only the compiler has to keep them so.
 __device__ __forceinline__ void wave_lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
 
