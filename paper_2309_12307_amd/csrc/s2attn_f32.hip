@@ -24,6 +24,8 @@
 // for delta took 2890 us (10 TFLOP/s of the 14 D flops per pair), these 388 us (78; executed 100
 // of the 153 TFLOP/s that a library fp32 product of 8192^3 reaches).  N = 256, H = 4, D = 64,
 // G = 64: 119 -> 19 us, of which the two kernels take 7 and 13.
+#include <cfloat>
+
 #include "s2attn_bf16_common.h"
 #include "s2attn_device.h"
 #include "s2attn_launch.h"
@@ -188,7 +190,10 @@ __global__ void __launch_bounds__(256, 2) fwd_f32_kernel(KArgs a, int T, Deal de
   for (int j = 0; j < D / 64; ++j)
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[j][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;    // scaled (base 2) row maximum; this lane's part of the row sum
+  // scaled (base 2) row maximum, and this lane's part of the row sum.  The maximum starts at the
+  // lowest finite number: a row whose scores so far are all -inf then has weights of
+  // exp2(-inf) = 0 and goes on with its later keys (from -inf they would be exp2(-inf + inf) = NaN)
+  float m_run = -FLT_MAX, l_run = 0.f;
 
   const int n_tiles = uni((min(i0 + kWgRows, run.len) - 1) / kTile + 1);
   for (int n = 0; n < n_tiles; ++n) {
@@ -213,7 +218,6 @@ __global__ void __launch_bounds__(256, 2) fwd_f32_kernel(KArgs a, int T, Deal de
         mx = fmaxf(mx, x);
       }
     mx = max_cols(mx);
-    // the first tile holds key 0, which every row sees, so the maximum is finite from there on
     if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {
       const float m_new = fmaxf(m_run, mx);
       const float alpha = exp2f(m_run - m_new);

@@ -24,3 +24,36 @@ def test_group_sizes_around_the_tiles(G, D):
         ref = orc.s2attn_fwd_bwd(inp["q"], inp["k"], inp["v"], inp["do"], G, **okw)
         for name, r in zip(("o", "lse", "dq", "dk", "dv"), ref):
             assert np.all(np.isfinite(out[name])) and max_abs(out[name], r) <= 1e-4, (name, kw)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("low", [-np.inf, -3e38])
+@pytest.mark.parametrize("n_low", [8, 32, 40])
+def test_first_scores_of_a_row_minus_infinity(D, low, n_low):
+    """The first keys of every group score -inf (or the lowest finite numbers): rows that see any
+    other key are softmax over the others, whether the low keys are part of their first tile of 32
+    keys, all of it, or reach into the second."""
+    import torch
+    from gpu_util import to_dev, to_np
+    from paper_2309_12307_amd import binding
+    N, H, G = 256, 2, 128
+    rng = np.random.default_rng(77)
+    q, k, v = (rng.standard_normal((1, N, H, D)).astype(np.float32) for _ in range(3))
+    q[..., 0] = np.abs(q[..., 0]) + 0.5
+    dead = np.arange(N) % G < n_low
+    k[:, dead, :, 0] = low
+    qt, kt, vt = (to_dev(x) for x in (q, k, v))
+    o = torch.full_like(qt, float("nan"))
+    lse = torch.full((1, H, N), float("nan"), dtype=torch.float32, device="cuda")
+    binding.s2attn_fwd_ex(binding.make_params(qt, kt, vt, o, lse, G, shift_rule=binding.SHIFT_NONE))
+    o, lse = to_np(o), to_np(lse)
+    for g in range(N // G):
+        rows = slice(g * G + n_low, (g + 1) * G)     # these rows and these keys only
+        for h in range(H):
+            s = q[0, rows, h].astype(np.float64) @ k[0, rows, h].astype(np.float64).T / np.sqrt(D)
+            s = np.where(np.tril(np.ones_like(s)) > 0, s, -np.inf)
+            m = s.max(axis=1, keepdims=True)
+            e = np.exp(s - m)
+            ref = e / e.sum(axis=1, keepdims=True) @ v[0, rows, h].astype(np.float64)
+            assert np.abs(o[0, rows, h] - ref).max() <= 1e-4
+            assert np.abs(lse[0, h, rows] - (m[:, 0] + np.log(e.sum(axis=1)))).max() <= 1e-4
