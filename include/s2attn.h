@@ -105,7 +105,7 @@ typedef struct s2attn_params {
   void* o;            /* written by forward, read by backward */
   float* lse;         /* written by forward, read by backward */
   const void* dout;   /* backward only */
-  void* dq;           /* backward only, overwritten */
+  void* dq;           /* backward only, overwritten; may be q's, o's or dout's memory, row for row */
   void* dk;           /* backward only, overwritten */
   void* dv;           /* backward only, overwritten */
   void* workspace;    /* backward only: s2attn_bwd_workspace_bytes(...) bytes, 256-byte aligned */

@@ -157,6 +157,26 @@ bool rows_disjoint(const long long (&st)[3], int B, int N, int heads, int D) {
   return true;
 }
 
+// Bytes that a tensor of `heads` heads spans from its pointer on.
+size_t span_bytes(const long long (&st)[3], int B, int N, int heads, int D, size_t elem) {
+  if (st[0] == 0 && st[1] == 0 && st[2] == 0) return (size_t)B * N * heads * D * elem;
+  return (size_t)(st[0] * (B - 1) + st[1] * (N - 1) + st[2] * (heads - 1) + D) * elem;
+}
+
+// dq may lie in the memory of q, o or dout: a dQ workgroup has read its rows before it stores them.
+// The dK/dV workgroups read all rows, so dQ then has to follow them in a launch of its own.
+bool dq_reuses_input(const s2attn_params* p) {
+  const size_t elem = p->dtype == S2ATTN_F32 ? 4 : 2;
+  const uintptr_t dq = reinterpret_cast<uintptr_t>(p->dq);
+  const size_t n_dq = span_bytes(p->dq_strides, p->B, p->N, p->H, p->D, elem);
+  auto meets = [&](const void* x, size_t n) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(x);
+    return at < dq + n_dq && dq < at + n;
+  };
+  const size_t n_o = (size_t)p->B * p->N * p->H * p->D * elem;
+  return meets(p->q, span_bytes(p->q_strides, p->B, p->N, p->H, p->D, elem)) || meets(p->o, n_o) || meets(p->dout, n_o);
+}
+
 int check_common(const s2attn_params* p, int backward) {
   if (!p) return S2ATTN_ERR_NULL;
   if (p->dtype != S2ATTN_BF16 && p->dtype != S2ATTN_F32) return S2ATTN_ERR_DTYPE;
@@ -341,9 +361,10 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
   int ds_heads = 0;
   if (p->bwd_algo == S2ATTN_BWD_STORED_DS) ds_heads = ds_heads_per_pass(p, p->workspace_bytes - basic);
   mark(0);
+  const bool dq_last = dq_reuses_input(p);
   if (p->dtype == S2ATTN_F32) {   // one launch, delta included
     mark(1);
-    if (s2::launch_bwd_f32(a, st) != 0) return S2ATTN_ERR_LAUNCH;
+    if (s2::launch_bwd_f32(a, dq_last, st) != 0) return S2ATTN_ERR_LAUNCH;
     mark(2);
     if (a.parts > 1 && s2::launch_combine_partials(a, p->dtype, st) != 0) return S2ATTN_ERR_LAUNCH;
     mark(3);
@@ -365,7 +386,7 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
     mark(3);
     return S2ATTN_OK;
   }
-  const int both = s2::launch_bwd_both_bf16(a, st);
+  const int both = dq_last ? 1 : s2::launch_bwd_both_bf16(a, st);
   if (both < 0) return S2ATTN_ERR_LAUNCH;
   if (both > 0 && s2::launch_bwd_dkdv_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
   mark(2);

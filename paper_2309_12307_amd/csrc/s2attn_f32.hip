@@ -478,11 +478,12 @@ int launch_fwd_t(const KArgs& a, hipStream_t st) {
 }
 
 template <int D>
-int launch_bwd_t(const KArgs& a, hipStream_t st) {
+int launch_bwd_t(const KArgs& a, bool dq_last, hipStream_t st) {
   const int T = ragged_tiles(a, kWgRows);
   const Grid kv = grid_of(T, a.B * a.Hkv * a.NG * a.parts, 1, 64), q = grid_of(T, a.B * a.H * a.NG, a.r, 64);
-  hipLaunchKernelGGL(bwd_f32_kernel<D>, dim3(kv.blocks + q.blocks), dim3(256), 0, st, a, kv.blocks, T, kv.deal,
-                     q.deal);
+  const int n_first = dq_last ? kv.blocks : kv.blocks + q.blocks;
+  hipLaunchKernelGGL(bwd_f32_kernel<D>, dim3(n_first), dim3(256), 0, st, a, kv.blocks, T, kv.deal, q.deal);
+  if (dq_last) hipLaunchKernelGGL(bwd_f32_kernel<D>, dim3(q.blocks), dim3(256), 0, st, a, 0, T, kv.deal, q.deal);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -492,8 +493,8 @@ int launch_fwd_f32(const KArgs& a, hipStream_t st) {
   return a.D == 64 ? launch_fwd_t<64>(a, st) : launch_fwd_t<128>(a, st);
 }
 
-int launch_bwd_f32(const KArgs& a, hipStream_t st) {
-  return a.D == 64 ? launch_bwd_t<64>(a, st) : launch_bwd_t<128>(a, st);
+int launch_bwd_f32(const KArgs& a, bool dq_last, hipStream_t st) {
+  return a.D == 64 ? launch_bwd_t<64>(a, dq_last, st) : launch_bwd_t<128>(a, dq_last, st);
 }
 
 }  // namespace s2
