@@ -196,8 +196,10 @@ int check_common(const s2attn_params* p, int backward) {
       return S2ATTN_ERR_HEADS;
   }
   if (p->D != 64 && p->D != 128) return S2ATTN_ERR_HEADDIM;
-  // grid z carries batch * heads (* 2 classes); element offsets are 64-bit
+  // heads and groups are counted in 16 bits; block numbers, up to twice the tiles of 64 rows (dK/dV and
+  // dQ in one launch) padded to whole rounds of the XCDs, are non-negative ints; element offsets are 64-bit
   if ((long long)p->B * p->H * 2 > 65535 || (long long)p->N / p->G > 65535) return S2ATTN_ERR_TOO_LARGE;
+  if (2.0 * p->B * p->H * (p->N / p->G) * (p->G / 64 + 2) > 2.0e9) return S2ATTN_ERR_TOO_LARGE;
   if ((double)p->B * p->N * p->H * p->D > 9.0e18 / 4) return S2ATTN_ERR_TOO_LARGE;
 
   const int align = p->dtype == S2ATTN_F32 ? 4 : 8;

@@ -141,7 +141,7 @@ fwd_d64_kernel(KArgs a, int T, Deal deal) {
   const int g32 = lane >> 5, l32 = lane & 31;
 
   int seq, rank;
-  if (!decode_block(block_id(), T, deal, seq, rank)) return;
+  if (!decode_block(a.first_block + block_id(), T, deal, seq, rank)) return;
   const HeadPos at = head_of_seq(a, seq);
   const int c = at.c, b = at.b, h = at.h;
   int qt = T - 1 - rank;
@@ -590,13 +590,13 @@ __global__ void __launch_bounds__(256, 2)
 bwd_dkdv_d64_kernel(KArgs a, int T, Deal deal) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * kTile];
   __shared__ __attribute__((aligned(1024))) RowTerms rows_s[2];
-  dkdv64_workgroup(a, T, deal, block_id(), thread_id(), smem, rows_s);
+  dkdv64_workgroup(a, T, deal, a.first_block + block_id(), thread_id(), smem, rows_s);
 }
 
 __global__ void __launch_bounds__(256, 3)
 bwd_dq_d64_kernel(KArgs a, int T, Deal deal) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * kTile];
-  dq64_workgroup(a, T, deal, block_id(), thread_id(), smem);
+  dq64_workgroup(a, T, deal, a.first_block + block_id(), thread_id(), smem);
 }
 
 // Both in one launch, dK/dV first: neither needs the other, and where they do not fill the chip their
@@ -616,15 +616,13 @@ bwd_both_d64_kernel(KArgs a, int n_kv, int T, Deal deal_kv, Deal deal_q) {
 int launch_fwd_d64(const KArgs& a, hipStream_t st) {
   const int T = ragged_tiles(a, kOwn);
   const Grid g = grid_of(T, a.B * a.H * a.NG, a.r, 128);   // 32 CUs per XCD, four workgroups each
-  hipLaunchKernelGGL(fwd_d64_kernel, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
+  return launch_blocks(fwd_d64_kernel, g.blocks, 256, st, a, T, g.deal);
 }
 
 int launch_bwd_dkdv_d64(const KArgs& a, hipStream_t st) {
   const int T = ragged_tiles(a, kOwn);
   const Grid g = grid_of(T, a.B * a.Hkv * a.NG * a.parts, 1, 64);
-  hipLaunchKernelGGL(bwd_dkdv_d64_kernel, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
+  return launch_blocks(bwd_dkdv_d64_kernel, g.blocks, 256, st, a, T, g.deal);
 }
 
 // dK/dV and dQ in one launch, dK/dV first; 1 and no launch where one by one is better.  Up to twenty
@@ -646,8 +644,7 @@ int launch_bwd_both_d64(const KArgs& a, hipStream_t st) {
 int launch_bwd_dq_d64(const KArgs& a, hipStream_t st) {
   const int T = ragged_tiles(a, kOwn);
   const Grid g = grid_of(T, a.B * a.H * a.NG, a.r, 96);
-  hipLaunchKernelGGL(bwd_dq_d64_kernel, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
+  return launch_blocks(bwd_dq_d64_kernel, g.blocks, 256, st, a, T, g.deal);
 }
 
 }  // namespace s2

@@ -223,7 +223,7 @@ template <bool RAGGED>
 __global__ void __launch_bounds__(256, 2)
 bwd_dq_bf16_kernel(KArgs a, int T, Deal deal) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes];
-  dq_workgroup<RAGGED, 4>(a, T, deal, block_id(), thread_id(), smem);
+  dq_workgroup<RAGGED, 4>(a, T, deal, a.first_block + block_id(), thread_id(), smem);
 }
 
 }  // namespace

@@ -175,7 +175,7 @@ fwd_bf16_kernel(KArgs a, int T, Deal deal) {
   // four of the eight XCDs only (N = 8192, H = 32, G = 2048: forward 278 us,
   // 149 dealt out per query head; dQ 383 and 198).
   int seq, rank;
-  if (!decode_block(block_id(), T, deal, seq, rank)) return;
+  if (!decode_block(a.first_block + block_id(), T, deal, seq, rank)) return;
   const HeadPos at = head_of_seq(a, seq);
   const int gidx = at.g, c = at.c, b = at.b, h = at.h;
   int qt = T - 1 - rank;
@@ -514,11 +514,8 @@ int launch_fwd_bf16(const KArgs& a, hipStream_t st) {
   }
   const int T = a.ragged ? ragged_tiles(a, 128) : a.G / 128;
   const Grid g = grid_of(T, n_seq, a.r, 64);     // 32 CUs per XCD, two workgroups each
-  if (a.ragged)
-    hipLaunchKernelGGL(fwd_bf16_kernel<true>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
-  else
-    hipLaunchKernelGGL(fwd_bf16_kernel<false>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
+  if (a.ragged) return launch_blocks(fwd_bf16_kernel<true>, g.blocks, 256, st, a, T, g.deal);
+  return launch_blocks(fwd_bf16_kernel<false>, g.blocks, 256, st, a, T, g.deal);
 }
 
 }  // namespace s2

@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(256, 2) fwd_f32_kernel(KArgs a, int T, Deal de
   const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
   const int c16 = lane & 15, q4 = lane >> 4;
   int seq, rank;
-  if (!decode_block(block_id(), T, deal, seq, rank)) return;
+  if (!decode_block(a.first_block + block_id(), T, deal, seq, rank)) return;
   const HeadPos at = head_of_seq(a, seq);
   const int s = uni(shift_of_head(a, at.h));
   Run run;
@@ -463,18 +463,18 @@ __global__ void __launch_bounds__(256, 2)
 bwd_f32_kernel(KArgs a, int n_kv, int T, Deal deal_kv, Deal deal_q) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * Lanes<D>::kTileBytes];   // [stage][Q, dO] or [stage][K, V]
   __shared__ __attribute__((aligned(16))) float rows_s[2 * 2 * kTile];             // [stage][lse * log2(e), delta]
-  if (block_id() < n_kv)
-    bwd_dkdv_block<D>(a, smem, rows_s, block_id(), T, deal_kv);
+  const int block = a.first_block + block_id();
+  if (block < n_kv)
+    bwd_dkdv_block<D>(a, smem, rows_s, block, T, deal_kv);
   else
-    bwd_dq_block<D>(a, smem, block_id() - n_kv, T, deal_q);
+    bwd_dq_block<D>(a, smem, block - n_kv, T, deal_q);
 }
 
 template <int D>
 int launch_fwd_t(const KArgs& a, hipStream_t st) {
   const int T = ragged_tiles(a, kWgRows);
   const Grid g = grid_of(T, a.B * a.H * a.NG, a.r, 64);
-  hipLaunchKernelGGL(fwd_f32_kernel<D>, dim3(g.blocks), dim3(256), 0, st, a, T, g.deal);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
+  return launch_blocks(fwd_f32_kernel<D>, g.blocks, 256, st, a, T, g.deal);
 }
 
 template <int D>
@@ -482,9 +482,9 @@ int launch_bwd_t(const KArgs& a, bool dq_last, hipStream_t st) {
   const int T = ragged_tiles(a, kWgRows);
   const Grid kv = grid_of(T, a.B * a.Hkv * a.NG * a.parts, 1, 64), q = grid_of(T, a.B * a.H * a.NG, a.r, 64);
   const int n_first = dq_last ? kv.blocks : kv.blocks + q.blocks;
-  hipLaunchKernelGGL(bwd_f32_kernel<D>, dim3(n_first), dim3(256), 0, st, a, kv.blocks, T, kv.deal, q.deal);
-  if (dq_last) hipLaunchKernelGGL(bwd_f32_kernel<D>, dim3(q.blocks), dim3(256), 0, st, a, 0, T, kv.deal, q.deal);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
+  const int rc = launch_blocks(bwd_f32_kernel<D>, n_first, 256, st, a, kv.blocks, T, kv.deal, q.deal);
+  if (rc != 0 || !dq_last) return rc;
+  return launch_blocks(bwd_f32_kernel<D>, q.blocks, 256, st, a, 0, T, kv.deal, q.deal);
 }
 
 }  // namespace

@@ -219,3 +219,13 @@ def test_static_scratch_backward_refuses_large_problems_on_the_host():
     assert "static" in binding.strerror(-14)
     p = params(B=1, N=16384, H=4, Hkv=1, D=128, G=1024)        # MQA: 32 MiB of partial sums
     assert binding.lib().s2attn_bwd_ex_static(ctypes.byref(p), None) == -14
+
+
+def test_block_numbers_stay_ints():
+    """Tiny groups of very many rows: refused where the number of blocks could leave an int, and not before."""
+    def code(rows_per_two, **kw):      # groups of two, 65535 of them to a sequence
+        return binding.check_args(params(N=131070, G=2, B=1, H=rows_per_two, Hkv=rows_per_two, D=64, **kw), True)
+    assert code(258, dtype=binding.F32) == 0
+    assert code(7628, dtype=binding.F32) == 0
+    assert code(7632, dtype=binding.F32) == -12
+    assert code(7632) == -12
