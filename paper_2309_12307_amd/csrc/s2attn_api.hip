@@ -3,8 +3,9 @@
 // block, and kernel launches.  Nothing here allocates device memory.
 #include "s2attn.h"
 
-#include <atomic>
 #include <algorithm>
+#include <atomic>
+#include <climits>
 #include <cmath>
 #include <cstring>
 
@@ -58,21 +59,53 @@ size_t workspace_bytes_least(int B, int N, int H, int Hkv, int D, bool mixed) {
   return 2 * delta_bytes(B, N, H) + partial_bytes(B, N, Hkv, D, mixed ? 2 : 1);
 }
 
+// Estimated time (us) of dK/dV, dQ and the summing of the partials when the query heads of a kv head
+// are cut into `parts`: the longest chain of tiles of a dK/dV workgroup (the first keys of a group, all
+// rows of a part) against the work per CU, to which the end of a grid adds a share of a chain, and the
+// partials, written by dK/dV and read back.  The rates are those of the kernels, and all constants fit
+// backward times measured with 1, 2, 4 ... 32 parts at 780 shapes (2 to 511 workgroups uncut, G = 32 to
+// 8192, 2 to 32 query heads to a kv head).
+double bwd_estimate_us(const s2attn_params* p, int parts) {
+  struct Kind {
+    double cu_rate, share;       // flop per us and CU; what one workgroup of it reaches alone
+    double end_share, bytes_us;  // share of a chain that the end of a full grid costs; bytes of partials per us
+    int keys, q_rows, one_launch;
+  };
+  static const Kind f32{3.6e5, 0.6, 0.25, 2.5e6, 64, 64, INT_MAX}, d64{3.5e6, 0.75, 0.1, 4e6, 128, 128, s2::kOneLaunchBlocks64},
+      d128{4e6, 1.1, 0.25, 2.5e6, 128, 256, s2::kOneLaunchBlocks};
+  const Kind& k = p->dtype == S2ATTN_F32 ? f32 : p->D == 64 ? d64 : d128;
+  const double row_flop = 8.0 * p->D, groups = (double)p->B * (p->N / p->G);
+  const double chain = 5 + (double)(p->H / p->Hkv) / parts * p->G * k.keys * row_flop / (k.cu_rate * k.share);
+  const double dkdv = groups * p->H * p->G * (p->G + k.keys) / 2.0 * row_flop / (256 * k.cu_rate), dq = 0.75 * dkdv;
+  const double blocks = groups * ((double)p->Hkv * parts * ((p->G + k.keys - 1) / k.keys) + p->H * ((p->G + k.q_rows - 1) / k.q_rows));
+  const double partials = parts > 1 ? 4 + 2.0 * 2 * parts * p->B * p->N * p->Hkv * p->D * sizeof(float) / k.bytes_us : 0;
+  const double kernels = blocks <= k.one_launch ? std::max(chain, dkdv + dq + k.end_share * chain)
+                                                : std::max(chain, dkdv + 0.4 * chain) + dq;
+  return kernels + partials;
+}
+
 // Parts the dK/dV workgroups should cut the query heads of a kv head into.  Without cutting there
-// is one workgroup per 128 keys of a kv head, and with few kv heads most of the chip idles.  Two
-// workgroups per CU (512) are enough: they are dealt out heaviest first, so a CU gets one heavy and
-// one light one.  Each part costs a write and a read of 8 bytes per key element, so a part keeps
-// at least 1024 query rows (fp32, ten times the time per row: 256).  N = 8192, H = 32, Hkv = 1,
-// G = 2048: dK/dV 873 us with the two parts that the two head classes need, 273 us with 8.
+// is one workgroup per 128 keys of a kv head, and with few kv heads most of the chip idles.  At most
+// two workgroups per CU (512), dealt out heaviest first so that a CU gets one heavy and one light
+// one, and at least 1024 query rows to a part (fp32, ten times the time per row: 256); fewer parts, or
+// none, where the estimate says that the partials cost more than the shorter chains give.
+// N = 8192, H = 32, Hkv = 1, G = 2048: dK/dV 873 us with the two parts that the two head classes need,
+// 273 us with 8.  H = 32, Hkv = 8, backward: N = 7680, G = 640 (480 workgroups uncut) 265 us with two
+// parts, 210 with one; N = 4096, G = 512 (256) 115 and 94; N = 6144, G = 2048 (384) 412 and 446.
 int parts_wanted(const s2attn_params* p, bool mixed) {
   const int r = p->H / p->Hkv, least = mixed ? 2 : 1;
   const long long groups = (long long)p->B * p->Hkv * (p->N / p->G) * ((p->G + 127) / 128);
   const long long rows = (long long)r * p->G / (p->dtype == S2ATTN_F32 ? 256 : 1024);
   const long long most = std::min<long long>(std::min<long long>((512 + groups - 1) / groups, rows), r);
-  int parts = 1;
-  for (int x = 2; x <= most; ++x)
-    if (r % x == 0) parts = x;
-  return std::max(parts, least);
+  int best = least, last = least;
+  double best_us = 0, last_us = 0;
+  for (int x = least; x <= most; ++x) {
+    if (r % x != 0) continue;
+    last = x;
+    last_us = bwd_estimate_us(p, x);
+    if (best_us == 0 || last_us < best_us) { best = x; best_us = last_us; }
+  }
+  return best_us <= 0.97 * last_us ? best : last;   // a smaller difference is none
 }
 
 // The largest number of parts, at most the one wanted, whose partial sums fit into `avail` bytes.

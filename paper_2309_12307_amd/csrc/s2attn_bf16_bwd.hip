@@ -472,7 +472,7 @@ int launch_bwd_both_bf16(const KArgs& a, hipStream_t st) {
   const int T_kv = partial ? ragged_tiles(a, 128) : a.G / 128, T_q = partial ? ragged_tiles(a, 256) : a.G / 256;
   const Grid kv = grid_of(T_kv, a.B * a.Hkv * a.NG * a.parts, 1, 32);
   const Grid q = grid_of(T_q, a.B * a.H * a.NG, a.r, 32);
-  if (kv.blocks + q.blocks > 6 * 256) return 1;
+  if (kv.blocks + q.blocks > kOneLaunchBlocks) return 1;
   const int kv_first = 2 * a.r >= 3 * a.parts;
   const int n_first = kv_first ? kv.blocks : q.blocks;
   if (partial)

@@ -635,7 +635,7 @@ int launch_bwd_dkdv_d64(const KArgs& a, hipStream_t st) {
 int launch_bwd_both_d64(const KArgs& a, hipStream_t st) {
   const int T = ragged_tiles(a, kOwn);
   const Grid kv = grid_of(T, a.B * a.Hkv * a.NG * a.parts, 1, 64), q = grid_of(T, a.B * a.H * a.NG, a.r, 64);
-  if (kv.blocks + q.blocks > 20 * 256) return 1;
+  if (kv.blocks + q.blocks > kOneLaunchBlocks64) return 1;
   hipLaunchKernelGGL(bwd_both_d64_kernel, dim3(kv.blocks + q.blocks), dim3(256), 0, st, a,
                      kv.blocks, T, kv.deal, q.deal);
   return hipGetLastError() == hipSuccess ? 0 : -1;

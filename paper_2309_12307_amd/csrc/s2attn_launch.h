@@ -12,6 +12,8 @@ int launch_bwd_f32(const KArgs& a, bool dq_last, hipStream_t st);
 int launch_fwd_bf16(const KArgs& a, hipStream_t st);
 int launch_bwd_dkdv_bf16(const KArgs& a, hipStream_t st);  // delta must be ready; a.ds_spill set: also stores the dS blobs
 int launch_bwd_dq_bf16(const KArgs& a, hipStream_t st);
+// most workgroups (D = 128, D = 64) that dK/dV and dQ share a launch with
+constexpr int kOneLaunchBlocks = 6 * 256, kOneLaunchBlocks64 = 20 * 256;
 // both in one launch for the shapes that gain by it; 1 and no launch for the others
 int launch_bwd_both_bf16(const KArgs& a, hipStream_t st);
 // head dimension 64, any shape (the three entry points above hand such calls on)

@@ -229,3 +229,24 @@ def test_block_numbers_stay_ints():
     assert code(7628, dtype=binding.F32) == 0
     assert code(7632, dtype=binding.F32) == -12
     assert code(7632) == -12
+
+
+@pytest.mark.parametrize("dtype,shape,parts", [
+    # dtype, (B, N, H, Hkv, D, G), pieces the query heads of a kv head are cut into
+    (binding.BF16, (1, 7680, 32, 8, 128, 640), 1),      # 480 workgroups uncut: partials cost more than they give
+    (binding.BF16, (1, 7680, 32, 8, 128, 1536), 1),
+    (binding.BF16, (1, 4096, 32, 8, 128, 512), 1),      # 256, of short chains
+    (binding.BF16, (1, 4096, 32, 8, 128, 4096), 2),     # 256, of long ones
+    (binding.BF16, (1, 20480, 8, 2, 128, 4096), 2),     # 320
+    (binding.BF16, (1, 8192, 32, 1, 128, 2048), 8),     # 64
+    (binding.BF16, (1, 5120, 32, 8, 64, 512), 1),
+    (binding.BF16, (1, 2048, 8, 1, 64, 1024), 8),
+    (binding.F32, (1, 6400, 8, 4, 128, 256), 1),
+    (binding.F32, (1, 512, 8, 1, 64, 256), 8),
+    (binding.BF16, (1, 1536, 6, 3, 128, 512), 2),       # a kv head of both classes: two parts at least
+])
+def test_heads_are_cut_where_the_shorter_chains_pay(dtype, shape, parts):
+    B, N, H, Hkv, D, G = shape
+    rows = 2 * ((B * H * N * 4 + 255) // 256 * 256)
+    partials = 2 * parts * B * N * Hkv * D * 4 if parts > 1 else 0
+    assert binding.bwd_workspace_bytes(B, N, H, Hkv, D, G, dtype) == rows + partials
