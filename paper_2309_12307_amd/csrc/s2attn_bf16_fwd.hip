@@ -503,13 +503,19 @@ int launch_fwd_bf16(const KArgs& a, hipStream_t st) {
   // faster (4-9 % at G = 512 ... 1024) with two independent four-wave workgroups per CU, whose
   // prologues and epilogues overlap
   const bool partial = a.ragged || a.G % 256 != 0;   // tiles of 256 rows that are not full
-  if (a.G >= 2048) {
-    const int T = partial ? ragged_tiles(a, 256) : a.G / 256;
-    const Grid g = grid_of(T, n_seq, a.r, 32);   // 32 CUs per XCD, one workgroup each
+  const int T8 = partial ? ragged_tiles(a, 256) : a.G / 256;
+  // Tiles that are not full go there only with more than three workgroups to two CUs: up to then four
+  // waves fill the chip better (G = 2050: 72 workgroups of eight waves 48.7 us, with four 42.0; 288 53.3 and
+  // 51.1; 432 78.4 and 77.1; G = 4000: 256 91.8 and 88.3, 512 131 and 143).  And where 128 rows would divide the group
+  // (G % 256 == 128), only from 4096 tokens on: the four-wave kernel then has no partial tile to test for
+  // (H = 32, eight groups: G = 2688 553 and 512 us, 3200 740 and 715; G = 4224 602 and 603, 6016 1152 and
+  // 1160, four groups of 10880 1774 and 1855).
+  if (a.G >= 2048 && (!partial || (n_seq * (long long)T8 > 384 && (a.ragged || a.G >= 4096)))) {
+    const Grid g = grid_of(T8, n_seq, a.r, 32);   // 32 CUs per XCD, one workgroup each
     if (partial)
-      hipLaunchKernelGGL(fwd_bf16_pp_kernel<true>, dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
+      hipLaunchKernelGGL(fwd_bf16_pp_kernel<true>, dim3(g.blocks), dim3(512), 0, st, a, T8, g.deal);
     else
-      hipLaunchKernelGGL(fwd_bf16_pp_kernel<false>, dim3(g.blocks), dim3(512), 0, st, a, T, g.deal);
+      hipLaunchKernelGGL(fwd_bf16_pp_kernel<false>, dim3(g.blocks), dim3(512), 0, st, a, T8, g.deal);
     return hipGetLastError() == hipSuccess ? 0 : -1;
   }
   const int T = a.ragged ? ragged_tiles(a, 128) : a.G / 128;

@@ -1,6 +1,6 @@
 """Head dimension 128, runs that no tile divides: dK/dV (64 query rows a tile, 128 keys a workgroup)
-at group sizes one step below, at and above each edge, the eight-wave forward (32 rows a wave, 256 a
-workgroup, groups of 2048 and more) likewise, with the wrap point of the roll at a tile's edge and
+at group sizes one step below, at and above each edge, and all kernels at the group sizes around 2048 where
+larger grids take the eight-wave forward, with the wrap point of the roll at a tile's edge and
 inside one, and the wrap-around group cut at its seam, against the oracle.  Bounds: those of the
 parity tests."""
 import pytest
@@ -31,5 +31,5 @@ def test_dkdv_group_sizes_around_the_tiles(G, shift):
 
 @pytest.mark.parametrize("G", [2046, 2048, 2050, 2078, 2082, 2110, 2112, 2114, 2176, 2302, 2306])
 @pytest.mark.parametrize("shift,split", [("half", False), ("odd", False), ("odd", True), (128, True)])
-def test_eight_wave_forward_group_sizes_around_the_tiles(G, shift, split):
+def test_group_sizes_from_2048_on(G, shift, split):
     check(G, 2, {"half": G // 2, "odd": G // 2 + 1}.get(shift, shift), split)
