@@ -20,27 +20,29 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {   // round to ne
   return u >> 16;
 }
 
-// A workgroup takes kRows consecutive tokens of one head, D / 8 lanes to a row, so that the row
-// terms (and lse) are whole lines; neighbouring workgroups take the heads of the same tokens, whose
-// rows are neighbours in memory.  Every lane has its eight loads out before it waits.  With one row
-// per 16 lanes and the heads of a token in one workgroup, forward + backward took 368 us at B = 2,
-// N = 4096, H = 32, Hkv = 8, G = 1024; 364 now.
-template <int D>
+// A workgroup takes kRows / HEADS consecutive tokens of HEADS neighbouring heads, D / 8 lanes to a row, so
+// that the row terms (and lse) are whole lines and the rows it reads pairs of neighbours in memory;
+// neighbouring workgroups take the other heads of the same tokens.  Every lane has its eight loads out
+// before it waits.  Two heads rather than one or four: D = 128, H = 32, N = 32768 112 us, 121 and 117
+// (one row per 16 lanes, sixteen heads to a workgroup: 111); N = 4096, B = 2 23.6, 24.9 and 23.7 (28.5).
+template <int D, int HEADS>
 __global__ void __launch_bounds__(256) delta_kernel(const void* o, const void* dout, const float* lse,
-                                                    float* neg_delta, float* lse2, int N, int H, Div by_H, Div by_tiles,
-                                                    int tiles) {
-  constexpr int kLanes = D / 8, kPass = 256 / kLanes, kRows = 4 * kPass;
+                                                    float* neg_delta, float* lse2, int N, int H, Div by_heads,
+                                                    Div by_tiles, int tiles) {
+  constexpr int kLanes = D / 8, kPass = 256 / kLanes, kRows = 4 * kPass, kTokens = kRows / HEADS;
   __shared__ float sums[kRows];
   const int tid = thread_id();
-  const int bt = quot(block_id(), by_H), h = block_id() - bt * H;
-  const int b = quot(bt, by_tiles), t0 = (bt - b * tiles) * kRows;
+  const int bt = quot(block_id(), by_heads), h0 = (block_id() - bt * (H / HEADS)) * HEADS;
+  const int b = quot(bt, by_tiles), t0 = (bt - b * tiles) * kTokens;
   const int sub = tid / kLanes, lane = tid % kLanes;
-  const bool row = tid < kRows && t0 + tid < N;
-  const size_t at = ((size_t)b * H + h) * N + t0 + tid;
+  // row terms of thread tid < kRows: token tid % kTokens of head tid / kTokens
+  const bool row = tid < kRows && t0 + tid % kTokens < N;
+  const size_t at = ((size_t)b * H + h0 + tid / kTokens) * N + t0 + tid % kTokens;
   uint4 x[4], y[4];
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
-    const int t = min(t0 + p * kPass + sub, N - 1);
+    const int r = p * kPass + sub, h = h0 + r % HEADS;
+    const int t = min(t0 + r / HEADS, N - 1);
     const size_t off = (((size_t)b * N + t) * H + h) * D;
     x[p] = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(o) + off)[lane];
     y[p] = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(dout) + off)[lane];
@@ -62,7 +64,10 @@ __global__ void __launch_bounds__(256) delta_kernel(const void* o, const void* d
     for (int p = 0; p < 4; ++p) acc[p] += __shfl_xor(acc[p], m);
   if (lane == 0)
 #pragma unroll
-    for (int p = 0; p < 4; ++p) sums[p * kPass + sub] = acc[p];
+    for (int p = 0; p < 4; ++p) {
+      const int r = p * kPass + sub;
+      sums[r % HEADS * kTokens + r / HEADS] = acc[p];
+    }
   __syncthreads();
   if (row) {
     neg_delta[at] = -sums[tid];
@@ -105,16 +110,18 @@ __global__ void __launch_bounds__(256) combine_kernel(const float* partial, void
 
 }  // namespace
 
-int launch_delta_bf16(const KArgs& a, hipStream_t st) {
-  const int rows = a.D == 64 ? 128 : 64, tiles = (a.N + rows - 1) / rows;
-  const dim3 grid((unsigned)(a.B * tiles * a.H));
-  if (a.D == 64)
-    hipLaunchKernelGGL(delta_kernel<64>, grid, dim3(256), 0, st, a.o, a.dout, a.lse, a.neg_delta, a.lse2, a.N, a.H,
-                       div_by(a.H), div_by(tiles), tiles);
-  else
-    hipLaunchKernelGGL(delta_kernel<128>, grid, dim3(256), 0, st, a.o, a.dout, a.lse, a.neg_delta, a.lse2, a.N, a.H,
-                       div_by(a.H), div_by(tiles), tiles);
+template <int D, int HEADS>
+static int launch_delta_t(const KArgs& a, hipStream_t st) {
+  constexpr int tokens = 4 * 256 / (D / 8) / HEADS;
+  const int tiles = (a.N + tokens - 1) / tokens;
+  hipLaunchKernelGGL((delta_kernel<D, HEADS>), dim3((unsigned)(a.B * tiles * (a.H / HEADS))), dim3(256), 0, st, a.o, a.dout,
+                     a.lse, a.neg_delta, a.lse2, a.N, a.H, div_by(a.H / HEADS), div_by(tiles), tiles);
   return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_delta_bf16(const KArgs& a, hipStream_t st) {
+  if (a.H % 2 != 0) return a.D == 64 ? launch_delta_t<64, 1>(a, st) : launch_delta_t<128, 1>(a, st);
+  return a.D == 64 ? launch_delta_t<64, 2>(a, st) : launch_delta_t<128, 2>(a, st);
 }
 
 int launch_combine_partials(const KArgs& a, int dtype, hipStream_t st) {
