@@ -462,17 +462,23 @@ int launch_bwd_dq_bf16(const KArgs& a, hipStream_t st) {
 // N = 8192: 665 and 654; H = 8, N = 16384 (1536 workgroups): 629 and 615.  With more workgroups
 // nothing is gained (H = 32, N = 8192, 3072 workgroups: 719 and 719) or lost to the eight-wave
 // dQ (H = 64, Hkv = 8, N = 32768: 18.25 and 18.70 ms).
+// Groups of 128 and less leave half or more of dQ's 256 rows empty, so they share a launch only up to 700
+// workgroups, with long chains of dK/dV beside them (8 query heads to a kv head, 16) up to 1100 or the same
+// 1536.  Backward, G = 128: H = 8, N = 2048 (256 workgroups) 14.6 us in one launch and 20.7; H = 32, Hkv = 8,
+// N = 2048 (640) 38.6 and 40.2, N = 4096 (1280) 75.4 and 62.2; H = 4, Hkv = 2, N = 16384 (768) 44.1 and 38.0;
+// Hkv = H / 8: H = 8, N = 2048 (576) 42.5 and 50.9, G = 64, N = 2048 (1152) 43.6 and 42.6; H = 32, Hkv = 1,
+// G = 100, N = 4000 (1360) 86 and 109.
 // The kernel with the longer chains goes first, so that short ones fill the end: a 64-key tile of
 // dQ's 256 rows is half as much work again as a 64-row tile of dK/dV's 128 keys, of which there is
 // one for every query head of the part (H = 8, N = 4096: 77.2 us with dK/dV first).
 int launch_bwd_both_bf16(const KArgs& a, hipStream_t st) {
-  if (a.ds_spill) return 1;
   if (a.D == 64) return launch_bwd_both_d64(a, st);
   const bool partial = a.ragged || a.G % 256 != 0 || (a.split < a.G && a.split % 256 != 0);
   const int T_kv = partial ? ragged_tiles(a, 128) : a.G / 128, T_q = partial ? ragged_tiles(a, 256) : a.G / 256;
   const Grid kv = grid_of(T_kv, a.B * a.Hkv * a.NG * a.parts, 1, 32);
   const Grid q = grid_of(T_q, a.B * a.H * a.NG, a.r, 32);
   if (kv.blocks + q.blocks > kOneLaunchBlocks) return 1;
+  if (a.G <= 128 && a.r < 16 && a.B * a.NG * (a.Hkv * a.parts * T_kv + a.H * T_q) > (a.r < 8 ? 700 : 1100)) return 1;
   const int kv_first = 2 * a.r >= 3 * a.parts;
   const int n_first = kv_first ? kv.blocks : q.blocks;
   if (partial)
