@@ -23,14 +23,25 @@ constexpr int kTileBytes = BN * kRowBytes;   // 16 KB
 //   steps 8-11:      dQ^T += K^T dS^T for keys 16k .. 16k+15
 // Every step first issues the LDS reads of the next step into the other fragment buffer
 // (also across the exp/multiply sections), then runs its own four MFMAs.
-template <int STEP>
-__device__ __forceinline__ void dq_load(bf16x8 (&buf)[4], const char* Ks, const char* Vs, const LaneOffsets& lo) {
+// XTR: the transposed fragments' addresses are made of one, tr0 (that of column block 0): a column block
+// is bits 6 and 7 of the chunk's offset under the swizzle, eight rows further on flips bit 5 of it.
+template <int STEP, bool XTR>
+__device__ __forceinline__ void dq_load(bf16x8 (&buf)[4], const char* Ks, const char* Vs, const LaneOffsets& lo,
+                                        uint32_t tr0) {
   if constexpr (STEP < 8) {
     constexpr int ROW0 = 32 * (STEP / 4), J = STEP % 4;
     buf[0] = frag_rm<ROW0>(Ks, lo, 2 * J);
     buf[1] = frag_rm<ROW0>(Vs, lo, 2 * J);
     buf[2] = frag_rm<ROW0>(Ks, lo, 2 * J + 1);
     buf[3] = frag_rm<ROW0>(Vs, lo, 2 * J + 1);
+  } else if constexpr (XTR) {
+    constexpr int ROW0 = 16 * (STEP - 8);
+#pragma unroll
+    for (int db = 0; db < 4; ++db) {
+      const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(S2_LDS(bf16x4, (tr0 ^ (db << 6)) + ROW0 * kRowBytes));
+      const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(S2_LDS(bf16x4, (tr0 ^ (db << 6 | 32)) + (ROW0 + 8) * kRowBytes));
+      buf[db] = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
   } else {
 #pragma unroll
     for (int db = 0; db < 4; ++db) buf[db] = frag_tr<16 * (STEP - 8)>(Ks, lo, db);
@@ -69,16 +80,22 @@ __device__ __forceinline__ void dq_ds(f32x16& sa, const f32x16& pa, bf16x8& ds_l
   ds_hi = pack8(sa[8], sa[9], sa[10], sa[11], sa[12], sa[13], sa[14], sa[15]);
 }
 
+template <bool XTR>
 __device__ __forceinline__ void dq_tile(f32x16 (&dq_acc)[4], const bf16x8 (&qf)[8], const bf16x8 (&dof)[8],
                                         const char* Ks, const char* Vs, const LaneOffsets& lo, int j0,
                                         int qrow, float c2, float lse2, float delta, int g32, bool masked) {
 #define S2_DQ_STEP(N, CUR, NXT)                                   \
-  dq_load<N + 1>(NXT, Ks, Vs, lo);                                \
+  dq_load<N + 1, XTR>(NXT, Ks, Vs, lo, tr0);                      \
   dq_mma<N>(CUR, qf, dof, sa, pa, dsf, dq_acc);                   \
   __builtin_amdgcn_sched_barrier(0)
   bf16x8 fa[4], fb[4], dsf[4];
   f32x16 sa = zero16(), pa = zero16();
-  dq_load<0>(fa, Ks, Vs, lo);
+  uint32_t tr0 = 0;
+  if constexpr (XTR) {   // hidden from the optimizer, which would keep what is made of it ahead of the loop
+    tr0 = (uint32_t)(uintptr_t)S2_LDS(const char, Ks) + lo.tr[0][0];
+    asm volatile("" : "+v"(tr0));
+  }
+  dq_load<0, XTR>(fa, Ks, Vs, lo, tr0);
   __builtin_amdgcn_sched_barrier(0);
   S2_DQ_STEP(0, fa, fb);
   S2_DQ_STEP(1, fb, fa);
@@ -200,7 +217,7 @@ __device__ __forceinline__ void dq_workgroup(const KArgs& a, int T, const Deal& 
     const char* Ks = smem + STAGE * 2 * kTileBytes;
     const char* Vs = Ks + kTileBytes;
     if (j0 > qw0 + 31 || j0 + BN - 1 < lo_w) return;   // wholly outside this wave's visible keys
-    dq_tile(dq_acc, qf, dof, Ks, Vs, lo, j0, qrow, c2, lse2, delta, g32, j0 + BN - 1 > qw0);
+    dq_tile<RAGGED && WAVES == 8>(dq_acc, qf, dof, Ks, Vs, lo, j0, qrow, c2, lse2, delta, g32, j0 + BN - 1 > qw0);
   };
   if constexpr (WAVES == 4) {
     for (int n = 0; n < n_tiles; n += 2) {
