@@ -42,6 +42,50 @@ def test_parts(dtype, shape, parts, least):
     (compare_bf16 if dtype == "bf16" else compare_f32)(out, ref)
 
 
+@pytest.mark.parametrize("dtype,shape,room,parts", [("bf16", (1, 2048, 8, 1, 128, 1024), 7, 4),
+                                                    ("bf16", (1, 1536, 12, 1, 128, 768), 5, 4),
+                                                    ("f32", (1, 512, 8, 1, 64, 256), 4, 4)])
+def test_a_workspace_between_the_least_and_the_wanted(dtype, shape, room, parts):
+    """Room for some of the parts: the largest number of them that divides the query heads and fits, with
+    the partials ending where the workspace of that many ends."""
+    from gpu_util import run_hip
+    from paper_2309_12307_amd import binding
+    from test_gpu_parity_bf16 import compare as compare_bf16
+    from test_gpu_parity_f32 import compare as compare_f32
+    B, N, H, Hkv, D, G = shape
+    rows = 2 * ((B * H * N * 4 + 255) // 256 * 256)
+    each = 2 * B * N * Hkv * D * 4
+    assert binding.bwd_workspace_bytes(B, N, H, Hkv, D, G, binding.BF16 if dtype == "bf16" else binding.F32) > rows + room * each
+    inp = inputs.make_inputs(B, N, H, Hkv, D, seed=620 + N, dtype=dtype)
+    out = run_hip(inp, G, dtype, ws_bytes=rows + room * each)
+    exact = run_hip(inp, G, dtype, ws_bytes=rows + parts * each)
+    for name in ("dq", "dk", "dv"):
+        assert np.array_equal(out[name], exact[name]), name
+    ref = orc.s2attn_fwd_bwd(inp["q"], inp["k"], inp["v"], inp["do"], G, dtype=np.float64)
+    (compare_bf16 if dtype == "bf16" else compare_f32)(out, ref)
+
+
+def test_static_scratch_with_room_for_fewer_parts():
+    """The library's own scratch holds two parts where the workspace query asks for more: dk and dv add up
+    in another order, within the bounds."""
+    import torch
+    from gpu_util import run_hip, to_dev, to_np
+    from paper_2309_12307_amd import binding
+    from test_gpu_parity_bf16 import compare
+    B, N, H, Hkv, D, G = 1, 4096, 8, 1, 128, 1024
+    assert binding.bwd_workspace_bytes(B, N, H, Hkv, D, G) > binding.STATIC_SCRATCH_BYTES
+    inp = inputs.make_inputs(B, N, H, Hkv, D, seed=630, dtype="bf16")
+    q, k, v, do = (to_dev(inp[n], inp[n + "_bits"]) for n in ("q", "k", "v", "do"))
+    o, dq, dk, dv = (torch.full_like(t, float("nan")) for t in (q, q, k, v))
+    lse = torch.full((B, H, N), float("nan"), dtype=torch.float32, device="cuda")
+    binding.s2attn_fwd(q, k, v, o, lse, G)
+    binding.s2attn_bwd_ex_static(binding.make_params(q, k, v, o, lse, G, dout=do, dq=dq, dk=dk, dv=dv))
+    torch.cuda.synchronize()
+    out = {n: to_np(t) for n, t in (("o", o), ("lse", lse), ("dq", dq), ("dk", dk), ("dv", dv))}
+    compare(out, orc.s2attn_fwd_bwd(inp["q"], inp["k"], inp["v"], inp["do"], G))
+    assert np.array_equal(out["dq"], run_hip(inp, G, "bf16")["dq"])     # dq does not depend on the parts
+
+
 def test_class_boundary_off_the_middle_of_a_kv_head():
     """A shard whose first kv head has two unshifted and six shifted query heads."""
     from gpu_util import run_hip

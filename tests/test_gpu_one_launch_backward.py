@@ -3,7 +3,6 @@ dQ tile, dK/dV first and dQ first (one or several query heads to a kv head), the
 takes one launch (1536 workgroups of 512 threads; fewer where groups are short) and the next one, against
 the oracle.  Bounds: those of the parity tests for the group sizes, those of the random sweep for the
 larger tensors of the grids."""
-import numpy as np
 import pytest
 
 from oracle import s2attn_oracle as orc
@@ -20,25 +19,9 @@ def run(B, N, H, Hkv, G, D=128, **kw):
 
 
 def check_grid(*shape, **kw):
-    """Element by element 2e-2 and the rounding of the value to its bf16 output.  Up to 16 elements of a
-    tensor may be beyond it (of 16.8 million of N(0,1) data in short groups a few are: P sits on few keys
-    there and delta carries the rounding of single elements of o), if they are what the fp64 model of those
-    roundings gives."""
-    from bf16_rounding_model import bf16_backward_model, to_bf16
-    from gpu_util import bf16_tol, check_bf16_tensor, half_ulp_bf16, max_abs
-    inp, out, (o, lse, *grads) = run(*shape, **kw)
-    assert max_abs(out["lse"], lse) <= 2e-3
-    check_bf16_tensor("o", out["o"], o)
-    model = None
-    for i, (name, r) in enumerate(zip(("dq", "dk", "dv"), grads)):
-        assert np.all(np.isfinite(out[name])), name
-        over = np.abs(out[name].astype(np.float64) - r) > bf16_tol(r)
-        if over.any():
-            assert over.sum() <= 16, (name, int(over.sum()))
-            if model is None:
-                model = bf16_backward_model(inp["q"], inp["k"], inp["v"], inp["do"], shape[4], None, "second_half", False)
-            m = model[i][over]
-            assert np.all(np.abs(out[name][over] - to_bf16(m)) <= 6e-3 + 2 * half_ulp_bf16(m)), (name, np.argwhere(over))
+    from bf16_rounding_model import compare_or_model
+    inp, out, ref = run(*shape, **kw)
+    compare_or_model(out, inp, ref, shape[4])
 
 
 @pytest.mark.parametrize("Hkv", [4, 1])

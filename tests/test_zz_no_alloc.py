@@ -1,7 +1,8 @@
 """s2attn_bwd_ex_static (backward on the library's static device scratch, no workspace and
 no allocation) against s2attn_bwd_ex on a caller workspace with the same (recomputing)
-backward: same kernels on the same inputs, so the outputs must be identical.  Two calls in a row share the scratch array, the
-second on a smaller problem."""
+backward: where the scratch holds as many parts of a kv head's query heads as the workspace query asks
+for, which it does for all problems here, the same kernels run on the same inputs, so the outputs must be
+identical.  Two calls in a row share the scratch array, the second on a smaller problem."""
 import numpy as np
 import pytest
 
