@@ -120,7 +120,7 @@ int parts_that_fit(const s2attn_params* p, bool mixed, size_t avail) {
 // kernel through the workspace, one kv head's query heads after the other.
 constexpr size_t kDsSpillCap = (size_t)16 << 30;   // what the workspace queries ask for at most
 
-// Shapes the role-split dK/dV kernel (and so the stored-dS path) accepts.
+// Shapes of the stored-dS backward: whole tiles throughout, and kv heads of one class.
 bool stored_ds_applies(const s2attn_params* p, int shift, int from) {
   if (p->dtype != S2ATTN_BF16 || p->D != 128) return false;
   if (p->G % 128 != 0 || shift % 64 != 0) return false;
@@ -526,7 +526,7 @@ const char* s2attn_strerror(int code) {
     case S2ATTN_ERR_GROUP: return "need N % G == 0, G even and 0 <= shift < G";
     case S2ATTN_ERR_HEADS: return "need H even and H % Hkv == 0";
     case S2ATTN_ERR_HEADDIM: return "unsupported head dimension (64 or 128)";
-    case S2ATTN_ERR_WORKSPACE: return "backward workspace missing or smaller than s2attn_bwd_workspace_bytes";
+    case S2ATTN_ERR_WORKSPACE: return "backward workspace missing or smaller than the row terms (and two parts of dk, dv where a kv head serves both head classes) need";
     case S2ATTN_ERR_DTYPE: return "unknown dtype, shift rule or wrap variant";
     case S2ATTN_ERR_DEVICE: return "current device is not gfx950 (MI355X)";
     case S2ATTN_ERR_LAUNCH: return "HIP kernel launch failed";

@@ -409,13 +409,13 @@ __device__ __forceinline__ void dkdv_workgroup(const KArgs& a, int T, const Deal
 
 template <bool SPILL, bool RAGGED>
 __global__ void __launch_bounds__(512, 1)
-bwd_dkdv_split_kernel(KArgs a, int T, Deal deal) {
+bwd_dkdv_split_kernel(KArgs a, int T, Deal deal, int first_block) {
   __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
-  dkdv_workgroup<SPILL, RAGGED>(a, T, deal, a.first_block + block_id(), thread_id(), smem);
+  dkdv_workgroup<SPILL, RAGGED>(a, T, deal, first_block + block_id(), thread_id(), smem);
 }
 
-// Both in one launch, dK/dV first: neither needs the other, and where one of them does not fill
-// the chip their chains of tiles run side by side.  dQ takes workgroups of eight waves here.
+// Both in one launch (kv_first: dK/dV first): neither needs the other, and where one of them does not
+// fill the chip their chains of tiles run side by side.  dQ takes workgroups of eight waves here.
 template <bool RAGGED>
 __global__ void __launch_bounds__(512, 1)
 bwd_both_kernel(KArgs a, int n_first, int kv_first, int T_kv, Deal deal_kv, int T_q, Deal deal_q) {

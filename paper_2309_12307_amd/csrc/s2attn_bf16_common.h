@@ -132,14 +132,6 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 
 __device__ __forceinline__ void wait_vmcnt0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// Value of the same register in lane (l ^ 32).
-__device__ __forceinline__ float other_half(float x) {
-  const uint32_t u = __float_as_uint(x);
-  auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  // lanes < 32 receive the partner in r[1], lanes >= 32 in r[0]
-  return __uint_as_float((thread_id() & 32) ? r[0] : r[1]);
-}
-
 __device__ __forceinline__ float max_halves(float x) {
   const uint32_t u = __float_as_uint(x);
   auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);

@@ -10,8 +10,8 @@
 // other.  LDS tile rows are 128 bytes, two to a 256-byte bank row (tile_off64).
 //
 // N = 32768, H = 32, G = 8192 against the 128-wide kernels with the upper half of every row left
-// out: forward 1516 -> 1245 us (53 % MFMA-busy at a clock of 1.6 GHz), dK/dV 3082 -> 2256 us,
-// dQ 1866 -> 1530 us (64 % MFMA-busy at 1.65 GHz, the power limit).
+// out: forward 1516 -> 1236 us (matrix unit busy 54 % of the time at a clock of 1.6 GHz), dK/dV 3082 ->
+// 2198 us (51 % at 1.9 GHz), dQ 1866 -> 1542 us (64 % at 1.6 GHz, the power limit).
 #include "s2attn_bf16_common.h"
 #include "s2attn_device.h"
 #include "s2attn_launch.h"
@@ -135,13 +135,13 @@ __device__ __forceinline__ void store_rows(const KArgs& a, void* out, const TStr
 // the clock it leaves.
 // ===========================================================================
 __global__ void __launch_bounds__(256, 4)
-fwd_d64_kernel(KArgs a, int T, Deal deal) {
+fwd_d64_kernel(KArgs a, int T, Deal deal, int first_block) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * kTile];   // [stage][K,V]
   const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
   const int g32 = lane >> 5, l32 = lane & 31;
 
   int seq, rank;
-  if (!decode_block(a.first_block + block_id(), T, deal, seq, rank)) return;
+  if (!decode_block(first_block + block_id(), T, deal, seq, rank)) return;
   const HeadPos at = head_of_seq(a, seq);
   const int c = at.c, b = at.b, h = at.h;
   int qt = T - 1 - rank;
@@ -253,7 +253,7 @@ fwd_d64_kernel(KArgs a, int T, Deal deal) {
 // the diagonal, heads innermost (workgroups of one group then read the same tile at about the same
 // time).  All four products in one wave: P and dS never leave its registers.  Two workgroups per
 // CU.  One 32-query block after the other instead of the phases of dkdv64_tile, in one loop with the
-// masked tiles: 2720 us at the size above, 2256 now.
+// masked tiles: 2720 us at the size above, 2198 now.
 // ===========================================================================
 struct RowTerms {
   float lse2[kTR], neg_delta[kTR];
@@ -587,16 +587,16 @@ __device__ __forceinline__ void dq64_workgroup(const KArgs& a, int T, const Deal
 }
 
 __global__ void __launch_bounds__(256, 2)
-bwd_dkdv_d64_kernel(KArgs a, int T, Deal deal) {
+bwd_dkdv_d64_kernel(KArgs a, int T, Deal deal, int first_block) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * kTile];
   __shared__ __attribute__((aligned(1024))) RowTerms rows_s[2];
-  dkdv64_workgroup(a, T, deal, a.first_block + block_id(), thread_id(), smem, rows_s);
+  dkdv64_workgroup(a, T, deal, first_block + block_id(), thread_id(), smem, rows_s);
 }
 
 __global__ void __launch_bounds__(256, 3)
-bwd_dq_d64_kernel(KArgs a, int T, Deal deal) {
+bwd_dq_d64_kernel(KArgs a, int T, Deal deal, int first_block) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * kTile];
-  dq64_workgroup(a, T, deal, a.first_block + block_id(), thread_id(), smem);
+  dq64_workgroup(a, T, deal, first_block + block_id(), thread_id(), smem);
 }
 
 // Both in one launch, dK/dV first: neither needs the other, and where they do not fill the chip their

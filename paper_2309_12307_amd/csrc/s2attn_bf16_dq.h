@@ -238,9 +238,9 @@ __device__ __forceinline__ void dq_workgroup(const KArgs& a, int T, const Deal& 
 
 template <bool RAGGED>
 __global__ void __launch_bounds__(256, 2)
-bwd_dq_bf16_kernel(KArgs a, int T, Deal deal) {
+bwd_dq_bf16_kernel(KArgs a, int T, Deal deal, int first_block) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes];
-  dq_workgroup<RAGGED, 4>(a, T, deal, a.first_block + block_id(), thread_id(), smem);
+  dq_workgroup<RAGGED, 4>(a, T, deal, first_block + block_id(), thread_id(), smem);
 }
 
 }  // namespace

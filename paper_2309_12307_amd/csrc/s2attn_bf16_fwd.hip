@@ -156,12 +156,12 @@ __device__ __forceinline__ void fwd_epilogue(const KArgs& a, FwdState& st, char*
 }
 
 // RAGGED: G is not a multiple of 128, the shift not of 64 or a Variant 2 split not of 128 --
-// tiles may be partial and the wrap point may fall inside one, so every staged row finds
-// its own token, and the two halves of a split wrap-around group run as causal runs of
-// their own (run_of_tile).
+// tiles may be partial and the wrap point may fall inside one; the rows of such a tile find
+// their tokens one by one, all other tiles are 64 consecutive tokens.  The two halves of a
+// split wrap-around group run as causal runs of their own (run_of_tile).
 template <bool RAGGED>
 __global__ void __launch_bounds__(256, 2)
-fwd_bf16_kernel(KArgs a, int T, Deal deal) {
+fwd_bf16_kernel(KArgs a, int T, Deal deal, int first_block) {
   constexpr int BM = 128;
   __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes];   // [stage][K,V]
 
@@ -175,7 +175,7 @@ fwd_bf16_kernel(KArgs a, int T, Deal deal) {
   // four of the eight XCDs only (N = 8192, H = 32, G = 2048: forward 278 us,
   // 149 dealt out per query head; dQ 383 and 198).
   int seq, rank;
-  if (!decode_block(a.first_block + block_id(), T, deal, seq, rank)) return;
+  if (!decode_block(first_block + block_id(), T, deal, seq, rank)) return;
   const HeadPos at = head_of_seq(a, seq);
   const int gidx = at.g, c = at.c, b = at.b, h = at.h;
   int qt = T - 1 - rank;

@@ -42,7 +42,6 @@ struct KArgs {
   float* dkv_partial;                        // fp32 [dk, dv][parts][B,N,Hkv,D] or null
   void* ds_spill;                            // bf16 dS tiles handed from the dK/dV kernel to the dQ kernel, or null
   int c_begin, c_count;                      // kv heads [c_begin, c_begin + c_count) of this launch (spill path)
-  int first_block;                           // of this launch, when a grid goes out in pieces (launch_blocks)
   TStride sq, sk, sv, sdq, sdk, sdv;         // q, k, v and their gradients may be strided views
   TStride so;                                // o and dout: contiguous (B,N,H,D)
   int B, N, H, Hkv, D, G;

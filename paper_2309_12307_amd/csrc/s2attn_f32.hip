@@ -17,13 +17,15 @@
 //     4 q4 + v.  The matching A operand is X[4 q4 + v][64 j + 4 c16 .. +3]: element e feeds the
 //     MFMA whose A row c16 is d = 64 j + 4 c16 + e, and C register w of accumulator (j, e) is
 //     d = 64 j + 16 q4 + 4 w + e: a lane ends with 16 consecutive d per j and stores float4s.
-// Both reads are free of bank conflicts with the sixteen-byte chunks of a row permuted by
-// chunk ^ (row & 7).  Tiles have 32 rows, two LDS stages, filled by direct global -> LDS loads.
+// The sixteen-byte chunks of a row are permuted by chunk ^ (row & 7): the transposed read (16 chunks of a
+// row) is free of bank conflicts, the row-major one (16 rows of a chunk column) takes two turns, half of the
+// cycles in which LDS is active, which is a fifth of all.  Tiles have 32 rows, two LDS stages, filled by direct global -> LDS loads.
 //
 // N = 4096, H = 8, D = 128, G = 1024, forward + backward: plain fp32 fma kernels with a pre-pass
-// for delta took 2890 us (10 TFLOP/s of the 14 D flops per pair), these 388 us (78; executed 100
-// of the 153 TFLOP/s that a library fp32 product of 8192^3 reaches).  N = 256, H = 4, D = 64,
-// G = 64: 119 -> 19 us, of which the two kernels take 7 and 13.
+// for delta took 2890 us (10 TFLOP/s of the 14 D flops per pair), these 386 us (78; executed 100
+// of the 154 TFLOP/s that a library fp32 product of 8192^3 reaches; forward 116 us and backward 272 with
+// the matrix unit busy 69 and 79 % of the time a CU works).  N = 256, H = 4, D = 64, G = 64: 119 -> 18 us,
+// of which the kernels are 6.8 and 9.7.
 #include <cfloat>
 
 #include "s2attn_bf16_common.h"
@@ -154,14 +156,14 @@ __device__ __forceinline__ void store_row(float* dst, const f32x4 (&acc)[D / 64]
 // layer of a few hundred tokens still spreads over the chip.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(256, 2) fwd_f32_kernel(KArgs a, int T, Deal deal) {
+__global__ void __launch_bounds__(256, 2) fwd_f32_kernel(KArgs a, int T, Deal deal, int first_block) {
   using L = Lanes<D>;
   __shared__ __attribute__((aligned(1024))) char smem[4 * L::kTileBytes];   // [stage][K, V]
 
   const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
   const int c16 = lane & 15, q4 = lane >> 4;
   int seq, rank;
-  if (!decode_block(a.first_block + block_id(), T, deal, seq, rank)) return;
+  if (!decode_block(first_block + block_id(), T, deal, seq, rank)) return;
   const HeadPos at = head_of_seq(a, seq);
   const int s = uni(shift_of_head(a, at.h));
   Run run;
@@ -460,10 +462,10 @@ __device__ __forceinline__ void bwd_dq_block(const KArgs& a, char* smem, int blo
 
 template <int D>
 __global__ void __launch_bounds__(256, 2)
-bwd_f32_kernel(KArgs a, int n_kv, int T, Deal deal_kv, Deal deal_q) {
+bwd_f32_kernel(KArgs a, int n_kv, int T, Deal deal_kv, Deal deal_q, int first_block) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * Lanes<D>::kTileBytes];   // [stage][Q, dO] or [stage][K, V]
   __shared__ __attribute__((aligned(16))) float rows_s[2 * 2 * kTile];             // [stage][lse * log2(e), delta]
-  const int block = a.first_block + block_id();
+  const int block = first_block + block_id();
   if (block < n_kv)
     bwd_dkdv_block<D>(a, smem, rows_s, block, T, deal_kv);
   else

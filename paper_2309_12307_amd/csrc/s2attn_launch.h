@@ -52,19 +52,18 @@ inline Grid grid_of(int T, int n_seq, int share, int slots) {
   return Grid{8 * T * pad_to(each, il), Deal{n_seq, bundle, il, div_by(bundle), div_by(il), div_by(T * il)}};
 }
 
-// Launches `blocks` blocks of `threads` threads as kernel(a, args...).  A launch counts the work items of
+// Launches `blocks` blocks of `threads` threads as kernel(args..., first_block).  A launch counts the work items of
 // a dimension in 32 bits and runs what is left modulo 2^32, without an error.  Many tiny groups reach
 // that (forward, G = 2: B * H * N = 2^25 rows), so a larger grid goes out in pieces, of a multiple of
-// eight blocks as the XCD is the block number mod 8; a kernel adds a.first_block to its block id.
+// eight blocks as the XCD is the block number mod 8; a kernel adds first_block to its block id.
 template <class Kernel, class... Args>
-inline int launch_blocks(Kernel kernel, int blocks, int threads, hipStream_t st, KArgs a, Args... args) {
+inline int launch_blocks(Kernel kernel, int blocks, int threads, hipStream_t st, const Args&... args) {
   const int piece = (int)(((1ll << 32) - 1) / threads / 8 * 8);
-  for (a.first_block = 0;;) {
-    const int n = blocks - a.first_block < piece ? blocks - a.first_block : piece;
-    hipLaunchKernelGGL(kernel, dim3(n), dim3(threads), 0, st, a, args...);
+  for (int first = 0;; first += piece) {
+    const int n = blocks - first < piece ? blocks - first : piece;
+    hipLaunchKernelGGL(kernel, dim3(n), dim3(threads), 0, st, args..., first);
     if (hipGetLastError() != hipSuccess) return -1;
-    if (n == blocks - a.first_block) return 0;
-    a.first_block += n;
+    if (n == blocks - first) return 0;
   }
 }
 

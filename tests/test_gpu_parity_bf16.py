@@ -102,8 +102,7 @@ def test_stored_ds_backward_with_variant2_and_custom_shift():
         compare(out, ref)
 
 
-# Head dimension 64 (runs on the kernels built for partial tiles, with the upper half of the
-# 128-element tile rows read as zeros).
+# Head dimension 64 (kernels of its own).
 D64_SHAPES = [
     (1, 512, 2, 2, 64, 128),       # aligned group
     (2, 1024, 4, 4, 64, 256),      # batch 2
