@@ -17,9 +17,11 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hi
          "-fno-honor-nans", "-mno-amdgpu-ieee",
          "-Wno-unused-command-line-argument", "-Wno-inline-asm"]
 
-# The forward's tile loops start at a multiple of 32 bytes.  Their speed depends on that address: 0.8 % slower
-# at six of its eight values modulo 32 (N = G = 32768, H = 32: 7232 us at one of those, 7178 aligned).
-FILE_FLAGS = {"s2attn_bf16_fwd.hip": ["-falign-loops=32"]}
+# The tile loops of these files start at a multiple of 32 bytes: their speed depends on the address modulo 32.
+# bf16 forward: 0.8 % slower at six of its eight values (N = G = 32768, H = 32: 7232 us at one of those, 7178
+# aligned); fp32 forward, D = 64: N = 4096, H = 8, G = 1024 67.6 and 67.2 us, Hkv = 1, G = 256 20.2 and 20.0.
+# (bf16 backward: the aligned dK/dV kernel is 2 % slower with every loop aligned; it pins its two loops itself.)
+FILE_FLAGS = {"s2attn_bf16_fwd.hip": ["-falign-loops=32"], "s2attn_f32.hip": ["-falign-loops=32"]}
 
 
 def build(verbose: bool = True, extra_flags=(), out_path: str | None = None) -> str:
