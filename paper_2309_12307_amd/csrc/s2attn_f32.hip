@@ -24,35 +24,20 @@
 // N = 4096, H = 8, D = 128, G = 1024, forward + backward: plain fp32 fma kernels with a pre-pass
 // for delta took 2890 us (10 TFLOP/s of the 14 D flops per pair), these 386 us (78; executed 100
 // of the 154 TFLOP/s that a library fp32 product of 8192^3 reaches; forward 116 us and backward 272 with
-// the matrix unit busy 69 and 79 % of the time a CU works).  N = 256, H = 4, D = 64, G = 64: 119 -> 18 us,
-// of which the kernels are 6.8 and 9.7.
+// the matrix unit busy 69 and 79 % of the time a CU works). 
+// Problems of few rows: s2attn_f32_small.hip.
 #include <cfloat>
 
 #include "s2attn_bf16_common.h"
 #include "s2attn_device.h"
+#include "s2attn_f32_common.h"
 #include "s2attn_launch.h"
 
 namespace s2 {
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kTile = 32;     // rows of a staged tile
 constexpr int kWgRows = 64;   // rows a workgroup owns: 16 per wave
-
-__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// Sum / maximum over the four lanes that share a column (lanes c16 + 16 q4).
-__device__ __forceinline__ float sum_cols(float x) {
-  x += __shfl_xor(x, 16);
-  return x + __shfl_xor(x, 32);
-}
-__device__ __forceinline__ float max_cols(float x) {
-  x = fmaxf(x, __shfl_xor(x, 16));
-  return fmaxf(x, __shfl_xor(x, 32));
-}
 
 template <int D>
 struct Lanes {
@@ -128,25 +113,6 @@ __device__ __forceinline__ void accumulate(f32x4 (&acc)[D / 64][4], const char* 
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[j][e] = mfma4(x1[e], wt[1][v], acc[j][e]);
     }
-}
-
-// The wave's own 16 rows as B operand: X[row][16 i + 4 q4 ..] straight from global memory.
-template <int D>
-__device__ __forceinline__ void load_own(f32x4 (&own)[D / 16], const void* src, size_t off, int q4) {
-  const float* p = static_cast<const float*>(src) + off + 4 * q4;
-#pragma unroll
-  for (int i = 0; i < D / 16; ++i) own[i] = *reinterpret_cast<const f32x4*>(p + 16 * i);
-}
-
-// Stores the accumulators of the lane's row (column c16 of C): 16 consecutive d per j.
-template <int D>
-__device__ __forceinline__ void store_row(float* dst, const f32x4 (&acc)[D / 64][4], float mul, int q4) {
-#pragma unroll
-  for (int j = 0; j < D / 64; ++j)
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-      *reinterpret_cast<float4*>(dst + 64 * j + 16 * q4 + 4 * w) =
-          make_float4(acc[j][0][w] * mul, acc[j][1][w] * mul, acc[j][2][w] * mul, acc[j][3][w] * mul);
 }
 
 // ---------------------------------------------------------------------------
@@ -489,13 +455,35 @@ int launch_bwd_t(const KArgs& a, bool dq_last, hipStream_t st) {
   return launch_blocks(bwd_f32_kernel<D>, q.blocks, 256, st, a, 0, T, kv.deal, q.deal);
 }
 
+// Few workgroups of 64 rows: 16 rows to a workgroup and its waves on different tiles (s2attn_f32_small.hip).
+// Forward up to one workgroup per CU (H = 4, D = 128, groups of 500, N = 1000: 44.7 us here and 16.7 there; H = 8,
+// N = 2048, groups of 512, 256 workgroups: 46.0 and 38.4; groups of 256, 512 workgroups: 34.9 and 42.5), in
+// groups of one workgroup or less up to a quarter of that (groups of 64, H = 4, D = 64, N = 256, 16 workgroups:
+// 6.4 and 4.7; N = 2560, 160 workgroups: 6.8 and 7.2).
+bool small_fwd(const KArgs& a) {
+  const long long n = (long long)a.B * a.H * a.NG * ragged_tiles(a, kWgRows);
+  return n <= (a.G > kWgRows ? 256 : 64);
+}
+// Backward, which reads every tile in four or five forms there, from the caches: up to half a workgroup per CU,
+// long chains up to one, groups of a few tiles an eighth unless several query heads to a kv head make dK/dV's
+// chains long again.  H = 4, D = 64, groups of 256, N = 1024 (64 workgroups): 26.2 us here and 19.7 there; D = 128,
+// groups of 512, N = 2048 (128) 82.2 and 72.1, N = 2560 (160) 113 and 134; groups of 1000, H = 2, N = 5000 (160)
+// 238 and 212; groups of 64, N = 256 (16) 14.6 and 10.6, N = 1024 (64) 15.8 and 17.9; H = 8, Hkv = 2, groups of
+// 128, N = 1024 (128) 47.7 and 38.8.
+bool small_bwd(const KArgs& a) {
+  const long long n = (long long)a.B * a.H * a.NG * ragged_tiles(a, kWgRows);
+  return n <= (a.G >= 1000 ? 256 : a.G >= 250 || a.r >= 4 ? 128 : 32);
+}
+
 }  // namespace
 
 int launch_fwd_f32(const KArgs& a, hipStream_t st) {
+  if (small_fwd(a)) return launch_fwd_f32_small(a, st);
   return a.D == 64 ? launch_fwd_t<64>(a, st) : launch_fwd_t<128>(a, st);
 }
 
 int launch_bwd_f32(const KArgs& a, bool dq_last, hipStream_t st) {
+  if (small_bwd(a)) return launch_bwd_f32_small(a, dq_last, st);
   return a.D == 64 ? launch_bwd_t<64>(a, dq_last, st) : launch_bwd_t<128>(a, dq_last, st);
 }
 

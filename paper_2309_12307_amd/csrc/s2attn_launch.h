@@ -8,6 +8,9 @@ namespace s2 {
 int launch_fwd_f32(const KArgs& a, hipStream_t st);
 // dQ, dK and dV (or partials), delta included; dq_last: dQ in a launch of its own after dK/dV
 int launch_bwd_f32(const KArgs& a, bool dq_last, hipStream_t st);
+// the same for problems of few rows
+int launch_fwd_f32_small(const KArgs& a, hipStream_t st);
+int launch_bwd_f32_small(const KArgs& a, bool dq_last, hipStream_t st);
 
 int launch_fwd_bf16(const KArgs& a, hipStream_t st);
 int launch_bwd_dkdv_bf16(const KArgs& a, hipStream_t st);  // delta must be ready; a.ds_spill set: also stores the dS blobs
