@@ -107,32 +107,55 @@ def _ptr(x):
     return x.data_ptr()
 
 
+def _ptrs(*ts):
+    """Addresses of contiguous tensors (None for None)."""
+    out = []
+    for t in ts:
+        if t is None:
+            out.append(None)
+        elif t.is_contiguous():
+            out.append(t.data_ptr())
+        else:
+            raise ValueError("s2attn tensors must be contiguous")
+    return out
+
+
+_torch = None   # torch, imported at the first call that needs it
+
+
+def _import_torch():
+    global _torch
+    import torch
+    _torch = torch
+    return torch
+
+
 def _stream(stream):
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
-    import torch
+    torch = _torch or _import_torch()
+    try:   # the handle itself: no Stream object for a call of a few microseconds
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        pass
     return torch.cuda.current_stream().cuda_stream
 
 
 def _dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.bfloat16:
+    torch = _torch or _import_torch()
+    dtype = t.dtype
+    if dtype == torch.bfloat16:
         return BF16
-    if t.dtype == torch.float32:
+    if dtype == torch.float32:
         return F32
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    raise TypeError(f"unsupported dtype {dtype}")
 
 
 def _dims(q, k):
     B, N, H, D = q.shape
     Hkv = k.shape[2]
     return B, N, H, Hkv, D
-
-
-def _require_contiguous(*ts):
-    for t in ts:
-        if t is not None and not t.is_contiguous():
-            raise ValueError("s2attn tensors must be contiguous")
 
 
 def bwd_workspace_bytes(B, N, H, Hkv, D, G, dtype=BF16) -> int:
@@ -183,20 +206,24 @@ def check_args(p: S2AttnParams, backward: bool) -> int:
 
 def s2attn_fwd(q, k, v, o, lse, G, stream=None) -> None:
     """o, lse <- S2-Attn(q, k, v) with the published defaults.  bf16 or fp32 tensors."""
-    _require_contiguous(q, k, v, o, lse)
-    B, N, H, Hkv, D = _dims(q, k)
-    f = lib().s2attn_fwd if _dtype_code(q) == BF16 else lib().s2attn_fwd_f32
-    _check(f(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), B, N, H, Hkv, D, G, _stream(stream)))
+    ptrs = _ptrs(q, k, v, o, lse)
+    B, N, H, D = q.shape
+    L = _lib or lib()
+    f = L.s2attn_fwd if _dtype_code(q) == BF16 else L.s2attn_fwd_f32
+    code = f(*ptrs, B, N, H, k.shape[2], D, G, _stream(stream))
+    if code:
+        _check(code)
 
 
 def s2attn_bwd(q, k, v, o, dout, lse, dq, dk, dv, workspace, G, stream=None) -> None:
     """dq, dk, dv <- gradients of sum(o * dout); workspace is a uint8 device tensor."""
-    _require_contiguous(q, k, v, o, dout, lse, dq, dk, dv, workspace)
-    B, N, H, Hkv, D = _dims(q, k)
-    f = lib().s2attn_bwd if _dtype_code(q) == BF16 else lib().s2attn_bwd_f32
-    _check(f(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(dout), _ptr(lse), _ptr(dq), _ptr(dk), _ptr(dv),
-             _ptr(workspace), workspace.numel() * workspace.element_size(),
-             B, N, H, Hkv, D, G, _stream(stream)))
+    ptrs = _ptrs(q, k, v, o, dout, lse, dq, dk, dv, workspace)
+    B, N, H, D = q.shape
+    L = _lib or lib()
+    f = L.s2attn_bwd if _dtype_code(q) == BF16 else L.s2attn_bwd_f32
+    code = f(*ptrs, workspace.numel() * workspace.element_size(), B, N, H, k.shape[2], D, G, _stream(stream))
+    if code:
+        _check(code)
 
 
 def s2attn_fwd_ex(p: S2AttnParams, stream=None) -> None:
