@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libs2attn.so")
 PROBES_LIB = os.path.join(HERE, "libs2attn_probes.so")
 SOURCES = ["s2attn_api.hip", "s2attn_prepost.hip", "s2attn_f32.hip", "s2attn_f32_small.hip", "s2attn_bf16_fwd.hip", "s2attn_bf16_bwd.hip",
-           "s2attn_bf16_dq_spill.hip", "s2attn_bf16_d64.hip"]
+           "s2attn_bf16_dq_spill.hip", "s2attn_bf16_d64.hip", "s2attn_bf16_small.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-fno-honor-nans", "-mno-amdgpu-ieee",

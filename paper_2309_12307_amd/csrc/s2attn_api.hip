@@ -405,6 +405,14 @@ static int run_bwd(const s2attn_params* p, void* stream, void* const* events) {
     mark(3);
     return S2ATTN_OK;
   }
+  if (ds_heads == 0 && s2::bwd_is_small(a)) {   // one launch, delta included
+    mark(1);
+    if (s2::launch_bwd_small(a, dq_last, st) != 0) return S2ATTN_ERR_LAUNCH;
+    mark(2);
+    if (a.parts > 1 && s2::launch_combine_partials(a, p->dtype, st) != 0) return S2ATTN_ERR_LAUNCH;
+    mark(3);
+    return S2ATTN_OK;
+  }
   if (s2::launch_delta_bf16(a, st) != 0) return S2ATTN_ERR_LAUNCH;
   mark(1);
   if (ds_heads > 0) {

@@ -25,6 +25,7 @@ namespace s2 {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 #define S2_LDS(T, p) ((__attribute__((address_space(3))) T*)(p))
@@ -87,6 +88,48 @@ __device__ __forceinline__ bf16x8 frag_tr(const char* tile, const LaneOffsets& o
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// ---- v_mfma_f32_16x16x32_bf16 operand layout (lane l, g = l / 16):
+//   A (16 x 32):  row  l % 16, contraction elements 8g .. 8g+7
+//   B (32 x 16):  col  l % 16, contraction elements 8g .. 8g+7
+//   C (16 x 16):  col  l % 16, register v holds row 4g + v
+// Two accumulator tiles of neighbouring 16-row blocks fed back as one B operand: slot e of a
+// 32-row step takes row 16*(e/4) + 4g + (e%4).
+struct LaneOffsets16 {
+  int rm[4];   // row-major fragment k: elements [32k + 8g, +8) of row (l % 16)
+  int tr[8];   // transposed fragment, columns 16db .. +15: row 4g + L/4 (the second half 16 rows further)
+};
+
+__device__ __forceinline__ void init_lane_offsets(LaneOffsets16& o, int lane) {
+  const int l16 = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) o.rm[k] = tile_off(l16, 4 * k + g);
+  const int row = 4 * g + (l16 >> 2);
+#pragma unroll
+  for (int db = 0; db < 8; ++db) {
+    const int col = 16 * db + 4 * (l16 & 3);
+    o.tr[db] = tile_off(row, col >> 3) + (col & 7) * 2;
+  }
+}
+
+// Row-major operand fragment k (elements [32k + 8g, +8)) of row ROW0 + (l % 16).
+template <int ROW0>
+__device__ __forceinline__ bf16x8 frag_rm(const char* tile, const LaneOffsets16& o, int k) {
+  static_assert(ROW0 % 16 == 0, "row block must start at a multiple of 16 rows");
+  return *reinterpret_cast<const bf16x8*>(tile + o.rm[k] + ROW0 * kRowBytes);
+}
+
+// Transposed operand fragment: 16 columns starting at 16*db along the operand rows, the 32 tile rows
+// starting at KROW0 along the contraction, in the accumulator-feedback order above.
+template <int KROW0>
+__device__ __forceinline__ bf16x8 frag_tr(const char* tile, const LaneOffsets16& o, int db) {
+  static_assert(KROW0 % 16 == 0, "row block must start at a multiple of 16 rows");
+  const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+      S2_LDS(bf16x4, tile + o.tr[db] + KROW0 * kRowBytes));
+  const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+      S2_LDS(bf16x4, tile + o.tr[db] + (KROW0 + 16) * kRowBytes));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 // Direct global -> LDS copy of 16 bytes per lane (global_load_lds_dwordx4): lane i of
 // the wave fetches the 16 bytes at its own global address `g`, and they land at LDS byte
 // address lds_base + 16*i, where lds_base must be wave-uniform.  Issued as inline
@@ -144,6 +187,19 @@ __device__ __forceinline__ float sum_halves(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Maximum and sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (one query in 16 x 16 tiles).
+__device__ __forceinline__ float max_of_4(float x) {
+  const uint32_t u = __float_as_uint(x);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return max_halves(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+
+__device__ __forceinline__ float sum_of_4(float x) {
+  const uint32_t u = __float_as_uint(x);
+  auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return sum_halves(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
 __device__ __forceinline__ bf16x8 pack8(float a0, float a1, float a2, float a3,
                                         float a4, float a5, float a6, float a7) {
   bf16x8 r;
@@ -162,6 +218,10 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 // Scheduling hint for the region since the last sched_barrier: N times
 // {1 MFMA, up to DS LDS reads, up to VA VALU/transcendental instructions}, so that the
 // vector work of one block is issued in the shadow of another block's matrix work.
@@ -174,6 +234,12 @@ __device__ __forceinline__ void interleave_mfma() {
     if (VA > 0) __builtin_amdgcn_sched_group_barrier(0x402, VA, 0);
   }
 }
+
+__device__ __forceinline__ bf16x8 pack8(f32x4 a, f32x4 b) {
+  return pack8(a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]);
+}
+
+__device__ __forceinline__ f32x4 zero4() { return f32x4{0.f, 0.f, 0.f, 0.f}; }
 
 __device__ __forceinline__ f32x16 zero16() {
   f32x16 z;

@@ -498,6 +498,7 @@ fwd_bf16_pp_kernel(KArgs a, int T, Deal deal) {
 
 int launch_fwd_bf16(const KArgs& a, hipStream_t st) {
   if (a.D == 64) return launch_fwd_d64(a, st);
+  if (fwd_is_small(a)) return launch_fwd_small(a, st);
   const int n_seq = a.B * a.H * a.NG;
   // groups of 2048 tokens or more: the eight-wave kernel; shorter tile sequences run a little
   // faster (4-9 % at G = 512 ... 1024) with two independent four-wave workgroups per CU, whose

@@ -103,6 +103,13 @@ struct Deal {
   Div by_bundle, by_il, by_span;   // span: T * il
 };
 
+// Reads one word of every 64 bytes of a kernel's arguments and waits once.  The compiler loads arguments
+// where they are first used, in three or four steps that each wait for memory as long as a workgroup's
+// CU has not seen them yet.
+__device__ __forceinline__ void fetch_args(const KArgs& a, const Deal& deal) {
+  asm volatile("" :: "s"(a.q), "s"(a.dv), "s"(a.sk.t), "s"(a.sdk.b), "s"(a.so.b), "s"(a.by_NG.mul), "s"(deal.by_span.shift));
+}
+
 // Block -> (sequence, rank): rank orders the T tiles of a sequence from heaviest (0) to lightest.
 // `il` sequences of an XCD are walked together, heaviest tiles of all of them first: when a
 // sequence has fewer tiles than the XCD has workgroup slots, several sequences are resident

@@ -19,6 +19,11 @@ int launch_bwd_dq_bf16(const KArgs& a, hipStream_t st);
 constexpr int kOneLaunchBlocks = 6 * 256, kOneLaunchBlocks64 = 20 * 256;
 // both in one launch for the shapes that gain by it; 1 and no launch for the others
 int launch_bwd_both_bf16(const KArgs& a, hipStream_t st);
+// few rows (D = 128): forward; dK/dV, dQ and delta in one launch (dq_last: dQ in a launch of its own after dK/dV)
+bool fwd_is_small(const KArgs& a);
+bool bwd_is_small(const KArgs& a);
+int launch_fwd_small(const KArgs& a, hipStream_t st);
+int launch_bwd_small(const KArgs& a, bool dq_last, hipStream_t st);
 // head dimension 64, any shape (the three entry points above hand such calls on)
 int launch_fwd_d64(const KArgs& a, hipStream_t st);
 int launch_bwd_dkdv_d64(const KArgs& a, hipStream_t st);
