@@ -420,6 +420,7 @@ template <bool RAGGED>
 __global__ void __launch_bounds__(512, 1)
 bwd_both_kernel(KArgs a, int n_first, int kv_first, int T_kv, Deal deal_kv, int T_q, Deal deal_q) {
   __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
+  if constexpr (!RAGGED) fetch_args(a, deal_q);   // (partial tiles: 3 % slower with it, no registers left)
   const int id = block_id();
   const bool first = id < n_first;
   const int block = first ? id : id - n_first;

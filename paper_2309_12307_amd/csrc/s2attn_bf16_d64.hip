@@ -137,6 +137,7 @@ __device__ __forceinline__ void store_rows(const KArgs& a, void* out, const TStr
 __global__ void __launch_bounds__(256, 4)
 fwd_d64_kernel(KArgs a, int T, Deal deal, int first_block) {
   __shared__ __attribute__((aligned(1024))) char smem[4 * kTile];   // [stage][K,V]
+  fetch_args(a, deal);
   const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
   const int g32 = lane >> 5, l32 = lane & 31;
 

@@ -214,6 +214,7 @@ __global__ void __launch_bounds__(256, 2)
 fwd_bf16_kernel(KArgs a, int T, Deal deal, int first_block) {
   constexpr int BM = 128;
   __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes];   // [stage][K,V]
+  fetch_args(a, deal);
 
   const int tid = thread_id(), lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g32 = lane >> 5, l32 = lane & 31;
@@ -384,6 +385,7 @@ fwd_bf16_pp_kernel(KArgs a, int T, Deal deal) {
   constexpr int BM = 256;
   constexpr int kStageBytes = 2 * kTileBytes;
   __shared__ __attribute__((aligned(1024))) char smem[3 * kStageBytes];   // [stage][K,V]
+  fetch_args(a, deal);
 
   const int tid = thread_id(), lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g32 = lane >> 5, l32 = lane & 31;

@@ -125,6 +125,7 @@ template <int D>
 __global__ void __launch_bounds__(256, 2) fwd_f32_kernel(KArgs a, int T, Deal deal, int first_block) {
   using L = Lanes<D>;
   __shared__ __attribute__((aligned(1024))) char smem[4 * L::kTileBytes];   // [stage][K, V]
+  fetch_args(a, deal);
 
   const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
   const int c16 = lane & 15, q4 = lane >> 4;

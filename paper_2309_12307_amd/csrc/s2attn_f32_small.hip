@@ -97,6 +97,7 @@ template <int D>
 __global__ void __launch_bounds__(64 * kWaves, 2) fwd_f32_small_kernel(KArgs a, int T, Deal deal, int first_block) {
   __shared__ __attribute__((aligned(16))) float blocks[kWaves * kBlockFloats<D>];
   __shared__ float max_s[kWaves][kRows], sum_s[kWaves][kRows];
+  fetch_args(a, deal);
 
   const int tid = thread_id(), lane = tid & 63, w = uni(tid >> 6);
   const int c16 = lane & 15, q4 = lane >> 4;
@@ -376,6 +377,7 @@ template <int D>
 __global__ void __launch_bounds__(64 * kWaves, 2)
 bwd_f32_small_kernel(KArgs a, int n_kv, int T, Deal deal_kv, Deal deal_q, int first_block) {
   __shared__ __attribute__((aligned(16))) float blocks[2 * kWaves * kBlockFloats<D>];
+  fetch_args(a, deal_q);
   const int block = first_block + block_id();
   if (block < n_kv)
     dkdv_small_block<D>(a, blocks, block, T, deal_kv);
