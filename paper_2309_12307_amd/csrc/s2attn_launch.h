@@ -56,7 +56,13 @@ inline Grid grid_of(int T, int n_seq, int share, int slots) {
     if (share % m == 0 && n_seq / m % 8 == 0) { bundle = m; break; }
   const int each = (n_seq / bundle + 7) / 8 * bundle;   // sequences of one XCD
   const int want = interleave_for(T, slots);
-  const int il = want < each ? want : each;
+  // An XCD's sequences go in walks of `want` or more, as even as they can be: a last walk of one or two starts its
+  // heaviest tiles when nothing is left to run beside them.  us, walks of `want` and even ones: forward, H = 32,
+  // Hkv = 16, D = 64, N = 6144, G = 1536 (three sequences, 2 + 1 and 3) 70 and 49; H = 32, N = 2304, G = 768 (twelve,
+  // 11 + 1 and 12) 32 and 25; backward, H = 8, N = 7168, G = 1792 127 and 106; H = 40, Hkv = 20, N = 2520, G = 1260 188
+  // and 147.  44 shapes where the two differ: 1.07 (forward) and 1.04 (backward) in the mean, worst 0.96 and 0.94.
+  const int walks = each > want ? each / want : 1;
+  const int il = (each + walks - 1) / walks;
   return Grid{8 * T * pad_to(each, il), Deal{n_seq, bundle, il, div_by(bundle), div_by(il), div_by(T * il)}};
 }
 
