@@ -208,18 +208,21 @@ __device__ __forceinline__ void dkdv_small_block(const KArgs& a, float* blocks, 
   const int tok = run_token(a, run, j0 + c16, s);
   f32x4 kf[D / 16], vf[D / 16], qf[D / 16], gf[D / 16], of[D / 16], qt[4][D / 64], gt[4][D / 64], dk[D / 64][4], dv[D / 64][4];
   float lse = 0.f;
+  // first row of the it-th query tile: from the end of the run to the diagonal, so that the large
+  // probabilities are added last
+  auto first_row = [&](int it) __attribute__((always_inline)) { return j0 + (nq - 1 - it) * kRows; };
   auto load_rows = [&](int h, int it) __attribute__((always_inline)) {
-    const int t = run_token(a, run, j0 + it * kRows + c16, s);
+    const int t = run_token(a, run, first_row(it) + c16, s);
     load_rm<D>(qf, static_cast<const float*>(a.q) + row_off(a.sq, at.b, t, h), q4);
     load_rm<D>(gf, static_cast<const float*>(a.dout) + row_off(a.so, at.b, t, h), q4);
     load_rm<D>(of, static_cast<const float*>(a.o) + row_off(a.so, at.b, t, h), q4);
     lse = a.lse[((size_t)at.b * a.H + h) * a.N + t];
   };
   auto load_gt = [&](int h, int it) __attribute__((always_inline)) {
-    load_tr<D>(gt, a, a.dout, a.so, run, s, at.b, h, j0 + it * kRows, c16, q4);
+    load_tr<D>(gt, a, a.dout, a.so, run, s, at.b, h, first_row(it), c16, q4);
   };
   auto load_qt = [&](int h, int it) __attribute__((always_inline)) {
-    load_tr<D>(qt, a, a.q, a.sq, run, s, at.b, h, j0 + it * kRows, c16, q4);
+    load_tr<D>(qt, a, a.q, a.sq, run, s, at.b, h, first_row(it), c16, q4);
   };
   zero<D>(dk);
   zero<D>(dv);
@@ -241,7 +244,7 @@ __device__ __forceinline__ void dkdv_small_block(const KArgs& a, float* blocks, 
   // D = 64: an operand is loaded for the next tile once this tile's products are out; D = 128 has no
   // registers left for that and loads a tile's operands together.
   while (hh < nheads) {
-    const int q0 = j0 + it * kRows;
+    const int q0 = first_row(it);
     int hn = hh, in = it + kWaves;
     settle(hn, in);
     const bool more = hn < nheads;
