@@ -60,9 +60,13 @@ inline Grid grid_of(int T, int n_seq, int share, int slots) {
   // heaviest tiles when nothing is left to run beside them.  us, walks of `want` and even ones: forward, H = 32,
   // Hkv = 16, D = 64, N = 6144, G = 1536 (three sequences, 2 + 1 and 3) 70 and 49; H = 32, N = 2304, G = 768 (twelve,
   // 11 + 1 and 12) 32 and 25; backward, H = 8, N = 7168, G = 1792 127 and 106; H = 40, Hkv = 20, N = 2520, G = 1260 188
-  // and 147.  44 shapes where the two differ: 1.07 (forward) and 1.04 (backward) in the mean, worst 0.96 and 0.94.
+  // and 147.  Not where a sequence has few tiles and the last walk fills half the slots or more, as it then has little left
+  // to lose: forward, H = 8, G = 384, N = 14976 (39 of three tiles, 22 + 17 and 39) 28.6 and 30.8; G = 256, N = 20480 (80
+  // of two, 32 + 32 + 16 and 40 + 40) 34.3 and 36.9; with eight tiles 1.02 to 1.14 for even walks.  58 shapes of two to
+  // twelve tiles: 1.09 (forward) and 1.03 (backward) in the mean over walks of `want`, worst 0.97.
+  const bool uneven = T <= 4 && each > want && 2 * (each % want) >= want;
   const int walks = each > want ? each / want : 1;
-  const int il = (each + walks - 1) / walks;
+  const int il = uneven ? want : (each + walks - 1) / walks;
   return Grid{8 * T * pad_to(each, il), Deal{n_seq, bundle, il, div_by(bundle), div_by(il), div_by(T * il)}};
 }
 
