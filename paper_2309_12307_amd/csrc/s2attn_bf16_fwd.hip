@@ -9,7 +9,7 @@
 //                      row sum are in-lane reductions plus one exchange with lane^32;
 //                      the running maximum is only raised (and O rescaled) when it
 //                      grows by more than 2^8, which keeps exp2 arguments <= 8 (eight-wave
-//                      kernel: when the sum over a tile's keys grows beyond 2^12)
+//                      kernel: when a lane's sum over its 32 keys of a tile grows beyond 2^32)
 //   O^T += V^T P^T     A = V^T through transposing LDS reads, B = P^T straight from the
 //                      S^T accumulators (no cross-lane movement)
 // K/V tiles go global -> LDS directly (global_load_lds, 16 bytes per lane) into two
@@ -25,7 +25,7 @@ namespace {
 constexpr int BN = 64;                       // keys per tile
 constexpr int kTileBytes = BN * kRowBytes;   // 16 KB
 constexpr float kRescaleThreshold = 8.f;     // log2 units
-constexpr float kRescaleSum = 4096.f;        // of 32 probabilities (fwd_softmax_long)
+constexpr float kRescaleSum = 4294967296.f;  // of a lane's 32 probabilities (fwd_softmax_long)
 
 struct FwdState {
   f32x16 o_acc[4];
@@ -141,8 +141,12 @@ __device__ __forceinline__ float fwd_probs(const FwdState& st, const f32x16& s0,
 // The same update without looking for the maximum of every tile: a score far above the running maximum
 // shows in the row sum, which is needed anyway, and only then (and at the first tile) is the maximum formed, O
 // rescaled and the probabilities formed again.  Sixteen instructions and a chain of ten less a tile, for
-// long sequences of tiles: N = G = 32768, H = 32 7358 -> 7218 us; N = 32768, G = 8192 2011 -> 1966.  (Eight
-// tiles, G = 512: the first one's second pass costs 1.9 %.)
+// long sequences of tiles.  (Eight tiles, G = 512: the first one's second pass costs 1.9 %.)
+// The second pass is dear, and any of a wave's 32 rows asks for it, so the line is far out: P keeps its bits at any
+// size, and with 2^32 a row, O and l stay finite for v up to 2^80.  Against a maximum per tile, N = 8192, H = 32,
+// G = 2048, and N = 32768, H = 8 in one group, with lines of 2^12, 2^24 and 2^32: N(0, 1) 1.00, 1.01, 1.01 and 1.01, 1.01, 1.01 times
+// as fast; scores of standard deviation 8 0.96, 1.11, 1.13 and 1.01, 1.03, 1.05; of 16 0.91, 1.00, 1.06 and 0.99, 1.03, 1.05;
+// scores that rise by e^8 from tile to tile 0.87, 1.02, 1.06 and 0.87, 0.98, 1.06.
 __device__ __forceinline__ void fwd_softmax_long(FwdState& st, const f32x16& s0, const f32x16& s1, float c2, bf16x8 (&pf)[4]) {
   float sum = fwd_probs(st, s0, s1, c2, pf);
   if (__builtin_amdgcn_ballot_w64(!(sum <= kRescaleSum)) != 0) {
