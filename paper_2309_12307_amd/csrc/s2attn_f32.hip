@@ -457,23 +457,34 @@ int launch_bwd_t(const KArgs& a, bool dq_last, hipStream_t st) {
 }
 
 // Few workgroups of 64 rows: 16 rows to a workgroup and its waves on different tiles (s2attn_f32_small.hip).
-// Forward up to one workgroup per CU (H = 4, D = 128, groups of 500, N = 1000: 44.7 us here and 16.7 there; H = 8,
+// Times: us here and there.
+// Forward up to one workgroup per CU (H = 4, D = 128, groups of 500, N = 1000: 44.7 and 16.7; H = 8,
 // N = 2048, groups of 512, 256 workgroups: 46.0 and 38.4; groups of 256, 512 workgroups: 34.9 and 42.5), in
 // groups of one workgroup or less up to a quarter of that (groups of 64, H = 4, D = 64, N = 256, 16 workgroups:
-// 6.4 and 4.7; N = 2560, 160 workgroups: 6.8 and 7.2).
+// 6.4 and 4.7; N = 2560, 160 workgroups: 6.8 and 7.2).  In groups of two workgroups, whose chains are short, the busiest
+// XCD's share of the workgroups of 16 rows counts (three to a CU; groups of 128, D = 128: 11 sequences, 88 workgroups,
+// 14.9 and 13.2; 16, 128 workgroups, 15.2 and 17.5).  And not for long runs, which the tiles in LDS serve better than the
+// caches (H = 2, one group, D = 128: N = 4500 491 and 456, 5500 626 and 676; D = 64, H = 1: 10000 1046 and 1033,
+// 16000 2366 and 2611).
 bool small_fwd(const KArgs& a) {
-  const long long n = (long long)a.B * a.H * a.NG * ragged_tiles(a, kWgRows);
-  return n <= (a.G > kWgRows ? 256 : 64);
+  const int n_seq = a.B * a.H * a.NG;
+  const long long n = (long long)n_seq * ragged_tiles(a, kWgRows);
+  if (n > (a.G > kWgRows ? 256 : 64) || (long long)a.G * a.D > 4608 * 128) return false;
+  return a.G > 2 * kWgRows || most_of_an_xcd(n_seq) * ((a.G + 15) / 16) <= 96;
 }
-// Backward, which reads every tile in four or five forms there, from the caches: up to half a workgroup per CU,
-// long chains up to one, groups of a few tiles an eighth unless several query heads to a kv head make dK/dV's
-// chains long again.  H = 4, D = 64, groups of 256, N = 1024 (64 workgroups): 26.2 us here and 19.7 there; D = 128,
-// groups of 512, N = 2048 (128) 82.2 and 72.1, N = 2560 (160) 113 and 134; groups of 1000, H = 2, N = 5000 (160)
-// 238 and 212; groups of 64, N = 256 (16) 14.6 and 10.6, N = 1024 (64) 15.8 and 17.9; H = 8, Hkv = 2, groups of
-// 128, N = 1024 (128) 47.7 and 38.8.
+// Backward, which reads every tile in four or five forms there, from the caches: up to half a workgroup per CU
+// in groups of more than 256, groups of a few tiles an eighth (of 250 to 256 three eighths) unless several query heads
+// to a kv head make dK/dV's chains long again.  H = 4, D = 64, groups of 256, N = 1024 (64 workgroups): 26.2 and 19.7;
+// D = 128, groups of 512, N = 2048 (128) 82.2 and 72.1, N = 2560 (160) 113 and 134; groups of 64, N = 256 (16) 14.6 and
+// 10.6, N = 1024 (64) 15.8 and 17.9; groups of 250, 24 sequences (96) 43.8 and 36.8, 32 (128) 44.1 and 46.8; H = 8,
+// Hkv = 2, groups of 128, N = 1024 (128) 47.7 and 38.8.
+// Long chains up to one workgroup per CU of the busiest XCD (D = 128; groups of 1000: eight sequences 159 and 117, sixteen
+// 235 and 214, twenty 223 and 312; of 1250: eight 238 and 174, ten 265 and 326; of 1500: eight 312 and 229, twelve 326
+// and 446; 2048: one to eight 470 and 400; 2500: 509 and 585; 4096: 1014 and 1490; 8192: 3860 and 5780).
 bool small_bwd(const KArgs& a) {
-  const long long n = (long long)a.B * a.H * a.NG * ragged_tiles(a, kWgRows);
-  return n <= (a.G >= 1000 ? 256 : a.G >= 250 || a.r >= 4 ? 128 : 32);
+  const int n_seq = a.B * a.H * a.NG, T = ragged_tiles(a, kWgRows);
+  if (a.G >= 1000) return (long long)most_of_an_xcd(n_seq) * T <= 32;
+  return (long long)n_seq * T <= (a.G > 256 || a.r >= 4 ? 128 : a.G >= 250 ? 96 : 32);
 }
 
 }  // namespace

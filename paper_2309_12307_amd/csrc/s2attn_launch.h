@@ -42,6 +42,9 @@ int launch_combine_partials(const KArgs& a, int dtype, hipStream_t st);
 inline int interleave_for(int T, int slots) { return T >= slots ? 1 : (slots + T - 1) / T; }
 inline int pad_to(int n, int il) { return (n + il - 1) / il * il; }
 
+// Sequences of the XCD that gets the most of n_seq: whole sequences are dealt round the eight.
+inline int most_of_an_xcd(int n_seq) { return (n_seq + 7) / 8; }
+
 // Grid of a launch with n_seq sequences of T tiles, neighbouring `share` of which (a divisor of
 // n_seq) read the same K and V, on XCDs that hold `slots` workgroups at a time.  A bundle is the
 // largest piece of the `share` that deals every XCD the same number of sequences; one sequence

@@ -47,6 +47,24 @@ def layer(B, N, H, Hkv, D, G, dtype, q=None, k=None, **kw):
     return call(L.s2attn_fwd_ex), call(L.s2attn_bwd_ex)
 
 
+def check(shape, dtype, backward, **kw):
+    """Twice the batch, which lies beyond the line of the kernels for few rows, takes longer."""
+    B, N, H, Hkv, D, G = shape
+    one, two = (layer(b, N, H, Hkv, D, G, dtype, **kw) for b in (B, 2 * B))
+    one[0](), two[0]()
+    t1, t2 = times_us([one[backward], two[backward]], reps=20 if N < 4096 else 5)
+    assert t1 <= 1.05 * t2, (t1, t2)
+
+
+@pytest.mark.parametrize("shape,backward", [
+    ((1, 4096, 4, 4, 128, 4096), True), ((1, 8192, 2, 2, 64, 8192), True), ((1, 3000, 4, 2, 128, 3000), True),   # 1.24-1.32 with few rows
+    ((1, 16000, 1, 1, 128, 16000), False),
+])
+def test_f32_with_twice_the_batch(shape, backward):
+    import torch
+    check(shape, torch.float32, backward, **(dict(heads_total=2) if shape[2] == 1 else {}))
+
+
 @pytest.mark.parametrize("N,H,G", [(8192, 32, 2048), (32768, 8, 32768)])
 def test_rising_scores(N, H, G):
     """Scores that rise by eight (natural log) from key tile to key tile: the eight-wave forward forms a tile's
