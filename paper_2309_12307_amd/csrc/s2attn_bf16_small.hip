@@ -542,15 +542,35 @@ static long long small_blocks(const KArgs& a) { return (long long)a.B * a.H * a.
 // waves and so need a quarter of the loads once the chip is full; and not for chains so long that these are
 // the faster loop.  Forward, us, workgroups of 128 or 256 rows and here: H = 4, groups of 256, N = 1024 (128
 // workgroups of 32 rows): 8.6 and 7.1; groups of 2048, N = 2048 (256): 45.7 and 29.7; groups of 4096, H = 2,
-// N = 4096 (256): 85 and 95; groups of 512, N = 2560 (320): 13.2 and 14.3.
-bool fwd_is_small(const KArgs& a) { return a.D == 128 && a.G <= 2048 && small_blocks(a) <= 256; }
+// N = 4096 (256): 85 and 95; groups of 512, N = 2560 (320): 13.2 and 14.3.  Short chains take the time of a second round
+// badly, so up to eight workgroups to a sequence the busiest XCD has to hold all of its own at once (groups of 96:
+// ten sequences of an XCD, 30 workgroups, 6.8 and 5.9; eleven, 33, 6.8 and 9.6; of 192: five 9.0 and 7.2, six, 36, 8.9
+// and 9.8; of 288: four, 36, 10.9 and 10.0).
+bool fwd_is_small(const KArgs& a) {
+  const int T = ragged_tiles(a, kRows);
+  return a.D == 128 && a.G <= 2048 && small_blocks(a) <= 256 && (T >= 9 || most_of_an_xcd(a.B * a.H * a.NG) * T <= 32);
+}
 // Backward (delta and both gradients): groups of 256, N = 1024, H = 4, Hkv = 2 (128) 20.5 and 16.3; H = Hkv = 8 (256)
 // 17.9 and 18.5; Hkv = 2 (256) 32.9 and 24.9; groups of 1024, N = 1024, H = 8 (256) 41.4 and 31.4; groups of 2048,
 // H = 2, N = 2048 (128) 74.7 and 79.5; groups of 640, N = 2560, H = 4 (320) 25.8 and 31.5; groups of 64,
 // N = 1024, H = 8, Hkv = 4 (256) 11.8 and 14.0.
+// One workgroup to a CU, and dK/dV's are as many as dQ's where a part is one head: both of the busiest XCD together then
+// want to fit into one round of its 32 CUs, a little more as the chains grow, two rounds from ten workgroups to a
+// sequence on.  One head to a kv head, sequences of an XCD and the workgroups of both: groups of 96 five (30) 12.2 and
+// 9.9, six (36) 11.9 and 13.8; of 128 three (24) 12.3 and 10.1, six (48) 12.6 and 15.7; of 192 three (36) 14.4 and 14.1,
+// four (48) 14.4 and 15.7; of 256 two (32) 16.5 and 12.0, three (48) 17.7 and 16.8, four (64) 17 and 18.5; of 320 two (40)
+// 17 and 15.5, three (60) 18 and 20; of 512 two (64) 24.3 and 22.7; of 768 one (48) 32 and 21.5, two (96) 32.4 and 38.2.
+// With partials, which the others write too: groups of 66 six (36) 15.9 and 15.8, eight (48) 16.8 and 18.3; of 160 four
+// (40) 21.0 and 19.2, five (50) 21.2 and 20.1; of 192 four (48) 20.8 and 20.1, six (72) 22.2 and 27.7; of 640 two (80) 32.5
+// and 35.8.
 bool bwd_is_small(const KArgs& a) {
   const int most = a.G <= 64 ? 128 : a.r > 1 || a.G >= 512 ? 256 : 160;
-  return a.D == 128 && a.G <= 1536 && small_blocks(a) <= most;
+  if (a.D != 128 || a.G > 1536 || small_blocks(a) > most) return false;
+  const int T = ragged_tiles(a, kRows);
+  const int dq = most_of_an_xcd(a.B * a.H * a.NG), dkdv = most_of_an_xcd(a.B * a.Hkv * a.NG * a.parts);
+  const bool one_head = a.Hkv * a.parts >= a.H;   // to a part
+  const int fit = T >= 10 ? 64 : a.parts > 1 ? (T < 4 ? 36 : T < 5 ? 40 : 50) : T < 6 ? 32 : T < 7 ? 36 : 48;
+  return !one_head || dq == 1 || (dq + dkdv) * T <= fit;
 }
 
 int launch_fwd_small(const KArgs& a, hipStream_t st) {

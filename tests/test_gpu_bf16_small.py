@@ -43,6 +43,12 @@ def test_few_rows(B, N, H, Hkv, G):
     (1, 512, 16, 16, 512), (1, 576, 16, 16, 576),   # the same, long chains 256 | 288
     (1, 1536, 2, 2, 1536), (1, 1664, 2, 2, 1664),   # backward, group size
     (1, 2048, 2, 2, 2048), (1, 2304, 2, 2, 2304),   # forward, group size
+    (1, 960, 8, 4, 96), (1, 1056, 8, 4, 96),        # forward, 30 | 33 workgroups of an XCD
+    (1, 480, 8, 8, 96), (1, 576, 8, 8, 96),         # backward, one head per kv head, 30 | 36 of both kernels
+    (1, 576, 8, 8, 192), (1, 768, 8, 8, 192),       # the same, longer chains 36 | 48
+    (1, 1280, 4, 4, 320), (1, 1600, 4, 4, 320),     # the same, ten workgroups to a sequence 40 | 60
+    (1, 768, 8, 8, 768), (1, 1536, 6, 6, 768),      # the same, one sequence of an XCD | two
+    (1, 960, 6, 3, 160), (1, 1120, 6, 3, 160),      # the same, a kv head of both classes 50 | 60
 ])
 def test_on_the_lines(B, N, H, Hkv, G):
     check(B, N, H, Hkv, G)

@@ -65,6 +65,16 @@ def test_f32_with_twice_the_batch(shape, backward):
     check(shape, torch.float32, backward, **(dict(heads_total=2) if shape[2] == 1 else {}))
 
 
+@pytest.mark.parametrize("shape,backward", [
+    ((1, 1386, 4, 4, 128, 66), False), ((1, 2016, 4, 1, 128, 96), False),   # 1.29 and 1.32 with few rows
+    ((1, 1248, 4, 4, 128, 96), True), ((1, 2016, 2, 2, 128, 96), True),     # 1.08-1.14
+    ((1, 4032, 2, 1, 128, 192), True), ((1, 3840, 2, 2, 128, 768), True),
+])
+def test_bf16_with_twice_the_batch(shape, backward):
+    import torch
+    check(shape, torch.bfloat16, backward)
+
+
 @pytest.mark.parametrize("N,H,G", [(8192, 32, 2048), (32768, 8, 32768)])
 def test_rising_scores(N, H, G):
     """Scores that rise by eight (natural log) from key tile to key tile: the eight-wave forward forms a tile's
