@@ -462,15 +462,15 @@ int launch_bwd_t(const KArgs& a, bool dq_last, hipStream_t st) {
 // N = 2048, groups of 512, 256 workgroups: 46.0 and 38.4; groups of 256, 512 workgroups: 34.9 and 42.5), in
 // groups of one workgroup or less up to a quarter of that (groups of 64, H = 4, D = 64, N = 256, 16 workgroups:
 // 6.4 and 4.7; N = 2560, 160 workgroups: 6.8 and 7.2).  In groups of two workgroups, whose chains are short, the busiest
-// XCD's share of the workgroups of 16 rows counts (three to a CU; groups of 128, D = 128: 11 sequences, 88 workgroups,
-// 14.9 and 13.2; 16, 128 workgroups, 15.2 and 17.5).  And not for long runs, which the tiles in LDS serve better than the
+// XCD's share of the workgroups of 16 rows counts (three to a CU, D = 64 four; groups of 128, D = 128: 11 sequences, 88
+// workgroups, 14.9 and 13.2; 16, 128 workgroups, 15.2 and 17.5; D = 64 10.1 and 10.0).  And not for long runs, which the tiles in LDS serve better than the
 // caches (H = 2, one group, D = 128: N = 4500 491 and 456, 5500 626 and 676; D = 64, H = 1: 10000 1046 and 1033,
 // 16000 2366 and 2611).
 bool small_fwd(const KArgs& a) {
   const int n_seq = a.B * a.H * a.NG;
   const long long n = (long long)n_seq * ragged_tiles(a, kWgRows);
   if (n > (a.G > kWgRows ? 256 : 64) || (long long)a.G * a.D > 4608 * 128) return false;
-  return a.G > 2 * kWgRows || most_of_an_xcd(n_seq) * ((a.G + 15) / 16) <= 96;
+  return a.G > 2 * kWgRows || most_of_an_xcd(n_seq) * ((a.G + 15) / 16) <= (a.D == 64 ? 128 : 100);
 }
 // Backward, which reads every tile in four or five forms there, from the caches: up to half a workgroup per CU
 // in groups of more than 256, groups of a few tiles an eighth (of 250 to 256 three eighths) unless several query heads

@@ -40,7 +40,7 @@ def test_few_rows(B, N, H, Hkv, G, D):
     (1, 2048, 4, 4, 256), (1, 2304, 4, 4, 256),     # two sizes beyond the backward's
     (1, 1536, 4, 4, 256), (1, 1792, 4, 4, 256),     # backward 96 | 112
     (1, 1920, 4, 4, 320), (1, 2240, 4, 4, 320),     # backward 120 | 140
-    (1, 3072, 4, 4, 128), (1, 3328, 4, 4, 128),     # forward 12 | 13 sequences of an XCD, 96 | 104 workgroups of 16 rows
+    (1, 3072, 4, 4, 128), (1, 3328, 4, 4, 128),     # forward, D = 128: 12 | 13 sequences of an XCD, 96 | 104 workgroups of 16 rows
     (1, 1024, 8, 2, 128), (1, 1152, 8, 2, 128),     # the same, four query heads per kv head
     (1, 8000, 2, 2, 1000), (1, 9000, 2, 2, 1000),   # both 256 | 288
     (1, 2048, 2, 2, 2048), (1, 2080, 2, 2, 2080),   # backward, one group: 32 | 33 workgroups of an XCD
