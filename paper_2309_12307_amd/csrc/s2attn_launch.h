@@ -45,6 +45,35 @@ inline int pad_to(int n, int il) { return (n + il - 1) / il * il; }
 // Sequences of the XCD that gets the most of n_seq: whole sequences are dealt round the eight.
 inline int most_of_an_xcd(int n_seq) { return (n_seq + 7) / 8; }
 
+// Sequences of T tiles that an XCD with `each` of them walks together, `want` or more (one walk where it has fewer).
+// A last walk of one or two starts its heaviest tiles when nothing is left to run beside them, so the walks are even
+// ones: forward, us, walks of `want` and these, H = 32, Hkv = 16, D = 64, N = 6144, G = 1536 (three sequences, 2 + 1 and 3)
+// 70 and 49; H = 32, N = 2304, G = 768 (twelve, 11 + 1 and 12) 32 and 25; backward, H = 8, N = 7168, G = 1792 127 and
+// 106; H = 40, Hkv = 20, N = 2520, G = 1260 188 and 147.  Where the even walks leave a last one less than three quarters
+// full, or less full than walks of `want` do, the latter where theirs is three quarters full, longer ones otherwise
+// (forward, walks of `want`, even ones, these: H = 8, Hkv = 1, N = 25536, G = 3648, Variant 2, seven sequences, three walks
+// of 2 and a 1, two of 3 and a 1, 4 + 3, 206, 222 and 197; H = 40, Hkv = 10, D = 64, N = 10764, G = 5382, ten, 370, 380 and 336;
+// H = 40, Hkv = 20, N = 17056, G = 1312, 65, ten of 6 and a 5, nine of 7 and a 2 321 and 328).
+// Sequences of up to four tiles have little left to lose in a last walk that is half full (H = 8, G = 384, N = 14976: 39 of
+// three, 22 + 17 and 39, 28.6 and 30.8; G = 256, N = 20480: 80 of two, 32 + 32 + 16 and 40 + 40, 34.3 and 36.9); nor have five or
+// six in a second one five eighths full where one walk of all would read twice the K and V that the XCD's L2 holds (no
+// heads that share them, 64 slots: G = 640, N = 16000, 25 of five, 13 + 12 and 25, 36.7 and 38.9; G = 768, N = 13824, 18 of
+// six, 11 + 7 and 18, 36.5 and 38.2; but four heads to a kv head, B = 2, H = 16, G = 714, 20 of six, 37.3 and 35.7).
+inline int walk_of(int T, int each, int share, int slots) {
+  const int want = interleave_for(T, slots);
+  if (each <= want) return each;
+  const int rest = each % want, walks = each / want;
+  if (rest == 0 || (T <= 4 && 2 * rest >= want)) return want;
+  if (T <= 6 && walks == 1 && share == 1 && slots <= 64 && 8 * rest >= 5 * want) return want;
+  auto last = [&](int il) { return (each - 1) % il + 1; };
+  const int even = (each + walks - 1) / walks;
+  if (4 * last(even) >= 3 * even && last(even) * want >= rest * even) return even;
+  if (4 * rest >= 3 * want) return want;
+  for (int il = even; il <= 2 * want; ++il)
+    if (4 * last(il) >= 3 * il) return il;
+  return last(even) * want >= rest * even ? even : want;
+}
+
 // Grid of a launch with n_seq sequences of T tiles, neighbouring `share` of which (a divisor of
 // n_seq) read the same K and V, on XCDs that hold `slots` workgroups at a time.  A bundle is the
 // largest piece of the `share` that deals every XCD the same number of sequences; one sequence
@@ -58,18 +87,7 @@ inline Grid grid_of(int T, int n_seq, int share, int slots) {
   for (int m = share; m > 1; --m)
     if (share % m == 0 && n_seq / m % 8 == 0) { bundle = m; break; }
   const int each = (n_seq / bundle + 7) / 8 * bundle;   // sequences of one XCD
-  const int want = interleave_for(T, slots);
-  // An XCD's sequences go in walks of `want` or more, as even as they can be: a last walk of one or two starts its
-  // heaviest tiles when nothing is left to run beside them.  us, walks of `want` and even ones: forward, H = 32,
-  // Hkv = 16, D = 64, N = 6144, G = 1536 (three sequences, 2 + 1 and 3) 70 and 49; H = 32, N = 2304, G = 768 (twelve,
-  // 11 + 1 and 12) 32 and 25; backward, H = 8, N = 7168, G = 1792 127 and 106; H = 40, Hkv = 20, N = 2520, G = 1260 188
-  // and 147.  Not where a sequence has few tiles and the last walk fills half the slots or more, as it then has little left
-  // to lose: forward, H = 8, G = 384, N = 14976 (39 of three tiles, 22 + 17 and 39) 28.6 and 30.8; G = 256, N = 20480 (80
-  // of two, 32 + 32 + 16 and 40 + 40) 34.3 and 36.9; with eight tiles 1.02 to 1.14 for even walks.  58 shapes of two to
-  // twelve tiles: 1.09 (forward) and 1.03 (backward) in the mean over walks of `want`, worst 0.97.
-  const bool uneven = T <= 4 && each > want && 2 * (each % want) >= want;
-  const int walks = each > want ? each / want : 1;
-  const int il = uneven ? want : (each + walks - 1) / walks;
+  const int il = walk_of(T, each, share, slots);
   return Grid{8 * T * pad_to(each, il), Deal{n_seq, bundle, il, div_by(bundle), div_by(il), div_by(T * il)}};
 }
 
