@@ -188,7 +188,7 @@ __device__ __forceinline__ float diag_cols(f32x4 d, int lane) {
   return __shfl(x, 16 * (c16 >> 2) + c16);
 }
 
-__global__ void __launch_bounds__(64 * kWaves, 2) fwd_small_kernel(KArgs a, int T, Deal deal, int first_block) {
+__global__ void __launch_bounds__(64 * kWaves, 1) fwd_small_kernel(KArgs a, int T, Deal deal, int first_block) {
   __shared__ __attribute__((aligned(1024))) char smem[kSmemFwd];
   __shared__ float max_s[kWaves][kRows], sum_s[kWaves][kRows];
   fetch_args(a, deal);
