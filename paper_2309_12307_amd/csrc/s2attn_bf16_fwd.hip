@@ -8,8 +8,7 @@
 //   online softmax     queries are lane-indexed, keys register-indexed, so row max and
 //                      row sum are in-lane reductions plus one exchange with lane^32;
 //                      the running maximum is only raised (and O rescaled) when it
-//                      grows by more than 2^8, which keeps exp2 arguments <= 8 (eight-wave
-//                      kernel: when a lane's sum over its 32 keys of a tile grows beyond 2^32)
+//                      grows by more than 2^8, which keeps exp2 arguments <= 8
 //   O^T += V^T P^T     A = V^T through transposing LDS reads, B = P^T straight from the
 //                      S^T accumulators (no cross-lane movement)
 // K/V tiles go global -> LDS directly (global_load_lds, 16 bytes per lane) into two
@@ -25,7 +24,6 @@ namespace {
 constexpr int BN = 64;                       // keys per tile
 constexpr int kTileBytes = BN * kRowBytes;   // 16 KB
 constexpr float kRescaleThreshold = 8.f;     // log2 units
-constexpr float kRescaleSum = 4294967296.f;  // of a lane's 32 probabilities (fwd_softmax_long)
 
 struct FwdState {
   f32x16 o_acc[4];
@@ -82,6 +80,12 @@ __device__ __forceinline__ void fwd_scores(f32x16& s0, f32x16& s1, const bf16x8 
 
 // Online softmax of the tile: updates the running maximum lazily, accumulates the row
 // sum and packs the probabilities as the four 16-key B operands of the PV product.
+// The maximum of every tile is formed, sixteen instructions and a chain of ten.  Without it (a score far above the
+// running maximum shows in the row sum, and only then is the maximum formed and the exponentials taken again) N(0, 1)
+// inputs take 0.98 to 1.00 of the time, but others more, or P is rounded where it is not now: a row's largest P is 1 and
+// exact if the maximum was raised for it.  With the line at a sum of 2^8, as here, scores of standard deviation 3
+// take 1.04 of the time, of 8 1.12 (N = 8192, H = 32, G = 2048); at 2^12 of 8 1.05, and O is 5 % further from 64 bits at 16; at
+// 2^32 none takes longer, and dq leaves its bound.
 __device__ __forceinline__ void fwd_softmax(FwdState& st, f32x16& s0, f32x16& s1, float c2, bf16x8 (&pf)[4]) {
   // two independent three-input maximum chains
   float ma = fmaxf(s0[0], s0[1]), mb = fmaxf(s1[0], s1[1]);
@@ -115,58 +119,6 @@ __device__ __forceinline__ void fwd_softmax(FwdState& st, f32x16& s0, f32x16& s1
   pf[1] = pack8(s0[8], s0[9], s0[10], s0[11], s0[12], s0[13], s0[14], s0[15]);
   pf[2] = pack8(s1[0], s1[1], s1[2], s1[3], s1[4], s1[5], s1[6], s1[7]);
   pf[3] = pack8(s1[8], s1[9], s1[10], s1[11], s1[12], s1[13], s1[14], s1[15]);
-}
-
-// Probabilities of the tile relative to the running maximum, as the four 16-key B operands of the PV
-// product; returns this lane's part of their row sum.
-__device__ __forceinline__ float fwd_probs(const FwdState& st, const f32x16& s0, const f32x16& s1, float c2, bf16x8 (&pf)[4]) {
-  const float mc = st.m_run * c2;
-  float ra = 0.f, rb = 0.f;
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    float x[8], y[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      x[e] = __builtin_amdgcn_exp2f(fmaf(s0[8 * t + e], c2, -mc));
-      y[e] = __builtin_amdgcn_exp2f(fmaf(s1[8 * t + e], c2, -mc));
-      ra += x[e];
-      rb += y[e];
-    }
-    pf[t] = pack8(x[0], x[1], x[2], x[3], x[4], x[5], x[6], x[7]);
-    pf[2 + t] = pack8(y[0], y[1], y[2], y[3], y[4], y[5], y[6], y[7]);
-  }
-  return ra + rb;
-}
-
-// The same update without looking for the maximum of every tile: a score far above the running maximum
-// shows in the row sum, which is needed anyway, and only then (and at the first tile) is the maximum formed, O
-// rescaled and the probabilities formed again.  Sixteen instructions and a chain of ten less a tile, for
-// long sequences of tiles.  (Eight tiles, G = 512: the first one's second pass costs 1.9 %.)
-// The second pass is dear, and any of a wave's 32 rows asks for it, so the line is far out: P keeps its bits at any
-// size, and with 2^32 a row, O and l stay finite for v up to 2^80.  Against a maximum per tile, N = 8192, H = 32,
-// G = 2048, and N = 32768, H = 8 in one group, with lines of 2^12, 2^24 and 2^32: N(0, 1) 1.00, 1.01, 1.01 and 1.01, 1.01, 1.01 times
-// as fast; scores of standard deviation 8 0.96, 1.11, 1.13 and 1.01, 1.03, 1.05; of 16 0.91, 1.00, 1.06 and 0.99, 1.03, 1.05;
-// scores that rise by e^8 from tile to tile 0.87, 1.02, 1.06 and 0.87, 0.98, 1.06.
-__device__ __forceinline__ void fwd_softmax_long(FwdState& st, const f32x16& s0, const f32x16& s1, float c2, bf16x8 (&pf)[4]) {
-  float sum = fwd_probs(st, s0, s1, c2, pf);
-  if (__builtin_amdgcn_ballot_w64(!(sum <= kRescaleSum)) != 0) {
-    float ma = fmaxf(s0[0], s0[1]), mb = fmaxf(s1[0], s1[1]);
-#pragma unroll
-    for (int v = 2; v < 16; v += 2) {
-      ma = fmaxf(fmaxf(ma, s0[v]), s0[v + 1]);
-      mb = fmaxf(fmaxf(mb, s1[v]), s1[v + 1]);
-    }
-    const float m_new = fmaxf(st.m_run, max_halves(fmaxf(ma, mb)));
-    const float alpha = __builtin_amdgcn_exp2f((st.m_run - m_new) * c2);
-    st.m_run = m_new;
-    st.l_run *= alpha;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) st.o_acc[db][v] *= alpha;
-    sum = fwd_probs(st, s0, s1, c2, pf);
-  }
-  st.l_run += sum;
 }
 
 // O^T += V^T P^T for the whole 64-key tile.
@@ -487,7 +439,7 @@ fwd_bf16_pp_kernel(KArgs a, int T, Deal deal) {
   __syncthreads();
   if (n_lo <= 0 && 0 <= n_hi) {
     fwd_scores(s0, s1, qf, smem, lo, jt_first * BN, qrow, g32, jt_first * BN + BN - 1 > qw0);
-    if (grp == 0) fwd_softmax_long(st, s0, s1, c2, pf);
+    if (grp == 0) fwd_softmax(st, s0, s1, c2, pf);
     pp_load<0>(ring[0], smem + kTileBytes, nullptr, lo);     // first two steps of P(0) V(0)
     pp_load<1>(ring[1], smem + kTileBytes, nullptr, lo);
   }
@@ -502,7 +454,7 @@ fwd_bf16_pp_kernel(KArgs a, int T, Deal deal) {
     const char* Vs_cur = smem + st_cur * kStageBytes + kTileBytes;
     const char* Ks_nxt = smem + st_nxt * kStageBytes;
     const char* Vs_nxt = Ks_nxt + kTileBytes;
-    if (grp == 1 && act) fwd_softmax_long(st, s0, s1, c2, pf);
+    if (grp == 1 && act) fwd_softmax(st, s0, s1, c2, pf);
     // Every step issues the LDS reads of the step two ahead, then its own four MFMAs.  The
     // matrix block runs at raised priority so that it is not starved by the vector work of
     // the wave it shares the SIMD with.
@@ -543,7 +495,7 @@ fwd_bf16_pp_kernel(KArgs a, int T, Deal deal) {
       __builtin_amdgcn_s_setprio(0);
       const int j0 = (jt_first + n + 1) * BN;
       if (j0 + BN - 1 > qw0) mask_scores(s0, s1, j0, qrow, g32);
-      if (grp == 0) fwd_softmax_long(st, s0, s1, c2, pf);
+      if (grp == 0) fwd_softmax(st, s0, s1, c2, pf);
     }
     __builtin_amdgcn_s_setprio(0);
     const int t = st_cur; st_cur = st_nxt; st_nxt = st_free; st_free = t;
