@@ -92,6 +92,12 @@ def check_bf16_tensor(name, got, ref):
     return float(err.max()), float((err - half_ulp_bf16(ref)).max())
 
 
+def beyond_few_rows(B, N, H, G, dtype):
+    """More workgroups (of 32 rows in bf16, of 64 in fp32) than any rule hands to the kernels for few rows: forward and
+    backward then run the others.  bf16: D = 128; D = 64 has none for few rows."""
+    return B * H * (N // G) * -(-G // (32 if dtype == "bf16" else 64)) > 256
+
+
 def max_abs(a, b):
     return float(np.max(np.abs(np.asarray(a, dtype=np.float64) - np.asarray(b, dtype=np.float64))))
 

@@ -10,11 +10,23 @@ from paper_2309_12307_amd import inputs
 pytestmark = pytest.mark.gpu
 
 # (dtype, B, N, H, Hkv, D, G)
-CASES = [
+FEW_ROWS = [
     ("f32", 1, 300, 4, 2, 64, 100),
-    ("bf16", 1, 1024, 4, 2, 128, 256),     # tile-aligned kernels
-    ("bf16", 1, 600, 4, 4, 128, 200),      # unaligned kernels
+    ("bf16", 1, 1024, 4, 2, 128, 256),
+    ("bf16", 1, 600, 4, 4, 128, 200),      # tiles that are not full
 ]
+MANY_ROWS = [
+    ("f32", 1, 3300, 4, 2, 64, 100),
+    ("bf16", 1, 2304, 4, 2, 128, 256),     # tile-aligned kernels
+    ("bf16", 1, 2000, 4, 4, 128, 200),     # partial tiles
+    ("bf16", 1, 6144, 2, 2, 128, 2048),    # eight-wave forward
+]
+CASES = FEW_ROWS + MANY_ROWS
+
+
+def test_which_kernels_the_cases_reach():
+    from gpu_util import beyond_few_rows
+    assert all(beyond_few_rows(B, N, H, G, dtype) == (case in MANY_ROWS) for case in CASES for dtype, B, N, H, _, _, G in [case])
 
 
 def scaled_inputs(dtype, B, N, H, Hkv, D, seed, **factor):

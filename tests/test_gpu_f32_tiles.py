@@ -1,4 +1,5 @@
-"""fp32 kernels at the edges of their tiles (16 rows a wave, 32 a staged tile, 64 a workgroup):
+"""fp32 kernels at the edges of their tiles (16 rows a wave, 32 a staged tile, 64 a workgroup; few rows: 16 a tile), on
+grids that the kernels for few rows take and on the fewest groups beyond:
 group sizes one step below, at and above each, the smallest group, several heads per kv head
 and the wrap-around group cut off any tile boundary, against the oracle.  Bound: the 1e-4
 max-abs of the fp32 mode (products and sums are fp32, so single elements err by some 1e-6)."""
@@ -13,9 +14,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("G", [2, 14, 16, 18, 30, 32, 34, 62, 64, 66, 126, 130, 322])
-def test_group_sizes_around_the_tiles(G, D):
-    from gpu_util import max_abs, run_hip
-    B, N, H, Hkv = 1, 3 * G, 4, 2
+@pytest.mark.parametrize("few", [True, False])
+def test_group_sizes_around_the_tiles(G, D, few):
+    from gpu_util import beyond_few_rows, max_abs, run_hip
+    B, H, Hkv = 1, 4, 2
+    N = G * (3 if few else 256 // (H * -(-G // 64)) + 1)
+    assert beyond_few_rows(B, N, H, G, "f32") != few
     inp = inputs.make_inputs(B, N, H, Hkv, D, seed=500 + G + D, dtype="f32")
     for kw, okw in ((dict(), dict()), (dict(wrap_variant=2, shift=G // 2 + 1), dict(variant2=True, shift=G // 2 + 1))):
         if kw and G // 2 + 1 >= G:
@@ -29,14 +33,16 @@ def test_group_sizes_around_the_tiles(G, D):
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("low", [-np.inf, -3e38])
 @pytest.mark.parametrize("n_low", [8, 32, 40])
-def test_first_scores_of_a_row_minus_infinity(D, low, n_low):
+@pytest.mark.parametrize("H", [2, 66])     # few rows (tiles of 16 keys), and the kernels beyond (32)
+def test_first_scores_of_a_row_minus_infinity(D, low, n_low, H):
     """The first keys of every group score -inf (or the lowest finite numbers): rows that see any
-    other key are softmax over the others, whether the low keys are part of their first tile of 32
-    keys, all of it, or reach into the second."""
+    other key are softmax over the others, whether the low keys are part of their first tile,
+    all of it, or reach into the second."""
     import torch
-    from gpu_util import to_dev, to_np
+    from gpu_util import beyond_few_rows, to_dev, to_np
     from paper_2309_12307_amd import binding
-    N, H, G = 256, 2, 128
+    N, G = 256, 128
+    assert beyond_few_rows(1, N, H, G, "f32") == (H > 2)
     rng = np.random.default_rng(77)
     q, k, v = (rng.standard_normal((1, N, H, D)).astype(np.float32) for _ in range(3))
     q[..., 0] = np.abs(q[..., 0]) + 0.5

@@ -160,9 +160,11 @@ def test_shift_rules(rule, name):
     compare(out, ref)
 
 
-def test_custom_shift_and_scale():
-    from gpu_util import run_hip
-    B, N, H, Hkv, D, G = 1, 1536, 4, 4, 128, 512
+@pytest.mark.parametrize("N", [1536, 2560])     # few rows, and the kernels beyond
+def test_custom_shift_and_scale(N):
+    from gpu_util import beyond_few_rows, run_hip
+    B, H, Hkv, D, G = 1, 4, 4, 128, 512
+    assert beyond_few_rows(B, N, H, G, "bf16") == (N > 1536)
     inp = inputs.make_inputs(B, N, H, Hkv, D, seed=180, dtype="bf16")
     out = run_hip(inp, G, "bf16", shift=128, scale=0.05)
     ref = orc.s2attn_fwd_bwd(inp["q"], inp["k"], inp["v"], inp["do"], G, shift=128, scale=0.05)

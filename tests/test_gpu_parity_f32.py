@@ -77,9 +77,11 @@ def test_shift_rules(rule, name):
     compare(out, ref)
 
 
-def test_custom_shift_and_scale():
-    from gpu_util import run_hip
-    B, N, H, Hkv, D, G = 1, 384, 4, 4, 64, 128
+@pytest.mark.parametrize("N", [384, 4224])      # few rows, and the kernels beyond
+def test_custom_shift_and_scale(N):
+    from gpu_util import beyond_few_rows, run_hip
+    B, H, Hkv, D, G = 1, 4, 4, 64, 128
+    assert beyond_few_rows(B, N, H, G, "f32") == (N > 384)
     inp = inputs.make_inputs(B, N, H, Hkv, D, seed=80, dtype="f32")
     out = run_hip(inp, G, "f32", shift=40, scale=0.2)
     ref = orc.s2attn_fwd_bwd(inp["q"], inp["k"], inp["v"], inp["do"], G, shift=40, scale=0.2)
@@ -97,7 +99,8 @@ def test_variant2_split_wrap_group(shape):
     compare(out, ref)
 
 
-@pytest.mark.parametrize("shape", [(2, 256, 4, 4, 64, 64), (1, 300, 6, 3, 64, 100), (1, 140, 2, 1, 128, 70)])
+@pytest.mark.parametrize("shape", [(2, 256, 4, 4, 64, 64), (1, 300, 6, 3, 64, 100), (1, 140, 2, 1, 128, 70),
+                                   (1, 2200, 6, 3, 64, 100), (1, 2310, 4, 2, 128, 70)])     # the last two: beyond few rows
 def test_packed_qkv_views(shape):
     """q, k, v (and dq, dk, dv) as strided views of one packed projection tensor."""
     from gpu_util import run_hip_packed
@@ -127,6 +130,8 @@ SHARDINGS = [
     ((1, 256, 8, 4, 64, 64), [(0, 2), (2, 8)]),
     ((2, 200, 12, 3, 64, 100), [(0, 4), (4, 8), (8, 12)]),   # middle head 6 splits kv head 1
     ((1, 256, 6, 6, 128, 128), [(0, 3), (3, 6), (1, 6)]),     # odd shards
+    ((1, 3300, 12, 3, 64, 100), [(4, 8)]),                    # beyond few rows, the middle head in the shard's kv head
+    ((1, 2970, 6, 6, 128, 66), [(3, 6)]),
 ]
 
 
