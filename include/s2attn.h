@@ -197,7 +197,8 @@ S2ATTN_API int s2attn_bwd_ex_static(const s2attn_params* p, void* stream);
 
 /* Measurement aid: s2attn_bwd_ex that also records up to four caller-owned HIP events
  * (hipEvent_t passed as void*, entries may be NULL) on `stream`: events[0] before the
- * delta pre-pass, [1] after it, [2] after the dK/dV kernel (small shapes run dK/dV and dQ in one
+ * delta pre-pass, [1] after it (fp32 and problems of few rows form delta in the backward kernel: nothing lies between
+ * the two), [2] after the dK/dV kernel (small shapes run dK/dV and dQ in one
  * launch: after both), [3] after the dQ kernel
  * (and the partial-sum pass, when present).  Same semantics and errors otherwise. */
 S2ATTN_API int s2attn_bwd_ex_marked(const s2attn_params* p, void* stream, void* const* events);

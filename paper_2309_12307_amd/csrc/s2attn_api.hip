@@ -62,9 +62,11 @@ size_t workspace_bytes_least(int B, int N, int H, int Hkv, int D, bool mixed) {
 // Estimated time (us) of dK/dV, dQ and the summing of the partials when the query heads of a kv head
 // are cut into `parts`: the longest chain of tiles of a dK/dV workgroup (the first keys of a group, all
 // rows of a part) against the work per CU, to which the end of a grid adds a share of a chain, and the
-// partials, written by dK/dV and read back.  The rates are those of the kernels, and all constants fit
-// backward times measured with 1, 2, 4 ... 32 parts at 780 shapes (2 to 511 workgroups uncut, G = 32 to
-// 8192, 2 to 32 query heads to a kv head).
+// partials, written by dK/dV and read back.  The rates are those of the kernels of 64 to 128 keys to a dK/dV workgroup,
+// and all constants fit their backward times measured with 1, 2, 4 ... 32 parts at 780 shapes (2 to 511 workgroups uncut,
+// G = 32 to 8192, 2 to 32 query heads to a kv head).  The few-row kernels (32 and 16 keys, the chain shared by four waves)
+// take the number that comes out; at 22 of their shapes it was the fastest of those up to it (H = 8, Hkv = 2, N = 1024, us with
+// 1, 2 and 4 parts: G = 1024 75, 46 and 36.5; G = 512 41.5 and 29; fp32, D = 64, G = 256 48, 33 and 30).
 double bwd_estimate_us(const s2attn_params* p, int parts) {
   struct Kind {
     double cu_rate, share;       // flop per us and CU; what one workgroup of it reaches alone

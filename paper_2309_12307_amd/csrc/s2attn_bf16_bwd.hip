@@ -458,9 +458,9 @@ int launch_bwd_dq_bf16(const KArgs& a, hipStream_t st) {
 
 // dK/dV and dQ in one launch where that is faster; 1: not for this shape, launch them one by one.
 // Up to six workgroups per CU: the chip is not full, or a good part of the time goes into the tails
-// of the two launches, which here lie beside each other.  Forward + backward, H = 4, Hkv = 2,
-// N = 1024: 41.2 us one by one, 30.5 in one launch; H = 8, N = 4096: 86.8 and 72.4; H = 32, Hkv = 1,
-// N = 8192: 665 and 654; H = 8, N = 16384 (1536 workgroups): 629 and 615.  With more workgroups
+// of the two launches, which here lie beside each other.  Backward, us, one by one and in one launch: H = 8, N = 2048,
+// G = 256 26.2 and 18.6; N = 4096, G = 1024 62.0 and 45.9; H = 32, Hkv = 1, N = 8192 513 and 500; H = 8, N = 16384 (1536
+// workgroups) 482 and 466.  With more workgroups
 // nothing is gained (H = 32, N = 8192, 3072 workgroups: 719 and 719) or lost to the eight-wave
 // dQ (H = 64, Hkv = 8, N = 32768: 18.25 and 18.70 ms).
 // Groups of 128 and less leave half or more of dQ's 256 rows empty, so they share a launch only up to 700
@@ -478,6 +478,7 @@ int launch_bwd_both_bf16(const KArgs& a, hipStream_t st) {
   const int T_kv = partial ? ragged_tiles(a, 128) : a.G / 128, T_q = partial ? ragged_tiles(a, 256) : a.G / 256;
   const Grid kv = grid_of(T_kv, a.B * a.Hkv * a.NG * a.parts, 1, 32);
   const Grid q = grid_of(T_q, a.B * a.H * a.NG, a.r, 32);
+  // counted with the padding of the XCDs and of the last walks (7 % of a grid in the mean, 16 % in one of ten)
   if (kv.blocks + q.blocks > kOneLaunchBlocks) return 1;
   if (a.G <= 128 && a.r < 16 && a.B * a.NG * (a.Hkv * a.parts * T_kv + a.H * T_q) > (a.r < 8 ? 700 : 1100)) return 1;
   const int kv_first = 2 * a.r >= 3 * a.parts;

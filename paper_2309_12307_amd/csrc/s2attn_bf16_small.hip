@@ -538,7 +538,8 @@ bwd_small_kernel(KArgs a, int n_kv, int T, Deal deal_kv, Deal deal_q, int first_
 
 static long long small_blocks(const KArgs& a) { return (long long)a.B * a.H * a.NG * ragged_tiles(a, kRows); }
 
-// Up to one workgroup of 32 rows per CU, for the workgroups of 128 (256) rows share a tile between four (eight)
+// Up to as many workgroups of 32 rows as there are CUs (fewer than eight sequences keep to as many XCDs), for the
+// workgroups of 128 (256) rows share a tile between four (eight)
 // waves and so need a quarter of the loads once the chip is full; and not for chains so long that these are
 // the faster loop.  Forward, us, workgroups of 128 or 256 rows and here: H = 4, groups of 256, N = 1024 (128
 // workgroups of 32 rows): 8.6 and 7.1; groups of 2048, N = 2048 (256): 45.7 and 29.7; groups of 4096, H = 2,

@@ -103,11 +103,15 @@ struct Deal {
   Div by_bundle, by_il, by_span;   // span: T * il
 };
 
-// Reads one word of every 64 bytes of a kernel's arguments and waits once.  The compiler loads arguments
-// where they are first used, in three or four steps that each wait for memory as long as the CU has not seen
-// them yet: 0.2 to 0.6 us of a launch (forward, N = 1024, H = 4, D = 64, G = 256: 7.3 -> 6.8 us; fp32, N = 256 4.7 ->
-// 4.1; dK/dV and dQ in one launch, N = 4096, H = 8, G = 1024 48.2 -> 46.3).  Not in the fp32 backward of 64 rows
-// and the D = 64 backwards, which have no registers left for what is then kept (2 % slower).
+// Reads one word of every 64 bytes of a kernel's KArgs and of the deal that follows them, and waits once.  The compiler
+// loads arguments where they are first used, in three or four steps that each wait for memory as long as the CU has not
+// seen them yet: 0.3 to 0.6 us of a launch (calls back to back, us without and with: forward, D = 64, N = 1024, H = 4,
+// G = 256 7.4 and 7.0; few rows, N = 1024, H = 4 7.5 and 7.2, fp32, N = 256 4.7 and 4.1; dK/dV and dQ in one launch, N = 4096,
+// H = 8, G = 1024 47.9 and 46.1; nothing at 100 us and more).  Kernels of two deals pass the second, and the 64 bytes that
+// hold most of the first stay out: reading them too changes nothing (102 backward shapes: 1.000).  The few-row backwards
+// spill 90 (bf16) and 48 (fp32) scalar registers with it, 75 and 40 without, and are 3 and 2 % faster all the same.  Not
+// in the other backwards: those of fp32 and of D = 64 and the shared launch on partial tiles have no registers left for what
+// is then kept (2 to 3 % slower), the separate dK/dV and dQ kernels are for large grids.
 __device__ __forceinline__ void fetch_args(const KArgs& a, const Deal& deal) {
   asm volatile("" :: "s"(a.q), "s"(a.dv), "s"(a.sk.t), "s"(a.sdk.b), "s"(a.so.b), "s"(a.by_NG.mul), "s"(deal.by_span.shift));
 }

@@ -24,7 +24,7 @@
 // N = 4096, H = 8, D = 128, G = 1024, forward + backward: plain fp32 fma kernels with a pre-pass
 // for delta took 2890 us (10 TFLOP/s of the 14 D flops per pair), these 386 us (78; executed 100
 // of the 154 TFLOP/s that a library fp32 product of 8192^3 reaches; forward 116 us and backward 272 with
-// the matrix unit busy 69 and 79 % of the time a CU works). 
+// the matrix unit busy 69 and 79 % of the time a CU works).
 // Problems of few rows: s2attn_f32_small.hip.
 #include <cfloat>
 

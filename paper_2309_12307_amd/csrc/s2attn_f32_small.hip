@@ -12,8 +12,9 @@
 // Forward and backward, us, 64 rows to a workgroup and here: N = 256, H = 4, D = 64, G = 64: 6.4 + 9.3 and
 // 4.7 + 7.1; N = 1000, H = 4, Hkv = 2, D = 128, G = 500: 44.7 + 85.0 and 16.7 + 62.0; N = 1024, H = 8, D = 64,
 // G = 1024: 53.8 + 92.7 and 23.1 + 64.0.  The backward reads a tile in five forms (40 KB for 4096 MFMA cycles
-// of four waves at D = 128), which is what the caches give once every CU has its workgroups: that is where
-// the lines at small_fwd and small_bwd lie.  Two waves to a tile (32 rows to a workgroup) is not faster anywhere
+// of four waves at D = 128), which is what the caches give once the CUs of an XCD have their workgroups (whole sequences go
+// to an XCD, so one sequence keeps to 32 CUs): the lines at small_fwd and small_bwd lie there, and at the length
+// from which the tiles in LDS feed a chain better.  Two waves to a tile (32 rows to a workgroup) is not faster anywhere
 // but between 128 and 256 workgroups of 64 rows (5 %).
 #include <cfloat>
 
