@@ -530,7 +530,7 @@ int launch_fwd_bf16(const KArgs& a, hipStream_t st) {
     return hipGetLastError() == hipSuccess ? 0 : -1;
   }
   const int T = a.ragged ? ragged_tiles(a, 128) : a.G / 128;
-  const Grid g = grid_of(T, n_seq, a.r, 64);     // 32 CUs per XCD, two workgroups each
+  const Grid g = grid_of(T, n_seq, a.r, 64, true);   // 32 CUs per XCD, two workgroups each
   if (a.ragged) return launch_blocks(fwd_bf16_kernel<true>, g.blocks, 256, st, a, T, g.deal);
   return launch_blocks(fwd_bf16_kernel<false>, g.blocks, 256, st, a, T, g.deal);
 }

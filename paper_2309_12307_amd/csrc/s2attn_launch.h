@@ -55,16 +55,17 @@ inline int most_of_an_xcd(int n_seq) { return (n_seq + 7) / 8; }
 // of 2 and a 1, two of 3 and a 1, 4 + 3, 206, 222 and 197; H = 40, Hkv = 10, D = 64, N = 10764, G = 5382, ten, 370, 380 and 336;
 // H = 40, Hkv = 20, N = 17056, G = 1312, 65, ten of 6 and a 5, nine of 7 and a 2 321 and 328).
 // Sequences of up to four tiles have little left to lose in a last walk that is half full (H = 8, G = 384, N = 14976: 39 of
-// three, 22 + 17 and 39, 28.6 and 30.8; G = 256, N = 20480: 80 of two, 32 + 32 + 16 and 40 + 40, 34.3 and 36.9); nor have five or
-// six in a second one five eighths full where one walk of all would read twice the K and V that the XCD's L2 holds (no
-// heads that share them, 64 slots: G = 640, N = 16000, 25 of five, 13 + 12 and 25, 36.7 and 38.9; G = 768, N = 13824, 18 of
-// six, 11 + 7 and 18, 36.5 and 38.2; but four heads to a kv head, B = 2, H = 16, G = 714, 20 of six, 37.3 and 35.7).
-inline int walk_of(int T, int each, int share, int slots) {
+// three, 22 + 17 and 39, 28.6 and 30.8; G = 256, N = 20480: 80 of two, 32 + 32 + 16 and 40 + 40, 34.3 and 36.9).  `crowded`, the
+// four-wave forward, which reads K and V fastest for what it computes: nor have five or six in a second walk five eighths
+// full where one walk of all would read twice the K and V that the XCD's L2 holds (G = 640, N = 16000, 25 of five, 13 + 12
+// and 25, 36.7 and 38.9; G = 768, N = 13824, 18 of six, 11 + 7 and 18, 36.5 and 38.2; but where bundles share them, B = 2, H = 16,
+// Hkv = 4, G = 714, 20 of six, 37.3 and 35.7; fp32, B = 2, H = 2, N = 14320, G = 358, Variant 2, backward, 238 and 214).
+inline int walk_of(int T, int each, int bundle, int slots, bool crowded) {
   const int want = interleave_for(T, slots);
   if (each <= want) return each;
   const int rest = each % want, walks = each / want;
   if (rest == 0 || (T <= 4 && 2 * rest >= want)) return want;
-  if (T <= 6 && walks == 1 && share == 1 && slots <= 64 && 8 * rest >= 5 * want) return want;
+  if (crowded && T <= 6 && walks == 1 && bundle == 1 && 8 * rest >= 5 * want) return want;
   auto last = [&](int il) { return (each - 1) % il + 1; };
   const int even = (each + walks - 1) / walks;
   if (4 * last(even) >= 3 * even && last(even) * want >= rest * even) return even;
@@ -82,12 +83,12 @@ struct Grid {
   int blocks;
   Deal deal;
 };
-inline Grid grid_of(int T, int n_seq, int share, int slots) {
+inline Grid grid_of(int T, int n_seq, int share, int slots, bool crowded = false) {
   int bundle = 1;
   for (int m = share; m > 1; --m)
     if (share % m == 0 && n_seq / m % 8 == 0) { bundle = m; break; }
   const int each = (n_seq / bundle + 7) / 8 * bundle;   // sequences of one XCD
-  const int il = walk_of(T, each, share, slots);
+  const int il = walk_of(T, each, bundle, slots, crowded);
   return Grid{8 * T * pad_to(each, il), Deal{n_seq, bundle, il, div_by(bundle), div_by(il), div_by(T * il)}};
 }
 
