@@ -463,9 +463,9 @@ int launch_bwd_t(const KArgs& a, bool dq_last, hipStream_t st) {
 // groups of one workgroup or less up to a quarter of that (groups of 64, H = 4, D = 64, N = 256, 16 workgroups:
 // 6.4 and 4.7; N = 2560, 160 workgroups: 6.8 and 7.2).  In groups of two workgroups, whose chains are short, the busiest
 // XCD's share of the workgroups of 16 rows counts (three to a CU, D = 64 four; groups of 128, D = 128: 11 sequences, 88
-// workgroups, 14.9 and 13.2; 16, 128 workgroups, 15.2 and 17.5; D = 64 10.1 and 10.0).  And not for long runs, which the tiles in LDS serve better than the
-// caches (H = 2, one group, D = 128: N = 4500 491 and 456, 5500 626 and 676; D = 64, H = 1: 10000 1046 and 1033,
-// 16000 2366 and 2611).
+// workgroups, 14.9 and 13.2; 16, 128 workgroups, 15.2 and 17.5; D = 64 10.1 and 10.0).  And not for long runs, which the
+// tiles in LDS serve better than the caches (H = 2, one group, D = 128: N = 4500 491 and 456, 5500 626 and 676; D = 64,
+// H = 1: 10000 1046 and 1033, 16000 2366 and 2611).
 bool small_fwd(const KArgs& a) {
   const int n_seq = a.B * a.H * a.NG;
   const long long n = (long long)n_seq * ragged_tiles(a, kWgRows);
